@@ -153,13 +153,12 @@ __device__ __forceinline__ int first_diff_orbital(const uint64_t (&a)[NW], const
 // Hidden unit at position u when the units of a layer of width w are sorted by degree
 // (degree of unit j is (j mod (n-1)) + 1; ties keep ascending j). Returns -1 past w.
 __host__ __device__ inline int sorted_unit(int n, int w, int u) {
-  const int q = n - 1;
-  for (int r = 0; r < q; ++r) {
-    const int cnt = (w > r) ? (w - r - 1) / q + 1 : 0;
-    if (u < cnt) return r + u * q;
-    u -= cnt;
-  }
-  return -1;
+  if (u >= w) return -1;
+  // degree r + 1 has full + 1 units r, r + q, ... for r < rem, else full
+  const int q = n - 1, full = w / q, rem = w % q, head = rem * (full + 1);
+  const int r = u < head ? u / (full + 1) : rem + (u - head) / full;
+  const int i = u < head ? u % (full + 1) : (u - head) % full;
+  return r + i * q;
 }
 
 // Eight occupation bits starting at bit `pos` (orbitals pos/2 .. pos/2 + 3).
@@ -290,15 +289,17 @@ __device__ __forceinline__ void build_ctx(const SysDev& S, const uint64_t (&x)[N
     if (lane == w) c.x[w] = x[w];
 }
 
-// Diagonal energy and the value of every single excitation of one sample (one wave; the
-// occupied/virtual lists `c` must be visible to the whole wave):
+// Diagonal energy and the value of every single excitation of one sample (one wave, or with
+// parts > 1 that many: wave `part` takes every parts-th group of singles, each computes the
+// diagonal; the occupied/virtual lists `c` must be visible to the whole wave):
 //   E_diag = sum_p n_p h_pp + 1/2 sum_pq [n_p n_q (pp|qq) - sum_s n_ps n_qs (pq|qp)]
 //   F_ai   = h_ai + sum_p n_p (ai|pp) - sum_p n_{p,s} (ap|pi)        (i -> a of spin s)
 // Writes F[0 .. nSa + nSb) (single index as in the canonical list) and returns E_diag
 // (the same value in every lane). Sums run in a fixed order (bitwise repeatable).
 template <int NW>
 __device__ __forceinline__ double sample_terms(const SysDev& S, const uint64_t (&xv)[NW], const SampleCtx& c,
-                                               int lane, double* __restrict__ Fb) {
+                                               int lane, double* __restrict__ Fb, int part = 0,
+                                               int parts = 1) {
   const int n = S.n;
   double e = 0.0;
   if (lane < n) {
@@ -322,7 +323,7 @@ __device__ __forceinline__ double sample_terms(const SysDev& S, const uint64_t (
   // contiguous table row together), then a 3-step lane reduction
   const uint32_t nS = S.nSa + S.nSb;
   const int sub = lane >> 3, pg = lane & 7;
-  for (uint32_t u0 = 0; u0 < nS; u0 += 8) {
+  for (uint32_t u0 = 8u * (uint32_t)part; u0 < nS; u0 += 8u * (uint32_t)parts) {
     const uint32_t u = u0 + sub;
     const bool valid = u < nS;
     const uint32_t uu = valid ? u : 0;

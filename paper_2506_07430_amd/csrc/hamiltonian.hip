@@ -1,5 +1,7 @@
 // Integral tables, per-sample diagonal/single terms, the materialised connected list
 // and the sample check.
+#include <algorithm>
+
 #include "elocal_internal.hpp"
 #include "kernels.hpp"
 
@@ -35,13 +37,17 @@ __device__ __forceinline__ void load_x(const uint64_t* __restrict__ x, int64_t b
   for (int w = 0; w < NW; ++w) xv[w] = x[b * NW + w];
 }
 
-// One wave per sample (per-sample terms: see sample_terms in elocal_internal.hpp).
+// `parts` waves per sample (per-sample terms: see sample_terms in elocal_internal.hpp). A wave's
+// singles are a chain of dependent table reads, so a small batch is bound by their latency
+// (60 orbitals, 32 samples, one wave each: 494 us); the launcher splits it over more waves.
 template <int NW>
-__global__ void __launch_bounds__(256) k_prep(SysDev S, const uint64_t* __restrict__ x, int64_t B,
+__global__ void __launch_bounds__(256) k_prep(SysDev S, const uint64_t* __restrict__ x, int64_t B, int parts,
                                               double* __restrict__ ediag, double* __restrict__ F) {
   __shared__ SampleCtx ctxs[4];
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  const int64_t b = (int64_t)blockIdx.x * 4 + wid;
+  const int64_t wave = (int64_t)blockIdx.x * 4 + wid;
+  const int64_t b = wave / parts;
+  const int part = (int)(wave % parts);
   if (b >= B) return;
   SampleCtx& c = ctxs[wid];
   uint64_t xv[NW];
@@ -49,8 +55,8 @@ __global__ void __launch_bounds__(256) k_prep(SysDev S, const uint64_t* __restri
   build_ctx<NW>(S, xv, c, lane);
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  const double e = sample_terms<NW>(S, xv, c, lane, F + (size_t)b * (S.nSa + S.nSb));
-  if (lane == 0) ediag[b] = e;
+  const double e = sample_terms<NW>(S, xv, c, lane, F + (size_t)b * (S.nSa + S.nSb), part, parts);
+  if (lane == 0 && part == 0) ediag[b] = e;
 }
 
 // One list entry: x' = the excitation applied to x, H_{x x'} with its sign, the sign, and the
@@ -221,9 +227,12 @@ hipError_t launch_build_tables(int n, const double* eri, double* S, double* J2, 
 hipError_t launch_prep(const SysDev& S, const uint64_t* x, int64_t B, double* ediag, double* F,
                        hipStream_t st) {
   if (B <= 0) return hipSuccess;
-  const unsigned blocks = (unsigned)((B + 3) / 4);
-  if (S.W == 1) hipLaunchKernelGGL(k_prep<1>, dim3(blocks), dim3(256), 0, st, S, x, B, ediag, F);
-  else hipLaunchKernelGGL(k_prep<2>, dim3(blocks), dim3(256), 0, st, S, x, B, ediag, F);
+  // enough waves to fill the chip (256 CUs of 16), at least two groups of eight singles each
+  const int64_t groups = (S.nSa + S.nSb + 7u) / 8u;
+  const int parts = (int)std::max<int64_t>(1, std::min<int64_t>((groups + 1) / 2, 4096 / B));
+  const unsigned blocks = (unsigned)((B * parts + 3) / 4);
+  if (S.W == 1) hipLaunchKernelGGL(k_prep<1>, dim3(blocks), dim3(256), 0, st, S, x, B, parts, ediag, F);
+  else hipLaunchKernelGGL(k_prep<2>, dim3(blocks), dim3(256), 0, st, S, x, B, parts, ediag, F);
   return hipGetLastError();
 }
 

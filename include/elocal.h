@@ -386,11 +386,14 @@ elocal_status elocal_tune(elocal_t h, int param, int64_t value);
  * kernel variant is built for, ELOCAL_INFO_ITEMS work items, ELOCAL_INFO_LDS_BYTES LDS per
  * block, ELOCAL_INFO_INPLACE 1 when the hidden layers are updated in place (one activation
  * array in registers; chosen when every hidden o-block pair j reads k-blocks j + 1 to j + 2
- * only), else 0.
+ * only), else 0; ELOCAL_INFO_WS_BYTES the workspace with which the launch takes all its
+ * blocks (elocal_workspace_bytes is what a call needs: with less room than this the launch
+ * may take fewer blocks, with the same results).
  */
 enum {
   ELOCAL_INFO_GRID = 0, ELOCAL_INFO_GROUPS = 1, ELOCAL_INFO_WAVES = 2, ELOCAL_INFO_COLS = 3,
-  ELOCAL_INFO_MAX_WAVES = 4, ELOCAL_INFO_ITEMS = 5, ELOCAL_INFO_LDS_BYTES = 6, ELOCAL_INFO_INPLACE = 7
+  ELOCAL_INFO_MAX_WAVES = 4, ELOCAL_INFO_ITEMS = 5, ELOCAL_INFO_LDS_BYTES = 6, ELOCAL_INFO_INPLACE = 7,
+  ELOCAL_INFO_WS_BYTES = 8
 };
 int64_t elocal_launch_info(elocal_t h, const elocal_ansatz* a, int64_t B, int what);
 

@@ -143,7 +143,37 @@ struct AnsatzGeom {
   int mode = 0;        // the caller's precision (ELOCAL_BF16X3 is in the BF16 family)
   int nterms = 2;      // fp16 terms per hidden activation (BF16 family)
   size_t wbytes = 0, bbytes = 0;
+  bool prefix = false; // takes the prefix-shared evaluation (BF16: packing padded for it)
+  MadeDev pm{};        // FP64: the network as that evaluation packs it
+  size_t pwbytes = 0, pbbytes = 0;
+  const MadeDev& prefix_md() const { return precision == ELOCAL_BF16 ? md : pm; }
 };
+
+// Compact BF16 packing: only the k-blocks each o-block uses are stored.
+void pack_bf16_offsets(AnsatzGeom& G) {
+  MadeDev& M = G.md;
+  uint32_t f = 0;
+  for (int l = 0; l <= M.L; ++l) {
+    for (int ob = 0; ob <= kMaxOutBlocks; ++ob) M.foff[l][ob] = 0;
+    for (int ob = 0; ob < M.nob[l]; ++ob) {
+      M.foff[l][ob] = (int32_t)f;
+      f += (uint32_t)M.kend[l][ob];
+    }
+    M.foff[l][M.nob[l]] = (int32_t)f;
+    M.woff[l] = (uint32_t)M.foff[l][0];
+  }
+  for (int l = M.L + 1; l < kMaxLayers; ++l)
+    for (int ob = 0; ob <= kMaxOutBlocks; ++ob) M.foff[l][ob] = (int32_t)f;
+  // the k-ranges as 4-bit fields (a BF16 o-block has at most 8 k-blocks)
+  static_assert(kMaxOutBlocks <= 24, "three words of eight 4-bit k-ranges");
+  for (int l = 0; l < kMaxLayers; ++l) {
+    M.kpack[l][0] = M.kpack[l][1] = M.kpack[l][2] = 0;
+    for (int ob = 0; l <= M.L && ob < kMaxOutBlocks; ++ob)
+      M.kpack[l][ob / 8] |= (uint32_t)(M.kend[l][ob] & 15) << (4 * (ob % 8));
+  }
+  M.nfrag = f;
+  G.wbytes = (size_t)f * 64 * 16;
+}
 
 elocal_status make_geom(const elocal_ctx* h, const elocal_ansatz* a, AnsatzGeom& G) {
   if (!a) return fail(ELOCAL_E_INVALID, "ansatz descriptor is null");
@@ -229,30 +259,9 @@ elocal_status make_geom(const elocal_ctx* h, const elocal_ansatz* a, AnsatzGeom&
       const int ke = 2 * j + 1 < M.nob[0] ? std::max(M.kend[0][2 * j], M.kend[0][2 * j + 1]) : M.kend[0][2 * j];
       M.kend[0][2 * j] = M.kend[0][2 * j + 1] = ke;
     }
-    // compact BF16 packing: only the k-blocks each o-block uses
-    uint32_t f = 0;
-    for (int l = 0; l <= L; ++l) {
-      for (int ob = 0; ob <= kMaxOutBlocks; ++ob) M.foff[l][ob] = 0;
-      for (int ob = 0; ob < M.nob[l]; ++ob) {
-        M.foff[l][ob] = (int32_t)f;
-        f += (uint32_t)M.kend[l][ob];
-      }
-      M.foff[l][M.nob[l]] = (int32_t)f;
-      M.woff[l] = (uint32_t)M.foff[l][0];
-    }
-    for (int l = L + 1; l < kMaxLayers; ++l)
-      for (int ob = 0; ob <= kMaxOutBlocks; ++ob) M.foff[l][ob] = (int32_t)f;
-    // the k-ranges as 4-bit fields (a BF16 o-block has at most 8 k-blocks)
-    static_assert(kMaxOutBlocks <= 24, "three words of eight 4-bit k-ranges");
-    for (int l = 0; l < kMaxLayers; ++l) {
-      M.kpack[l][0] = M.kpack[l][1] = M.kpack[l][2] = 0;
-      for (int ob = 0; l <= L && ob < kMaxOutBlocks; ++ob)
-        M.kpack[l][ob / 8] |= (uint32_t)(M.kend[l][ob] & 15) << (4 * (ob % 8));
-    }
-    M.nfrag = f;
-    wo = f;
+    pack_bf16_offsets(G);
   }
-  G.wbytes = (size_t)wo * 64 * (bf ? 16 : 8);
+  if (!bf) G.wbytes = (size_t)wo * 64 * 8;
   G.bbytes = (size_t)bo * (bf ? 4 : 8);
   // caller's flat layout
   uint32_t off = 0;
@@ -281,6 +290,8 @@ struct StagePlan {
 
 struct EvalPlan {
   uint32_t rows_per_tile, tpi, ips;
+  uint32_t count, fold;   // sums per sample (of 2^lgp partial sums each), and how many the
+  int lgp;                // reduction folds to one before it adds those of a sample
   int64_t n_items;
   bool ldsw;
   StagePlan stage;  // BF16: which layers are staged (biases follow the weights, then the
@@ -290,9 +301,15 @@ struct EvalPlan {
   int cols;         // BF16: 16-row tiles per network pass (kernel variant)
   int waves;        // waves per block
   unsigned grid;
+  bool prefix;      // BF16: prefix-shared evaluation (see prefix.hpp)
+  int lmode;        // its weight source: 0 global memory, 1 LDS, 2 the last classes (top) in LDS
+  PrefixDev px;
+  PrefixTop top;
 };
 
 constexpr size_t kLdsBytes = 160 * 1024;
+// Fewest orbitals for which the prefix-shared evaluation is used.
+constexpr int kPrefixMinOrb = 10;
 
 // Persistent grid: 32 waves per CU in total (a few rounds of resident blocks), unless tuned.
 int64_t grid_cap(const elocal_ctx* h, int waves) {
@@ -363,6 +380,225 @@ static bool inplace_ok_f64(const MadeDev& M) {
   return true;
 }
 
+// Whether a network takes the prefix-shared evaluation: FP64 or two-term BF16 mode and hidden
+// layers of one width of at least two 32-unit blocks (one block has no class boundary, and
+// layers of different widths have different ones).
+bool prefix_net(const AnsatzGeom& G) {
+  if ((G.precision == ELOCAL_BF16 && G.nterms != 2) || G.hmax < 64) return false;
+  const MadeDev& M = G.md;
+  for (int l = 1; l < M.L; ++l)
+    if (M.nout[l] != M.nout[0]) return false;
+  return M.nout[0] >= 64 && (G.precision == ELOCAL_BF16 ? inplace_ok(M) : inplace_ok_f64(M));
+}
+
+// The FP64 network of the prefix-shared evaluation: input blocks of 16 (k-ranges kend in
+// those), dense blocks, 4(n - 1) logits and the phase row.
+void prefix_md_f64(AnsatzGeom& G) {
+  MadeDev& M = G.pm;
+  M = G.md;
+  const int n = M.n, L = M.L;
+  M.nout[L] = 4 * (n - 1) + 1;
+  uint32_t wo = 0, bo = 0;
+  for (int l = 0; l <= L; ++l) {
+    M.nk[l] = (M.nin[l] + 15) / 16;
+    M.nob[l] = (M.nout[l] + 15) / 16;
+    M.woff[l] = wo;
+    M.boff[l] = bo;
+    wo += (uint32_t)(M.nob[l] * M.nk[l]);
+    bo += (uint32_t)(16 * M.nob[l]);
+    for (int ob = 0; ob < M.nob[l]; ++ob) {
+      int need;
+      const int w = M.nout[0];
+      auto count_le = [&](int D) {
+        int c = 0;
+        for (int j = 0; j < w; ++j) c += (j % (n - 1)) + 1 <= D;
+        return c;
+      };
+      if (l < L) {
+        const int mmax = sorted_unit(n, w, std::min(16 * ob + 15, w - 1)) % (n - 1) + 1;
+        need = l == 0 ? 2 * mmax : count_le(mmax);
+      } else {
+        need = 16 * ob + 16 > 4 * (n - 1) ? M.nin[l] : count_le(4 * ob + 3);
+      }
+      M.kend[l][ob] = std::max(1, std::min(M.nk[l], (need + 15) / 16));
+    }
+  }
+  M.nfrag = wo;
+  M.nbias = bo;
+  G.pwbytes = (size_t)wo * 2048;
+  G.pbbytes = (size_t)bo * 8;
+}
+
+// Hidden o-blocks 2 j of a prefix-shared network that read j + 2 input blocks (else j + 1).
+int prefix_extra(const MadeDev& M) {
+  for (int l = 1; l < M.L; ++l)
+    for (int j = 0; 2 * j < M.nob[l]; ++j)
+      if (M.kend[l][2 * j] > j + 1) return 1;
+  return 0;
+}
+
+// The packing of a prefix-shared network: k-ranges padded (with masked zeros) to ones that
+// the kernels know at compile time.
+void pad_prefix(AnsatzGeom& G) {
+  MadeDev& M = G.md;
+  const int x = prefix_extra(M), nblk = M.nout[0] / 32;
+  for (int l = 0; l < M.L; ++l)
+    for (int ob = 0; ob < M.nob[l]; ++ob)
+      M.kend[l][ob] = l == 0 ? M.nk[0] : std::min(nblk, ob / 2 + 1 + (ob % 2 ? 1 : x));
+  pack_bf16_offsets(G);
+}
+
+// Classes, checkpoint layout and segments of the prefix-shared evaluation.
+// Scratch of one wave: as many parents per segment as fit, at most a tile of 16. Early
+// parents have more boundaries below them (13.9 KB each at 60 orbitals, 3 x 256; 0.5 KB in
+// the last class) and more entries to amortise a partly filled tile.
+// (FP64 values are twice as long.)
+size_t prefix_scratch_bytes(const AnsatzGeom& G) {
+  return (G.hmax >= 256 ? 32 : G.hmax >= 128 ? 18 : 8) * 1024 * (G.precision == ELOCAL_BF16 ? 1 : 2);
+}
+
+void plan_prefix(const elocal_ctx* h, const AnsatzGeom& G, PrefixDev& X) {
+  const MadeDev& M = G.prefix_md();
+  const bool bf = G.precision == ELOCAL_BF16;
+  const uint32_t slot_bytes = bf ? 64 : 128;
+  const int n = M.n, w = M.nout[0], L = M.L, nblk = w / 32;
+  X.nblk = nblk;
+  X.extra = bf ? prefix_extra(M) : 0;
+  auto count_le = [&](int q) {   // hidden units of degree <= q
+    int c = 0;
+    for (int j = 0; j < w; ++j) c += (j % (n - 1)) + 1 <= q;
+    return c;
+  };
+  PrefixClass* K = X.cls;
+  for (int b = 0; b <= kMaxClasses; ++b) K[b].qb = n;
+  for (int q = n - 1; q >= 0; --q)
+    for (int b = 0, c = std::min(count_le(q) / 32, nblk - 1); b <= c; ++b) K[b].qb = q;
+  auto slots = [&](int b) { return (uint32_t)(2 * (nblk - b) * L + M.nob[L] - K[b].qb / 4); };
+  for (int b = nblk - 1; b >= 0; --b) {
+    K[b].kin = 2 * K[b].qb / (bf ? 32 : 16);
+    K[b].obq = K[b].qb / 4;
+    K[b].soff = b == nblk - 1 ? 0u : K[b + 1].soff + slots(b + 1);
+    K[b].oslot = K[b].soff + (uint32_t)(2 * (nblk - b) * L) - (uint32_t)K[b].obq;
+    K[b].f0 = bf ? M.foff[0][2 * b] : (int)M.woff[0] + 2 * b * M.nk[0];
+  }
+  for (int l = 0; l <= L; ++l) {
+    X.lay[l].ke = 0;
+    for (int ob = 0; ob < M.nob[l]; ++ob) X.lay[l].ke |= (uint64_t)((bf ? M.kend[l][ob] : M.kend[l][ob] - 1) & 15) << (4 * ob);
+    X.lay[l].boff = M.boff[l];
+    X.lay[l].fend = bf ? M.foff[l][M.nob[l]] : (int)M.woff[l];   // (FP64: the layer's first fragment)
+    X.lay[l].tend = X.lay[l].fend;
+  }
+  for (int ob = 0; ob <= kMaxOutBlocks; ++ob) X.fout[ob] = X.tout[ob] = M.foff[L][std::min(ob, M.nob[L])];
+  for (int b = 0; b < nblk; ++b) K[b].t0 = K[b].f0;   // (LDS holding the whole network)
+  const size_t cap = prefix_scratch_bytes(G);
+  X.stride = 0;
+  X.seg0[0] = 0;
+  for (int c = 0; c < nblk; ++c) {
+    const int b = std::max(1, c);
+    X.stot[c] = K[b].soff + slots(b);
+    X.ng[c] = (int)std::max<size_t>(1, std::min<size_t>(16, cap / (slot_bytes * X.stot[c])));
+    X.stride = std::max(X.stride, (uint32_t)X.ng[c] * X.stot[c] * (slot_bytes / 4));
+    X.rank0[c] = (uint32_t)binom2(2 * K[c].qb);
+    X.rank0[c + 1] = (uint32_t)binom2(2 * K[c + 1].qb);
+    X.seg0[c + 1] = X.seg0[c] + (X.rank0[c + 1] - X.rank0[c] + X.ng[c] - 1) / X.ng[c];
+  }
+}
+
+// The last classes' weights (input blocks from class bs on) as they lie in LDS; their bytes.
+size_t plan_top(const AnsatzGeom& G, int kernel_hmax, PrefixDev& X, PrefixTop& T) {
+  const MadeDev& M = G.md;
+  const int bs = std::max(0, X.nblk - prefix_lds_blocks(kernel_hmax));
+  T.kb0 = bs;
+  T.kin0 = X.cls[bs].kin;
+  int32_t f = 0;
+  for (int l = 0; l <= M.L; ++l) {
+    T.ob0[l] = l < M.L ? 2 * bs : X.cls[bs].obq;
+    for (int ob = 0; ob <= M.nob[l]; ++ob) {
+      T.foff[l][ob] = f;
+      if (ob >= T.ob0[l] && ob < M.nob[l]) f += std::max(0, M.kend[l][ob] - (l == 0 ? T.kin0 : T.kb0));
+    }
+  }
+  for (int b = bs; b < X.nblk; ++b) X.cls[b].t0 = T.foff[0][2 * b];
+  for (int l = 0; l <= M.L; ++l) X.lay[l].tend = T.foff[l][M.nob[l]];
+  for (int ob = 0; ob <= kMaxOutBlocks; ++ob) X.tout[ob] = T.foff[M.L][std::min(ob, M.nob[M.L])];
+  return align256((size_t)f * 1024);
+}
+
+// Weight source and LDS of a prefix-shared block of `waves` waves with `bias_bytes` of biases.
+void plan_prefix_lds(const AnsatzGeom& G, int kernel_hmax, int waves, size_t bias_bytes, EvalPlan& p, size_t& wbytes) {
+  const size_t state = waves * kPrefixWaveBytes + kXLutBytes, fixed = align256(bias_bytes) + state;
+  p.lmode = 0;
+  wbytes = 0;
+  if (kernel_hmax < kLdsPartialWidth) {
+    if (fixed + align256(G.wbytes) <= kLdsBytes) { p.lmode = 1; wbytes = align256(G.wbytes); }
+  } else {
+    const size_t tb = plan_top(G, kernel_hmax, p.px, p.top);
+    if (state + tb <= kLdsBytes) { p.lmode = 2; wbytes = tb; }
+  }
+}
+
+// Geometry of elocal_eval and elocal_eval_multi (the Pauli route and the others: make_geom).
+elocal_status make_eval_geom(const elocal_ctx* h, const elocal_ansatz* a, AnsatzGeom& G) {
+  if (elocal_status e = make_geom(h, a, G)) return e;
+  G.prefix = prefix_net(G) && h->sys.n >= kPrefixMinOrb && h->sys.C > 1;
+  if (G.prefix) {
+    if (G.precision == ELOCAL_BF16) pad_prefix(G);
+    else prefix_md_f64(G);
+  }
+  return ELOCAL_OK;
+}
+
+// Work items of the prefix-shared evaluation. A sample's sum is over groups of consecutive
+// segments, as many groups as the plain path has items (so the partial sums take no more
+// memory), and an item is one of them. A batch with few of these has an item per segment, or
+// 2^k items where a segment has more entries than one wave's share of the batch: the launch is
+// else as long as its longest segment (24 orbitals, 64 samples: 456 us whole, 356 in parts, 428
+// and 584 in parts of a half and a third of the share, because a part runs its segment's
+// parents again; 60 orbitals, 8 samples: 2.67 ms, 2.65). The sums are the same bit for bit:
+// see add_to_slot, k_reduce.
+constexpr int64_t kFineItems = 131072;   // a few tens of items per wave of the chip
+constexpr int kMaxLgParts = 4;
+void plan_items(const elocal_ctx* h, int64_t B, EvalPlan& p) {
+  PrefixDev& X = p.px;
+  const uint32_t nseg = X.seg0[X.nblk];
+  const uint32_t group = h->tune_groups > 0 ? (uint32_t)std::min<int64_t>(h->tune_groups, nseg)
+                                            : (nseg + p.ips - 1) / std::max(1u, p.ips);
+  X.spi = group;
+  X.lgp = 0;
+  p.ips = p.count = (nseg + group - 1) / group;
+  if (h->tune_groups <= 0 && (int64_t)nseg * B <= kFineItems) {
+    X.spi = 0;
+    p.count = nseg;
+    p.fold = group;
+    // entries of a parent whose c2 is in orbital q, averaged over the kinds and spins of its
+    // two changes
+    const int n = h->sys.n;
+    const double na = h->sys.na, nb = h->sys.nb, pa = na / n, pb = nb / n;
+    auto entries = [&](int q) {
+      const double f = (double)(n - q) / n, ao = na * f, av = (n - na) * f, bo = nb * f, bv = (n - nb) * f;
+      const double cross = (pa * av + (1 - pa) * ao) * (pb * bv + (1 - pb) * bo), mixed = ao * av + bo * bv;
+      const double sa = pa * pa * av * av / 2 + (1 - pa) * (1 - pa) * ao * ao / 2 + 2 * pa * (1 - pa) * mixed;
+      const double sb = pb * pb * bv * bv / 2 + (1 - pb) * (1 - pb) * bo * bo / 2 + 2 * pb * (1 - pb) * mixed;
+      return 0.5 * cross + 0.25 * (sa + sb);
+    };
+    const double share = std::max(64.0, (double)B * h->sys.C / ((double)p.waves * h->cu_count));
+    for (int c = 0; c < X.nblk; ++c) {
+      int k = 0;
+      while (k < kMaxLgParts && ((int64_t)nseg * B << (k + 1)) <= kFineItems &&
+             X.ng[c] * entries(X.cls[c].qb) > share * (1 << k))
+        ++k;
+      X.lgk[c] = k;
+      X.lgp = std::max(X.lgp, k);
+    }
+    X.item0[0] = 0;
+    for (int c = 0; c < X.nblk; ++c) X.item0[c + 1] = X.item0[c] + ((X.seg0[c + 1] - X.seg0[c]) << X.lgk[c]);
+    p.ips = X.item0[X.nblk];
+  }
+  p.lgp = X.lgp;
+  p.n_items = (int64_t)p.ips * B;
+  p.tpi = std::max(1u, X.spi);
+}
+
 EvalPlan plan_eval(const elocal_ctx* h, const AnsatzGeom& G, int64_t B, int64_t list_len = -1) {
   EvalPlan p{};
   // BF16: groups of 64 entries (one per lane), 8 per item; FP64: tiles of 16, 16 per item
@@ -374,11 +610,15 @@ EvalPlan plan_eval(const elocal_ctx* h, const AnsatzGeom& G, int64_t B, int64_t 
   const uint64_t per_item = (uint64_t)p.rows_per_tile * p.tpi;
   p.ips = (uint32_t)((rows + per_item - 1) / per_item);
   p.n_items = (int64_t)p.ips * B;
+  p.count = p.ips;
+  p.fold = 1;
+  p.lgp = 0;
   for (int l = 0; l < kMaxLayers; ++l) p.stage.frag[l] = -1;
   if (G.precision == ELOCAL_BF16) {
     p.cols = eval_cols_default_bf16(G.hmax, G.nterms);
     if (h->tune_cols > 0 && eval_cols_available_bf16(G.hmax, G.nterms, (int)h->tune_cols)) p.cols = (int)h->tune_cols;
-    p.waves = eval_waves_bf16(G.hmax, G.nterms, p.cols);
+    p.prefix = G.prefix;
+    p.waves = p.prefix ? prefix_waves_bf16(G.hmax, p.cols) : eval_waves_bf16(G.hmax, G.nterms, p.cols);
     if (h->tune_waves > 0) p.waves = (int)std::min<int64_t>(h->tune_waves, p.waves);
     p.stage = plan_stage(G, G.hmax, p.waves, G.bbytes);
     p.ldsw = p.stage.any;   // one block per CU owns the CU's LDS
@@ -388,12 +628,54 @@ EvalPlan plan_eval(const elocal_ctx* h, const AnsatzGeom& G, int64_t B, int64_t 
     p.ldsw = false;
     p.lds = 0;
     p.cols = 1;
-    p.waves = 4;
+    p.prefix = G.prefix;
+    p.waves = p.prefix ? kPrefixWavesF64 : 4;
     p.inplace = G.hmax >= 128 && inplace_ok_f64(G.md);
+  }
+  if (p.prefix) {
+    plan_prefix(h, G, p.px);
+    plan_items(h, B, p);
+    if (G.precision == ELOCAL_BF16) {
+      size_t wb = 0;
+      plan_prefix_lds(G, G.hmax, p.waves, G.bbytes, p, wb);
+      p.ldsw = p.lmode != 0;
+      p.stage.wbytes = wb;
+      for (int l = 0; l <= G.md.L; ++l) p.stage.frag[l] = p.lmode == 1 ? G.md.foff[l][0] : -1;
+      p.lds = wb + (p.lmode == 1 ? align256(G.bbytes) : 0) + p.waves * kPrefixWaveBytes + kXLutBytes;
+    } else {
+      p.lds = p.waves * kPrefixWaveBytes;
+    }
+    p.inplace = true;
   }
   const int64_t want = (p.n_items + p.waves - 1) / p.waves;
   p.grid = (unsigned)std::max<int64_t>(1, std::min(want, grid_cap(h, p.waves)));
+  // every wave of a prefix-shared launch has its own scratch: one block per CU (a block of
+  // fewer waves than the kernel is built for leaves room for more)
+  const int full = G.precision == ELOCAL_BF16 ? prefix_waves_bf16(G.hmax, p.cols) : kPrefixWavesF64;
+  if (p.prefix) p.grid = std::min(p.grid, (unsigned)h->cu_count * (unsigned)std::max(1, full / p.waves));
   return p;
+}
+
+// Launches the prefix-shared kernel of a width class.
+hipError_t launch_prefix(const EvalArgs& E, int hmax, int cols, const EvalPlan& p, hipStream_t st) {
+  if (hmax == 64)
+    return cols == 2 ? launch_prefix_w64c2(E, p.lmode, p.lds, p.grid, p.waves, st)
+                     : launch_prefix_w64(E, p.lmode, p.lds, p.grid, p.waves, st);
+  if (hmax == 128)
+    return cols == 2 ? launch_prefix_w128c2(E, p.lmode, p.lds, p.grid, p.waves, st)
+                     : launch_prefix_w128(E, p.lmode, p.lds, p.grid, p.waves, st);
+  return launch_prefix_w256(E, p.lmode, p.lds, p.grid, p.waves, st);
+}
+
+hipError_t launch_prefix_multi(const EvalArgs* args, int n_sys, int hmax, int cols, int lmode, size_t lds,
+                               unsigned grid, int waves, hipStream_t st) {
+  if (hmax == 64)
+    return cols == 2 ? launch_prefix_multi_w64c2(args, n_sys, lmode, lds, grid, waves, st)
+                     : launch_prefix_multi_w64(args, n_sys, lmode, lds, grid, waves, st);
+  if (hmax == 128)
+    return cols == 2 ? launch_prefix_multi_w128c2(args, n_sys, lmode, lds, grid, waves, st)
+                     : launch_prefix_multi_w128(args, n_sys, lmode, lds, grid, waves, st);
+  return launch_prefix_multi_w256(args, n_sys, lmode, lds, grid, waves, st);
 }
 
 // The LDS layout fields of the BF16 kernel arguments for a plan.
@@ -401,7 +683,7 @@ void set_lds_args(EvalArgs& E, const EvalPlan& p, size_t bias_bytes) {
   const size_t wb = p.ldsw ? p.stage.wbytes : 0, bb = p.ldsw ? align256(bias_bytes) : 0;
   E.lds_bias_off = (uint32_t)wb;
   E.lds_ctx_off = (uint32_t)(wb + bb);
-  E.lds_lut_off = (uint32_t)(wb + bb + (size_t)p.waves * kWaveCtxBytesBF16);
+  E.lds_lut_off = (uint32_t)(wb + bb + (size_t)p.waves * (p.prefix ? kPrefixWaveBytes : kWaveCtxBytesBF16));
   for (int l = 0; l < kMaxLayers; ++l) E.lds_frag[l] = p.ldsw ? p.stage.frag[l] : -1;
 }
 
@@ -414,10 +696,15 @@ struct EvalWs {
   double* lpx64;
   double* zphi;
   double* partial;
+  uint32_t* queue;   // prefix-shared evaluation: the work-item ticket and the checkpoints
+  float* scratch;
+  void* pfrag;       // FP64 prefix-shared evaluation: its own packing of the network
+  double* pbias;
   size_t bytes;
 };
 
-EvalWs carve_eval(const elocal_ctx* h, const AnsatzGeom& G, const EvalPlan& p, int64_t B, void* ws) {
+EvalWs carve_eval(const elocal_ctx* h, const AnsatzGeom& G, const EvalPlan& p, int64_t B, void* ws,
+                  bool scratch = true) {
   Carve c(ws);
   EvalWs w{};
   const size_t nS = h->sys.nSa + h->sys.nSb;
@@ -433,9 +720,45 @@ EvalWs carve_eval(const elocal_ctx* h, const AnsatzGeom& G, const EvalPlan& p, i
     w.lpx64 = c.take<double>(std::max<size_t>((size_t)B * h->sys.n, 1));
   }
   w.zphi = c.take<double>(std::max<int64_t>(B, 1));
-  w.partial = c.take<double>(std::max<size_t>((size_t)p.n_items * 2, 1));
+  w.partial = c.take<double>(std::max<size_t>(((size_t)p.count * B << p.lgp) * 2, 1));
+  w.queue = nullptr;
+  w.scratch = nullptr;
+  if (p.prefix) {
+    w.queue = c.take<uint32_t>(1);
+    if (G.precision == ELOCAL_FP64) {
+      w.pfrag = c.take<char>(G.pwbytes);
+      w.pbias = c.take<double>(G.pbbytes / 8);
+    }
+    w.scratch = c.take<float>(scratch ? (size_t)p.grid * p.waves * p.px.stride : 0);
+  }
   w.bytes = c.off;
   return w;
+}
+
+// Fewer blocks where the checkpoints of the whole grid do not fit in `bytes` (results do not
+// depend on the grid).
+void shrink_grid(const elocal_ctx* h, const AnsatzGeom& G, int64_t B, size_t bytes, EvalPlan& p) {
+  if (!p.prefix || carve_eval(h, G, p, B, nullptr).bytes <= bytes) return;
+  const size_t fixed = carve_eval(h, G, p, B, nullptr, false).bytes;
+  const size_t block = (size_t)p.waves * p.px.stride * sizeof(float);
+  const size_t fit = bytes > fixed + 256 ? (bytes - fixed - 256) / block : 0;
+  p.grid = (unsigned)std::max<size_t>(1, std::min<size_t>(p.grid, fit));
+}
+
+// Bytes elocal_eval needs. A prefix-shared launch holds checkpoints per wave; a batch that fits
+// the scratch of elocal_eval_noalloc with 16 bytes per 512 list entries in their place needs no
+// more than that scratch (its launch then takes fewer blocks; with more room it takes them all).
+size_t eval_need(const elocal_ctx* h, const AnsatzGeom& G, int64_t B, const EvalPlan& p) {
+  const size_t full = carve_eval(h, G, p, B, nullptr).bytes;
+  if (!p.prefix || full <= kNoAllocScratchBytes) return full;
+  EvalPlan q = p;
+  q.prefix = false;
+  q.count = ((uint32_t)h->sys.C - 1 + 511) / 512;
+  q.lgp = 0;
+  if (carve_eval(h, G, q, B, nullptr).bytes > kNoAllocScratchBytes + (64 << 10)) return full;
+  q = p;
+  shrink_grid(h, G, B, kNoAllocScratchBytes, q);
+  return carve_eval(h, G, q, B, nullptr).bytes;
 }
 
 struct ConnectWs {
@@ -647,10 +970,9 @@ size_t elocal_workspace_bytes(elocal_t h, const elocal_ansatz* a, int64_t B, int
   if (B < 0) { fail(ELOCAL_E_INVALID, "B=%lld is negative", (long long)B); return 0; }
   if (op == ELOCAL_OP_CONNECT) return carve_connect(h, B, nullptr).bytes;
   AnsatzGeom G;
-  if (make_geom(h, a, G) != ELOCAL_OK) return 0;
+  if (make_eval_geom(h, a, G) != ELOCAL_OK) return 0;
   if (op == ELOCAL_OP_EVAL) {
-    const EvalPlan p = plan_eval(h, G, B);
-    return carve_eval(h, G, p, B, nullptr).bytes;
+    return eval_need(h, G, B, plan_eval(h, G, B));
   }
   if (op == ELOCAL_OP_GRAD) return carve_grad(h, G, B, nullptr, nullptr);
   fail(ELOCAL_E_INVALID, "unknown op %d", op);
@@ -685,14 +1007,14 @@ elocal_status elocal_eval(elocal_t h, elocal_stream s, const elocal_ansatz* a, c
                           void* ws, size_t ws_bytes, double* eloc, double* logpsi) {
   if (!h) return fail(ELOCAL_E_INVALID, "handle is null");
   AnsatzGeom G;
-  if (elocal_status e = make_geom(h, a, G)) return e;
+  if (elocal_status e = make_eval_geom(h, a, G)) return e;
   if (B < 0) return fail(ELOCAL_E_INVALID, "B=%lld is negative", (long long)B);
   if (B == 0) return ELOCAL_OK;
   if (!a->theta || !x || !ws || !eloc) return fail(ELOCAL_E_INVALID, "null pointer argument");
-  const EvalPlan p = plan_eval(h, G, B);
-  const EvalWs need = carve_eval(h, G, p, B, nullptr);
-  if (ws_bytes < need.bytes)
-    return fail(ELOCAL_E_WORKSPACE, "workspace %zu bytes < %zu needed", ws_bytes, need.bytes);
+  EvalPlan p = plan_eval(h, G, B);
+  const size_t need = eval_need(h, G, B, p);
+  if (ws_bytes < need) return fail(ELOCAL_E_WORKSPACE, "workspace %zu bytes < %zu needed", ws_bytes, need);
+  shrink_grid(h, G, B, ws_bytes, p);
   if (elocal_status st = check_device(h)) return st;
   const EvalWs w = carve_eval(h, G, p, B, ws);
   hipStream_t st = (hipStream_t)s;
@@ -700,9 +1022,11 @@ elocal_status elocal_eval(elocal_t h, elocal_stream s, const elocal_ansatz* a, c
   M.wfrag = w.frag;
   M.bias = w.bias;
   if (G.precision == ELOCAL_BF16)
-    HIP_TRY(launch_pack_bf16(M, G.T, (const uint16_t*)a->theta, w.frag, (float*)w.bias, st), "pack launch");
+    HIP_TRY(launch_pack_bf16(M, G.T, (const uint16_t*)a->theta, w.frag, (float*)w.bias, w.queue, st), "pack launch");
   else
     HIP_TRY(launch_pack_f64(M, G.T, (const double*)a->theta, w.frag, (double*)w.bias, st), "pack launch");
+  if (p.prefix && G.precision == ELOCAL_FP64)
+    HIP_TRY(launch_pack_prefix_f64(G.pm, G.T, (const double*)a->theta, w.pfrag, w.pbias, w.queue, st), "pack launch");
   HIP_TRY(launch_prep(h->sys, x, B, w.ediag, w.F, st), "prep launch");
   RowsArgs R{};
   R.sys = h->sys; R.made = M; R.x = x; R.B = B; R.lpx = w.lpx; R.lpx64 = w.lpx64; R.zphi = w.zphi;
@@ -716,7 +1040,16 @@ elocal_status elocal_eval(elocal_t h, elocal_stream s, const elocal_ansatz* a, c
   const bool timed = h->timing && p.n_items > 0;
   const int slot = (int)(h->ring_pos % elocal_ctx::kRing);
   if (timed) HIP_TRY(hipEventRecord(h->ev_start[slot], st), "timing event");
-  if (G.precision == ELOCAL_BF16) {
+  if (p.prefix) {
+    set_lds_args(E, p, p.lmode == 1 ? G.bbytes : 0);
+    E.px = p.px; E.px.scratch = w.scratch; E.px.queue = w.queue; E.top = p.top;
+    if (G.precision == ELOCAL_BF16) {
+      HIP_TRY(launch_prefix(E, G.hmax, p.cols, p, st), "eval launch");
+    } else {
+      E.made = G.pm; E.made.wfrag = w.pfrag; E.made.bias = w.pbias;
+      HIP_TRY(launch_prefix_f64(E, G.hmax, p.grid, st), "eval launch");
+    }
+  } else if (G.precision == ELOCAL_BF16) {
     set_lds_args(E, p, G.bbytes);
     HIP_TRY(launch_eval_bf16(E, G.hmax, G.nterms, p.cols, p.ldsw, p.inplace, p.lds, p.grid, p.waves, st),
             "eval launch");
@@ -728,7 +1061,7 @@ elocal_status elocal_eval(elocal_t h, elocal_stream s, const elocal_ansatz* a, c
     h->ring_pos++;
     h->recorded++;
   }
-  HIP_TRY(launch_reduce(w.ediag, w.partial, B, p.ips, eloc, st), "reduce launch");
+  HIP_TRY(launch_reduce(w.ediag, w.partial, B, p.count, p.fold, p.lgp, eloc, st), "reduce launch");
   return ELOCAL_OK;
 }
 
@@ -746,9 +1079,9 @@ elocal_status elocal_eval_noalloc(elocal_t h, elocal_stream s, const elocal_ansa
     ws = t.ptr[h->dev];
   }
   AnsatzGeom G;
-  if (elocal_status e = make_geom(h, a, G)) return e;
+  if (elocal_status e = make_eval_geom(h, a, G)) return e;
   if (B < 0) return fail(ELOCAL_E_INVALID, "B=%lld is negative", (long long)B);
-  const size_t need = carve_eval(h, G, plan_eval(h, G, B), B, nullptr).bytes;
+  const size_t need = eval_need(h, G, B, plan_eval(h, G, B));
   if (need > kNoAllocScratchBytes)
     return fail(ELOCAL_E_WORKSPACE,
                 "elocal_eval_noalloc needs %zu bytes of scratch for B=%lld, above its fixed %zu bytes "
@@ -767,8 +1100,14 @@ struct MultiPlan {
   size_t off[ELOCAL_MAX_SYSTEMS];   // byte offset of system s's eval workspace
   int order[ELOCAL_MAX_SYSTEMS];    // position in the item space -> system
   size_t args_off, first_off, bytes;
-  int64_t first[ELOCAL_MAX_SYSTEMS + 1];
+  int64_t first[ELOCAL_MAX_SYSTEMS + 1];   // of the systems order[n_pre..]
   int hmax, precision;
+  // order[0 .. n_pre): the systems that take the prefix-shared evaluation, in one launch of
+  // its own (shape and LDS layout in `pre`, its scratch at pre_off)
+  int n_pre, pre_hmax;
+  EvalPlan pre;
+  uint32_t pre_bias_off, pre_ctx_off, pre_lut_off;
+  size_t pre_off;
   bool ldsw;            // BF16: some system stages weights in LDS
   bool inplace;         // BF16: in-place hidden layers (every system allows them)
   int cols, waves;      // BF16: tiles per pass and waves per block of the launch
@@ -787,20 +1126,26 @@ elocal_status plan_multi(int n_sys, const elocal_t* hs, const elocal_ansatz* con
   if (n_sys < 1 || n_sys > ELOCAL_MAX_SYSTEMS)
     return fail(ELOCAL_E_INVALID, "n_sys=%d outside [1, %d]", n_sys, (int)ELOCAL_MAX_SYSTEMS);
   if (!hs || !a || !B) return fail(ELOCAL_E_INVALID, "null array argument");
-  M.hmax = 0;
+  M.hmax = M.pre_hmax = 32;
+  M.n_pre = 0;
   size_t off = 0;
   double cost[ELOCAL_MAX_SYSTEMS];
   for (int s = 0; s < n_sys; ++s) {
     if (!hs[s]) return fail(ELOCAL_E_INVALID, "handle %d is null", s);
     if (hs[s]->dev != hs[0]->dev) return fail(ELOCAL_E_INVALID, "handles %d and 0 are on different devices", s);
     if (B[s] < 0) return fail(ELOCAL_E_INVALID, "B[%d]=%lld is negative", s, (long long)B[s]);
-    if (elocal_status e = make_geom(hs[s], a[s], M.G[s])) return e;
+    if (elocal_status e = make_eval_geom(hs[s], a[s], M.G[s])) return e;
     if (s > 0 && M.G[s].mode != M.G[0].mode)
       return fail(ELOCAL_E_INVALID, "ansatz %d has another precision than ansatz 0", s);
-    M.hmax = std::max(M.hmax, M.G[s].hmax);
     M.p[s] = plan_eval(hs[s], M.G[s], B[s]);
+    if (M.p[s].prefix) {
+      ++M.n_pre;
+      M.pre_hmax = std::max(M.pre_hmax, M.G[s].hmax);
+    } else {
+      M.hmax = std::max(M.hmax, M.G[s].hmax);
+    }
     M.off[s] = off;
-    off = align256(off + carve_eval(hs[s], M.G[s], M.p[s], B[s], nullptr).bytes);
+    off = align256(off + carve_eval(hs[s], M.G[s], M.p[s], B[s], nullptr, false).bytes);
     // cost of one item ~ rows x dense multiply-adds per row
     double per_row = 0.0;
     const MadeDev& md = M.G[s].md;
@@ -811,6 +1156,43 @@ elocal_status plan_multi(int n_sys, const elocal_t* hs, const elocal_ansatz* con
   M.precision = M.G[0].precision;
   // most expensive items first: the grid's last items are then the cheapest ones
   std::stable_sort(M.order, M.order + n_sys, [&](int u, int v) { return cost[u] > cost[v]; });
+  std::stable_partition(M.order, M.order + n_sys, [&](int s) { return M.p[s].prefix; });
+  if (M.n_pre > 0) {
+    EvalPlan& q = M.pre;
+    const bool bf = M.precision == ELOCAL_BF16;
+    q.cols = eval_cols_default_bf16(M.pre_hmax, 2);
+    if (bf && hs[0]->tune_cols > 0 && eval_cols_available_bf16(M.pre_hmax, 2, (int)hs[0]->tune_cols))
+      q.cols = (int)hs[0]->tune_cols;
+    const int full = bf ? prefix_waves_bf16(M.pre_hmax, q.cols) : kPrefixWavesF64;
+    q.waves = full;
+    if (bf && hs[0]->tune_waves > 0) q.waves = (int)std::min<int64_t>(hs[0]->tune_waves, q.waves);
+    size_t wmax = 0, bmax = 0;
+    int64_t items = 0;
+    q.px.stride = 0;
+    for (int i = 0; i < M.n_pre; ++i) bmax = std::max(bmax, align256(M.G[M.order[i]].bbytes));
+    bool all = true;
+    for (int i = 0; i < M.n_pre; ++i) {
+      const int s = M.order[i];
+      size_t wb = 0;
+      if (bf) plan_prefix_lds(M.G[s], M.pre_hmax, q.waves, bmax, M.p[s], wb);
+      all = all && M.p[s].lmode != 0;
+      wmax = std::max(wmax, wb);
+      q.px.stride = std::max(q.px.stride, M.p[s].px.stride);
+      items = std::max(items, M.p[s].n_items);
+    }
+    q.lmode = all ? M.p[M.order[0]].lmode : 0;
+    M.pre_bias_off = q.lmode ? (uint32_t)wmax : 0u;
+    M.pre_ctx_off = q.lmode == 1 ? (uint32_t)(wmax + bmax) : q.lmode ? (uint32_t)wmax : 0u;
+    M.pre_lut_off = M.pre_ctx_off + (uint32_t)(q.waves * kPrefixWaveBytes);
+    q.lds = M.pre_lut_off + kXLutBytes;
+    const int64_t want = (items + q.waves - 1) / q.waves;
+    q.grid = (unsigned)std::max<int64_t>(1, std::min(want, grid_cap(hs[0], q.waves)));
+    q.grid = std::min(q.grid, (unsigned)hs[0]->cu_count * (unsigned)std::max(1, full / q.waves));
+    M.pre_off = off;
+    off = align256(off + (size_t)q.grid * q.waves * q.px.stride * sizeof(float));
+  }
+  const int n_old = n_sys - M.n_pre;
+  const int* old_order = M.order + M.n_pre;
   // BF16: index space of chunks (one item per wave of a block, never two systems in a
   // chunk); FP64: index space of items
   // BF16 launch shape: the first handle's tuning, for the widest system's kernel
@@ -821,7 +1203,7 @@ elocal_status plan_multi(int n_sys, const elocal_t* hs, const elocal_ansatz* con
   if (hs[0]->tune_waves > 0) M.waves = (int)std::min<int64_t>(hs[0]->tune_waves, M.waves);
   const int unit = (M.precision == ELOCAL_BF16) ? M.waves : 1;
   M.first[0] = 0;
-  for (int i = 0; i < n_sys; ++i) M.first[i + 1] = M.first[i] + (M.p[M.order[i]].n_items + unit - 1) / unit;
+  for (int i = 0; i < n_old; ++i) M.first[i + 1] = M.first[i] + (M.p[old_order[i]].n_items + unit - 1) / unit;
   M.ldsw = M.inplace = false;
   M.bias_off = M.ctx_off = M.lut_off = 0;
   M.lds = 0;
@@ -829,9 +1211,10 @@ elocal_status plan_multi(int n_sys, const elocal_t* hs, const elocal_ansatz* con
     // one LDS layout for all systems, sized for the kernel's width class and wave count
     const int waves = M.waves;
     size_t wmax = 0, bmax = 0;
-    for (int s = 0; s < n_sys; ++s) bmax = std::max(bmax, align256(M.G[s].bbytes));
+    for (int i = 0; i < n_old; ++i) bmax = std::max(bmax, align256(M.G[old_order[i]].bbytes));
     M.inplace = inplace_kernel_bf16(M.hmax, M.G[0].nterms) && M.cols == 1;
-    for (int s = 0; s < n_sys; ++s) {
+    for (int i = 0; i < n_old; ++i) {
+      const int s = old_order[i];
       M.stage[s] = plan_stage(M.G[s], M.hmax, waves, bmax);
       M.ldsw = M.ldsw || M.stage[s].any;
       wmax = std::max(wmax, M.stage[s].wbytes);
@@ -850,7 +1233,7 @@ elocal_status plan_multi(int n_sys, const elocal_t* hs, const elocal_ansatz* con
   off = align256(off + sizeof(int64_t) * (n_sys + 1));
   M.bytes = off;
   const int waves = (M.precision == ELOCAL_BF16) ? M.waves : 4;
-  const int64_t want = (M.precision == ELOCAL_BF16) ? M.first[n_sys] : (M.first[n_sys] + 3) / 4;
+  const int64_t want = (M.precision == ELOCAL_BF16) ? M.first[n_old] : (M.first[n_old] + 3) / 4;
   M.grid = (unsigned)std::max<int64_t>(1, std::min(want, grid_cap(hs[0], waves)));
   return ELOCAL_OK;
 }
@@ -884,15 +1267,18 @@ elocal_status elocal_eval_multi(int n_sys, const elocal_t* hs, elocal_stream s, 
   for (int i = 0; i < n_sys; ++i) {
     const elocal_ctx* h = hs[i];
     const AnsatzGeom& G = M.G[i];
-    W[i] = carve_eval(h, G, M.p[i], B[i], base + M.off[i]);
+    W[i] = carve_eval(h, G, M.p[i], B[i], base + M.off[i], false);
     if (B[i] == 0) continue;
     MadeDev md = G.md;
     md.wfrag = W[i].frag;
     md.bias = W[i].bias;
     if (G.precision == ELOCAL_BF16)
-      HIP_TRY(launch_pack_bf16(md, G.T, (const uint16_t*)a[i]->theta, W[i].frag, (float*)W[i].bias, st), "pack launch");
+      HIP_TRY(launch_pack_bf16(md, G.T, (const uint16_t*)a[i]->theta, W[i].frag, (float*)W[i].bias, W[i].queue, st), "pack launch");
     else
       HIP_TRY(launch_pack_f64(md, G.T, (const double*)a[i]->theta, W[i].frag, (double*)W[i].bias, st), "pack launch");
+    if (M.p[i].prefix && G.precision == ELOCAL_FP64)
+      HIP_TRY(launch_pack_prefix_f64(G.pm, G.T, (const double*)a[i]->theta, W[i].pfrag, W[i].pbias, W[i].queue, st),
+              "pack launch");
     HIP_TRY(launch_prep(h->sys, x[i], B[i], W[i].ediag, W[i].F, st), "prep launch");
     RowsArgs R{};
     R.sys = h->sys; R.made = md; R.x = x[i]; R.B = B[i]; R.lpx = W[i].lpx; R.lpx64 = W[i].lpx64;
@@ -908,30 +1294,49 @@ elocal_status elocal_eval_multi(int n_sys, const elocal_t* hs, elocal_stream s, 
     E.sys = h->sys; E.made = M.G[i].md; E.made.wfrag = W[i].frag; E.made.bias = W[i].bias;
     E.x = x[i]; E.B = B[i]; E.ediag = W[i].ediag; E.F = W[i].F; E.lpx = W[i].lpx; E.lpx64 = W[i].lpx64;
     E.zphi = W[i].zphi; E.partial = W[i].partial; E.n_items = M.p[i].n_items; E.ips = M.p[i].ips;
-    E.tpi = M.p[i].tpi; E.lds_bias_off = M.bias_off; E.lds_ctx_off = M.ctx_off; E.lds_lut_off = M.lut_off;
-    for (int l = 0; l < kMaxLayers; ++l) E.lds_frag[l] = M.ldsw ? M.stage[i].frag[l] : -1;
+    E.tpi = M.p[i].tpi;
+    if (M.p[i].prefix) {
+      E.lds_bias_off = M.pre_bias_off; E.lds_ctx_off = M.pre_ctx_off; E.lds_lut_off = M.pre_lut_off;
+      for (int l = 0; l < kMaxLayers; ++l) E.lds_frag[l] = M.pre.lmode == 1 && l <= M.G[i].md.L ? M.G[i].md.foff[l][0] : -1;
+      E.px = M.p[i].px; E.px.stride = M.pre.px.stride; E.px.scratch = (float*)(base + M.pre_off);
+      E.px.queue = W[i].queue; E.top = M.p[i].top;
+      if (M.precision == ELOCAL_FP64) { E.made = M.G[i].pm; E.made.wfrag = W[i].pfrag; E.made.bias = W[i].pbias; }
+    } else {
+      E.lds_bias_off = M.bias_off; E.lds_ctx_off = M.ctx_off; E.lds_lut_off = M.lut_off;
+      for (int l = 0; l < kMaxLayers; ++l) E.lds_frag[l] = M.ldsw ? M.stage[i].frag[l] : -1;
+    }
     HIP_TRY(launch_store_bytes(&E, sizeof(EvalArgs), (char*)d_args + kArgsStride * k, st), "argument store");
   }
-  HIP_TRY(launch_store_bytes(M.first, sizeof(int64_t) * (n_sys + 1), d_first, st), "argument store");
+  const int n_old = n_sys - M.n_pre;
+  bool any_pre = false;
+  for (int k = 0; k < M.n_pre; ++k) any_pre = any_pre || M.p[M.order[k]].n_items > 0;
+  const bool any_old = M.first[n_old] > 0;
+  if (any_old) HIP_TRY(launch_store_bytes(M.first, sizeof(int64_t) * (n_old + 1), d_first, st), "argument store");
   elocal_ctx* h0 = hs[0];
-  const bool timed = h0->timing && M.first[n_sys] > 0;
+  const bool timed = h0->timing && (any_old || any_pre);
   const int slot = (int)(h0->ring_pos % elocal_ctx::kRing);
-  if (M.first[n_sys] > 0) {
-    if (timed) HIP_TRY(hipEventRecord(h0->ev_start[slot], st), "timing event");
+  if (timed) HIP_TRY(hipEventRecord(h0->ev_start[slot], st), "timing event");
+  if (any_pre && M.precision == ELOCAL_FP64)
+    HIP_TRY(launch_prefix_multi_f64(d_args, M.n_pre, M.pre_hmax, M.pre.grid, st), "multi eval launch");
+  else if (any_pre)
+    HIP_TRY(launch_prefix_multi(d_args, M.n_pre, M.pre_hmax, M.pre.cols, M.pre.lmode, M.pre.lds, M.pre.grid,
+                                M.pre.waves, st),
+            "multi eval launch");
+  if (any_old) {
     if (M.precision == ELOCAL_BF16)
-      HIP_TRY(launch_eval_multi_bf16(d_args, d_first, n_sys, M.hmax, M.G[0].nterms, M.cols, M.ldsw, M.inplace, M.lds,
-                                     M.grid, M.waves, st),
+      HIP_TRY(launch_eval_multi_bf16(d_args + M.n_pre, d_first, n_old, M.hmax, M.G[0].nterms, M.cols, M.ldsw,
+                                     M.inplace, M.lds, M.grid, M.waves, st),
               "multi eval launch");
     else
-      HIP_TRY(launch_eval_multi_f64(d_args, d_first, n_sys, M.hmax, M.grid, st), "multi eval launch");
-    if (timed) {
-      HIP_TRY(hipEventRecord(h0->ev_stop[slot], st), "timing event");
-      h0->ring_pos++;
-      h0->recorded++;
-    }
+      HIP_TRY(launch_eval_multi_f64(d_args + M.n_pre, d_first, n_old, M.hmax, M.grid, st), "multi eval launch");
+  }
+  if (timed) {
+    HIP_TRY(hipEventRecord(h0->ev_stop[slot], st), "timing event");
+    h0->ring_pos++;
+    h0->recorded++;
   }
   for (int i = 0; i < n_sys; ++i)
-    if (B[i] > 0) HIP_TRY(launch_reduce(W[i].ediag, W[i].partial, B[i], M.p[i].ips, eloc[i], st), "reduce launch");
+    if (B[i] > 0) HIP_TRY(launch_reduce(W[i].ediag, W[i].partial, B[i], M.p[i].count, M.p[i].fold, M.p[i].lgp, eloc[i], st), "reduce launch");
   return ELOCAL_OK;
 }
 
@@ -1091,7 +1496,7 @@ elocal_status elocal_eval_pauli(elocal_t h, elocal_stream s, const elocal_ansatz
   MadeDev M = G.md;
   M.wfrag = w.frag;
   M.bias = w.bias;
-  HIP_TRY(launch_pack_bf16(M, G.T, (const uint16_t*)a->theta, w.frag, (float*)w.bias, st), "pack launch");
+  HIP_TRY(launch_pack_bf16(M, G.T, (const uint16_t*)a->theta, w.frag, (float*)w.bias, w.queue, st), "pack launch");
   HIP_TRY(launch_pauli_diag(x, B, h->d_pl_off, h->d_pl_z, h->d_pl_coef, w.ediag, st), "diagonal launch");
   RowsArgs R{};
   R.sys = h->sys; R.made = M; R.x = x; R.B = B; R.lpx = w.lpx; R.zphi = w.zphi; R.logpsi = nullptr;
@@ -1111,7 +1516,7 @@ elocal_status elocal_eval_pauli(elocal_t h, elocal_stream s, const elocal_ansatz
     h->ring_pos++;
     h->recorded++;
   }
-  HIP_TRY(launch_reduce(w.ediag, w.partial, B, p.ips, eloc, st), "reduce launch");
+  HIP_TRY(launch_reduce(w.ediag, w.partial, B, p.count, p.fold, p.lgp, eloc, st), "reduce launch");
   return ELOCAL_OK;
 }
 
@@ -1285,7 +1690,7 @@ elocal_status elocal_eval_dedup(elocal_t h, elocal_stream s, const elocal_ansatz
   M.wfrag = w.frag;
   M.bias = w.bias;
   if (G.precision == ELOCAL_BF16)
-    HIP_TRY(launch_pack_bf16(M, G.T, (const uint16_t*)a->theta, w.frag, (float*)w.bias, st), "pack launch");
+    HIP_TRY(launch_pack_bf16(M, G.T, (const uint16_t*)a->theta, w.frag, (float*)w.bias, nullptr, st), "pack launch");
   else
     HIP_TRY(launch_pack_f64(M, G.T, (const double*)a->theta, w.frag, (double*)w.bias, st), "pack launch");
   HIP_TRY(launch_prep(h->sys, x, B, w.ediag, w.F, st), "prep launch");
@@ -1477,7 +1882,7 @@ int64_t elocal_launch_info(elocal_t h, const elocal_ansatz* a, int64_t B, int wh
   if (!h) { fail(ELOCAL_E_INVALID, "handle is null"); return -1; }
   if (B < 0) { fail(ELOCAL_E_INVALID, "B=%lld is negative", (long long)B); return -1; }
   AnsatzGeom G;
-  if (make_geom(h, a, G) != ELOCAL_OK) return -1;
+  if (make_eval_geom(h, a, G) != ELOCAL_OK) return -1;
   const EvalPlan p = plan_eval(h, G, B);
   switch (what) {
     case ELOCAL_INFO_GRID: return p.grid;
@@ -1485,10 +1890,12 @@ int64_t elocal_launch_info(elocal_t h, const elocal_ansatz* a, int64_t B, int wh
     case ELOCAL_INFO_WAVES: return p.waves;
     case ELOCAL_INFO_COLS: return p.cols;
     case ELOCAL_INFO_MAX_WAVES:
+      if (p.prefix) return prefix_waves_bf16(G.hmax, p.cols);
       return G.precision == ELOCAL_BF16 ? eval_waves_bf16(G.hmax, G.nterms, p.cols) : p.waves;
     case ELOCAL_INFO_ITEMS: return p.n_items;
     case ELOCAL_INFO_LDS_BYTES: return (int64_t)p.lds;
     case ELOCAL_INFO_INPLACE: return p.inplace ? 1 : 0;
+    case ELOCAL_INFO_WS_BYTES: return (int64_t)carve_eval(h, G, p, B, nullptr).bytes;
   }
   fail(ELOCAL_E_INVALID, "unknown launch-info query %d", what);
   return -1;

@@ -88,6 +88,49 @@ struct MadeDev {
   const void* bias;            // float (BF16 mode) or double (FP64 mode)
 };
 
+// Geometry of the prefix-shared evaluation (see prefix.hpp). An entry x' of a list changes up
+// to four spin-orbitals c1 < c2 < c3 < c4 of the sample x; x with c1 and c2 changed is its
+// parent. Hidden units of degree <= q depend only on orbitals < q, so below the orbital of c3
+// the entry's network is the parent's. Class b holds the orbitals q whose first affected
+// hidden unit lies in block b (of `unit` units): an entry of class b (that of c3's orbital)
+// starts from its parent's accumulators after the first b blocks of every layer's inputs.
+constexpr int kMaxClasses = 16;
+// What one pass reads of its class and of each layer: eight words each, one scalar load.
+struct PrefixClass {
+  int kin;           // layer-0 input blocks shared at this boundary
+  uint32_t soff;     // slot offset of the boundary in a parent's checkpoint
+  uint32_t oslot;    // slot of output block 0 (wraps below zero; the class's first is obq)
+  int obq;           // first output block of the class (that of orbital qb)
+  int f0, t0;        // layer 0: first fragment of the class's first o-block, in the packing and in LDS
+  int qb;            // first orbital of the class
+  int pad;
+};
+struct PrefixLayer {
+  uint64_t ke;       // k-ranges of the o-blocks, 4 bits each
+  uint32_t boff;     // bias offset
+  int fend, tend;    // fragment offset past the layer's last o-block, in the packing and in LDS
+  int pad[3];
+};
+struct PrefixDev {
+  int nblk;                          // classes = hidden width / unit; 0: path not used
+  int extra;                         // BF16: 1 if the first o-block of a hidden pair j reads j + 2 blocks
+  PrefixClass cls[kMaxClasses + 1];  // class b = orbitals [cls[b].qb, cls[b + 1].qb)
+  PrefixLayer lay[kMaxLayers];
+  int fout[kMaxOutBlocks + 1], tout[kMaxOutBlocks + 1];   // output layer: fragment offset of o-block ob
+  uint32_t stot[kMaxClasses];        // slots of a parent whose c2 is in class b
+  uint32_t rank0[kMaxClasses + 1];   // parents (pairs c1 < c2, ranked c2 (c2 - 1) / 2 + c1) of
+                                     // class b (that of c2): ranks [rank0[b], rank0[b+1])
+  uint32_t seg0[kMaxClasses + 1];    // their segments, ng[b] parents each
+  int ng[kMaxClasses];
+  uint32_t spi;                      // segments per work item; 0: an item is a part of one segment:
+  uint32_t item0[kMaxClasses + 1];   //   the items of class b's segments are [item0[b], item0[b+1])
+  int lgk[kMaxClasses];              //   of a sample, 2^lgk[b] each
+  int lgp;                           //   the largest lgk: every segment has 2^lgp partial sums
+  float* scratch;                    // checkpoints, `stride` floats per wave of the grid
+  uint32_t stride;
+  uint32_t* queue;                   // next work item (zeroed by the packing kernel)
+};
+
 // ----------------------------------------------------------------------------- bit helpers
 template <int NW>
 __device__ __forceinline__ int parity_below(const uint64_t (&x)[NW], int k) {

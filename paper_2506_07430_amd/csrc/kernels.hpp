@@ -11,6 +11,15 @@ struct ThetaLayout {
   uint32_t offwphi, offbphi, P;
 };
 
+// Prefix-shared kernels whose network does not fit in LDS hold its last classes there: the
+// fragments of input blocks >= kb0 (kin0 in layer 0) of the o-blocks >= ob0[l]; those of
+// o-block ob start at foff[l][ob].
+struct PrefixTop {
+  int kb0, kin0;
+  int ob0[kMaxLayers];
+  int32_t foff[kMaxLayers][kMaxOutBlocks + 1];
+};
+
 // Arguments of the fused local-energy kernels.
 struct EvalArgs {
   SysDev sys;
@@ -22,7 +31,7 @@ struct EvalArgs {
   const float* lpx;        // [B][n]   BF16 mode: log p_p(s_p) of each sample
   const double* lpx64;     // [B][n]   FP64 mode
   const double* zphi;      // [B]      phase logit of each sample
-  double* partial;         // [n_items][2]
+  double* partial;         // [partials][2]
   int64_t n_items;
   uint32_t ips;            // work items per sample
   uint32_t tpi;            // row tiles per work item
@@ -38,6 +47,9 @@ struct EvalArgs {
   const uint64_t* pl_z;
   const double* pl_coef;
   uint32_t pl_len;
+  // prefix-shared evaluation only
+  PrefixDev px;
+  PrefixTop top;
 };
 
 // Arguments of the ansatz pass over the samples themselves.
@@ -65,8 +77,9 @@ hipError_t launch_check(const SysDev& S, const uint64_t* x, int64_t B, unsigned 
 
 // Ansatz (precision-specific): pack caller parameters, run the sample pass, run the
 // fused evaluation; `hmax` is the padded hidden width class (32, 64, 128, 256).
+// (queue, where not null, is set to 0)
 hipError_t launch_pack_bf16(const MadeDev& M, const ThetaLayout& T, const uint16_t* theta,
-                            void* frag, float* bias, hipStream_t st);
+                            void* frag, float* bias, uint32_t* queue, hipStream_t st);
 hipError_t launch_rows_bf16(const RowsArgs& A, int hmax, int nterms, hipStream_t st);
 hipError_t launch_eval_bf16(const EvalArgs& A, int hmax, int nterms, int cols, bool lds_weights, bool inplace,
                             size_t lds_bytes, unsigned grid, int waves, hipStream_t st);
@@ -106,6 +119,29 @@ constexpr size_t block_lds_bf16(int waves) { return (size_t)waves * kWaveCtxByte
 // suffices and the pair's k-loop has one runtime test). At width 128 the in-place variant
 // measured 2% slower, so it is not built there.
 constexpr bool inplace_kernel_bf16(int hmax, int nterms) { return hmax >= kLdsPartialWidth && nterms == 2; }
+// Prefix-shared evaluation (two-term BF16 mode, hidden layers of one width >= 64). Waves per
+// block: 16 (four per SIMD, 128 registers each) with one 16-row tile per network pass up to
+// width 128, else 8. lmode: where weights are read from (0: global memory, 1: the whole
+// network in LDS, 2: the last classes, PrefixTop, in LDS).
+constexpr int prefix_waves_bf16(int hmax, int cols) { return hmax <= 128 && cols == 1 ? 16 : 8; }
+constexpr int prefix_lds_blocks(int hmax) { return hmax >= 256 ? 5 : hmax >= 128 ? 3 : 1; }
+constexpr size_t kPrefixWaveBytes = 3840;   // LDS state of one wave (PrefixWave)
+// FP64: 8 waves per block (two per SIMD, 256 registers each), weights from global memory.
+constexpr int kPrefixWavesF64 = 8;
+hipError_t launch_pack_prefix_f64(const MadeDev& M, const ThetaLayout& T, const double* theta, void* frag,
+                                  double* bias, uint32_t* queue, hipStream_t st);
+hipError_t launch_prefix_f64(const EvalArgs& A, int hmax, unsigned grid, hipStream_t st);
+hipError_t launch_prefix_multi_f64(const EvalArgs* args, int n_sys, int hmax, unsigned grid, hipStream_t st);
+#define ELOCAL_PREFIX_DECL(name)                                                                                    \
+  hipError_t launch_prefix_##name(const EvalArgs& A, int lmode, size_t lds, unsigned grid, int waves,               \
+                                  hipStream_t st);                                                                  \
+  hipError_t launch_prefix_multi_##name(const EvalArgs* args, int n_sys, int lmode, size_t lds, unsigned grid,      \
+                                        int waves, hipStream_t st);
+ELOCAL_PREFIX_DECL(w64)
+ELOCAL_PREFIX_DECL(w64c2)
+ELOCAL_PREFIX_DECL(w128)
+ELOCAL_PREFIX_DECL(w128c2)
+ELOCAL_PREFIX_DECL(w256)
 // Several systems in one launch: args[s] describes system s (device copy). BF16: system
 // s owns chunks [first[s], first[s+1]) of `waves` work items each (LDS layout as
 // for one system, with the bias, context and table offsets of args[0] for all). FP64:
@@ -130,8 +166,8 @@ hipError_t launch_rows_f64(const RowsArgs& A, int hmax, hipStream_t st);
 // the caller checks that the network allows it)
 hipError_t launch_eval_f64(const EvalArgs& A, int hmax, bool inplace, unsigned grid, hipStream_t st);
 
-// Sum of the per-item partials plus the diagonal: eloc[b] = ediag[b] + sum_s partial[b][s].
-hipError_t launch_reduce(const double* ediag, const double* partial, int64_t B, uint32_t ips,
+// Local energies: eloc[b] = ediag[b] + sum of the sample's count * 2^lgp partial sums.
+hipError_t launch_reduce(const double* ediag, const double* partial, int64_t B, uint32_t count, uint32_t fold, int lgp,
                          double* eloc, hipStream_t st);
 
 // Full-sector vectors (index = rank_alpha * C(n, n_beta) + rank_beta; binom[o * 65 + i] =

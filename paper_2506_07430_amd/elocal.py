@@ -21,6 +21,7 @@ FP64 = 0
 BF16 = 1      # bfloat16 parameters; two fp16 terms per hidden activation
 BF16X3 = 2    # bfloat16 parameters; three fp16 terms per hidden activation
 OP_CONNECT, OP_EVAL, OP_GRAD = 0, 1, 2
+INFO_WS_BYTES = 8   # ELOCAL_INFO_WS_BYTES of include/elocal.h
 NOALLOC_SCRATCH_MIB = 64   # ELOCAL_NOALLOC_SCRATCH_MIB of include/elocal.h
 
 STATUS = {0: "OK", 1: "E_INVALID", 2: "E_CONFIG", 3: "E_WORKSPACE", 4: "E_NOMEM", 5: "E_DEVICE",
@@ -198,6 +199,8 @@ class Hamiltonian:
 
     def _workspace(self, op: int, B: int, ansatz: Optional[Ansatz] = None) -> Tuple[torch.Tensor, int]:
         need = self.workspace_bytes(op, B, ansatz)
+        if op == OP_EVAL:   # room for every block of the launch
+            need = max(need, int(lib().elocal_launch_info(self._h, ansatz.ref(), int(B), INFO_WS_BYTES)))
         buf = self._ws.get(op)
         if buf is None or buf.numel() < need:
             buf = torch.empty(need, dtype=torch.uint8, device=self.device)

@@ -18,7 +18,7 @@ LIB = os.path.join(PKG, "libelocal.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 SOURCES = ["prefix_w128.hip", "prefix_w128c2.hip", "prefix_w256.hip", "prefix_f64.hip", "made_bf16.hip", "made_f64.hip",
-           "prefix_w64.hip", "hamiltonian.hip", "grad.hip", "kpm.hip", "dedup.hip", "sampler.hip", "api.cpp"]
+           "prefix_w64.hip", "hamiltonian.hip", "grad.hip", "kpm.hip", "sector.hip", "dedup.hip", "sampler.hip", "api.cpp"]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17",
     # packed FP32 instructions stay off in all device code

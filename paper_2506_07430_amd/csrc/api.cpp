@@ -1716,17 +1716,63 @@ namespace {
 struct SectorWs {
   double* partial;   // [waves][2]
   double* vec[3];    // recursion buffers (KPM only)
+  bool product;      // matrix products over strings (see sector.hip)
+  SectorTables T;
+  double *V, *VT, *Ya, *YbT;
   size_t bytes;
   unsigned grid;
 };
+
+// Whether H on the sector's vectors is formed by matrix products over strings. The row lists
+// take over where these would do much more work (few electrons in many orbitals: the products
+// run over all pairs of orbitals) or need tables larger than the vectors, where one string's
+// row of products does not fit in LDS, and for sectors of few entries, whose time is launches
+// (per product, lists -> matrices: 4900 rows of 361 24 -> 35 us, 4356 of 531 31 -> 51 us,
+// 15876 of 621 72 -> 38 us, 853776 of 1819 8.0 -> 0.42 ms).
+constexpr int64_t kProductMinEntries = 5000000;
+bool sector_product(const elocal_ctx* h, SectorTables& T) {
+  const SysDev& S = h->sys;
+  const int64_t dim = h->sector_dim;
+  if (dim * S.C < kProductMinEntries || S.na < 1 || S.nb < 1) return false;
+  T.ndb = h->sector_nb;
+  T.nda = (uint32_t)(dim / T.ndb);
+  T.K = sector_couple_k(S.nSa, T.ndb);
+  T.npair = (uint32_t)(S.n * (S.n + 1) / 2);
+  T.lda_h = (1 + S.nSa + S.nDaa + 15) / 16 * 16;
+  T.ldb_h = (1 + S.nSb + S.nDbb + 15) / 16 * 16;
+  if (sector_couple_lds(T.ndb) > kLdsBytes - 2048) return false;
+  T.ldp = (T.npair + 15) / 16 * 16;
+  if ((uint64_t)T.ldp * T.K > 16ull * S.C) return false;
+  // the kernels' offsets into vectors and integral rows are 32-bit
+  if (dim > 500000000 || (uint64_t)(T.npair + T.nda + 1) * T.ldp > 500000000) return false;
+  return (uint64_t)T.nda * T.lda_h * 12 + (uint64_t)T.ndb * (T.ldb_h * 12 + T.ldp * 2) +
+             (uint64_t)(T.npair + T.nda) * T.ldp * 8 <= 64ull * (uint64_t)dim;
+}
 
 SectorWs carve_sector(const elocal_ctx* h, bool kpm, void* ws) {
   SectorWs w{};
   const int64_t dim = std::max<int64_t>(h->sector_dim, 1);
   w.grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>((dim + 3) / 4, (int64_t)h->cu_count * 8));
+  w.product = sector_product(h, w.T);
   Carve c(ws);
-  w.partial = c.take<double>((size_t)w.grid * 4 * 2);
+  w.partial = c.take<double>(std::max<size_t>((size_t)w.grid * 4, w.product ? w.T.nda : 0) * 2);
   for (int k = 0; k < 3; ++k) w.vec[k] = kpm ? c.take<double>((size_t)dim) : nullptr;
+  if (w.product) {
+    SectorTables& T = w.T;
+    w.V = c.take<double>((size_t)dim);
+    w.VT = c.take<double>((size_t)dim);
+    w.Ya = c.take<double>((size_t)dim);
+    w.YbT = c.take<double>((size_t)dim);
+    T.mask_a = c.take<uint64_t>(T.nda);
+    T.mask_b = c.take<uint64_t>(T.ndb);
+    T.col_a = c.take<uint32_t>((size_t)T.nda * T.lda_h);
+    T.col_b = c.take<uint32_t>((size_t)T.ndb * T.ldb_h);
+    T.val_a = c.take<double>((size_t)T.nda * T.lda_h);
+    T.val_b = c.take<double>((size_t)T.ndb * T.ldb_h);
+    T.one = c.take<uint2>((size_t)T.nda * T.K);
+    T.two = c.take<double>((size_t)(T.npair + T.nda + 1) * T.ldp);
+    T.hop = c.take<uint16_t>((size_t)T.ldp * T.ndb);
+  }
   w.bytes = c.off;
   return w;
 }
@@ -1766,9 +1812,17 @@ elocal_status elocal_sector_apply(elocal_t h, elocal_stream s, double ch, const 
   if (elocal_status st = check_device(h)) return st;
   const SectorWs w = carve_sector(h, false, ws);
   hipStream_t st = (hipStream_t)s;
-  HIP_TRY(launch_sector_apply(h->sys, h->d_binom, h->sector_dim, h->sector_nb, ch, cv, v, cz, z, y, w.partial, w.grid,
-                              st), "sector apply launch");
-  if (dots) HIP_TRY(launch_sector_dots(w.partial, (int64_t)w.grid * 4, dots, nullptr, -1, 0, st), "dots launch");
+  if (w.product) {
+    HIP_TRY(launch_sector_tables(h->sys, w.T, h->d_binom, st), "string tables launch");
+    HIP_TRY(launch_sector_turn(w.T, v, 1, w.V, w.VT, st), "sector turn launch");
+    HIP_TRY(launch_sector_product(w.T, ch, cv, v, cz, z, 1, w.V, w.VT, w.Ya, w.YbT, y, w.partial, st),
+            "sector product launch");
+  } else {
+    HIP_TRY(launch_sector_apply(h->sys, h->d_binom, h->sector_dim, h->sector_nb, ch, cv, v, cz, z, y, w.partial, w.grid,
+                                st), "sector apply launch");
+  }
+  const int64_t nw = w.product ? w.T.nda : (int64_t)w.grid * 4;
+  if (dots) HIP_TRY(launch_sector_dots(w.partial, nw, dots, nullptr, -1, 0, st), "dots launch");
   return ELOCAL_OK;
 }
 
@@ -1783,17 +1837,28 @@ elocal_status elocal_kpm_moments(elocal_t h, elocal_stream s, const double* alph
   if (elocal_status st = check_device(h)) return st;
   const SectorWs w = carve_sector(h, true, ws);
   hipStream_t st = (hipStream_t)s;
-  const int64_t dim = h->sector_dim, nw = (int64_t)w.grid * 4;
-  HIP_TRY(launch_norm2(alpha, dim, moments, st), "norm launch");   // Omega_0
+  const int64_t dim = h->sector_dim, nw = w.product ? w.T.nda : (int64_t)w.grid * 4;
+  HIP_TRY(launch_norm2(alpha, dim, w.partial, moments, st), "norm launch");   // Omega_0
   // a_1 = (H - b) a_0 / a; then a_{n+1} = 2 (H - b) a_n / a - a_{n-1}
   const double* prev = nullptr;
   const double* cur = alpha;
+  if (w.product && n_moments > 1) {   // the recursion runs on vectors in the order alpha first
+    HIP_TRY(launch_sector_tables(h->sys, w.T, h->d_binom, st), "string tables launch");
+    HIP_TRY(launch_sector_turn(w.T, alpha, 1, w.V, w.VT, st), "sector turn launch");
+    cur = w.V;
+  }
   int slot = 0;
   for (int64_t n = 0; 2 * n + 1 < n_moments; ++n) {
     double* nxt = w.vec[slot];
     const double ch = (n == 0 ? 1.0 : 2.0) / a, cv = -(n == 0 ? 1.0 : 2.0) * b / a;
-    HIP_TRY(launch_sector_apply(h->sys, h->d_binom, dim, h->sector_nb, ch, cv, cur, -1.0, prev, nxt, w.partial,
-                                w.grid, st), "sector apply launch");
+    if (w.product) {
+      if (n > 0) HIP_TRY(launch_sector_turn(w.T, cur, 0, nullptr, w.VT, st), "sector turn launch");
+      HIP_TRY(launch_sector_product(w.T, ch, cv, cur, -1.0, prev, 0, cur, w.VT, w.Ya, w.YbT, nxt, w.partial,
+                                    st), "sector product launch");
+    } else {
+      HIP_TRY(launch_sector_apply(h->sys, h->d_binom, dim, h->sector_nb, ch, cv, cur, -1.0, prev, nxt, w.partial,
+                                  w.grid, st), "sector apply launch");
+    }
     HIP_TRY(launch_sector_dots(w.partial, nw, nullptr, moments, n, n_moments, st), "moments launch");
     prev = cur;
     cur = nxt;

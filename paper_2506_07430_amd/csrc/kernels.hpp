@@ -175,9 +175,33 @@ hipError_t launch_reduce(const double* ediag, const double* partial, int64_t B, 
 hipError_t launch_sector_apply(const SysDev& S, const uint32_t* binom, int64_t dim, uint32_t nb_dim, double ch,
                                double cv, const double* v, double cz, const double* z, double* y, double* partial,
                                unsigned grid, hipStream_t st);
+// The string tables of the matrix-product route (see sector.hip) and its vectors' shape.
+struct SectorTables {
+  uint32_t nda, ndb;         // strings of either spin
+  uint32_t K, npair;         // excitations of an alpha string (see sector_couple_k), pairs r <= s
+  uint32_t lda_h, ldb_h;     // entries per row of the strings' H, padded to 16
+  uint32_t ldp;              // npair, padded to 16
+  uint64_t *mask_a, *mask_b;
+  uint32_t *col_a, *col_b;
+  double *val_a, *val_b;
+  uint2* one;
+  double* two;
+  uint16_t* hop;
+};
+size_t sector_couple_lds(uint32_t ndb);
+uint32_t sector_couple_k(uint32_t singles, uint32_t ndb);
+hipError_t launch_sector_tables(const SysDev& S, const SectorTables& T, const uint32_t* binom, hipStream_t st);
+// out (if not null) = v in the order alpha first, outT its transpose
+hipError_t launch_sector_turn(const SectorTables& T, const double* v, int sign, double* out, double* outT,
+                              hipStream_t st);
+// y = ch H v + cv v + cz z with V, VT the turned v; partial[nda][2] sums y.y and y.v
+hipError_t launch_sector_product(const SectorTables& T, double ch, double cv, const double* v,
+                                 double cz, const double* z, int sign, const double* V, const double* VT, double* Ya,
+                                 double* YbT, double* y, double* partial, hipStream_t st);
 hipError_t launch_sector_dots(const double* partial, int64_t nw, double* dots, double* mu, int64_t n,
                               int64_t n_moments, hipStream_t st);
-hipError_t launch_norm2(const double* v, int64_t dim, double* out, hipStream_t st);
+// out = v.v; partial holds 256 doubles, or dim / 4 if that is less
+hipError_t launch_norm2(const double* v, int64_t dim, double* partial, double* out, hipStream_t st);
 hipError_t launch_sector_basis(const SysDev& S, const uint32_t* binom, int64_t dim, uint32_t nb_dim, uint64_t* x,
                                hipStream_t st);
 hipError_t launch_line_shape(const double* mu, int64_t N, const double* w, int64_t P, double* rho, hipStream_t st);

@@ -8,6 +8,8 @@
 // row's canonical connected list (the same generator and Slater--Condon values as the
 // local-energy path), ranks every x' and gathers v there. The row's sum, a fixed xor
 // tree over the wave, is bitwise repeatable; nothing per row is stored in HBM.
+#include <algorithm>
+
 #include "elocal_internal.hpp"
 #include "kernels.hpp"
 
@@ -225,18 +227,21 @@ __global__ void __launch_bounds__(1024) k_sector_dots(const double* __restrict__
   }
 }
 
-// Omega_0 = <a_0|a_0> (fixed tree, one block).
+// Omega_0 = <a_0|a_0>: sums of v.v over strided blocks, or (SQUARE false) of v, in fixed trees
+// (one block over a sector of 853776: 216 us).
+template <bool SQUARE>
 __global__ void __launch_bounds__(1024) k_norm2(const double* __restrict__ v, int64_t dim, double* __restrict__ out) {
   __shared__ double s[1024];
   double a = 0.0;
-  for (int64_t i = threadIdx.x; i < dim; i += 1024) a += v[i] * v[i];
+  for (int64_t i = (int64_t)blockIdx.x * 1024 + threadIdx.x; i < dim; i += (int64_t)gridDim.x * 1024)
+    a += SQUARE ? v[i] * v[i] : v[i];
   s[threadIdx.x] = a;
   __syncthreads();
   for (int off = 512; off >= 1; off >>= 1) {
     if ((int)threadIdx.x < off) s[threadIdx.x] += s[threadIdx.x + off];
     __syncthreads();
   }
-  if (threadIdx.x == 0) out[0] = s[0];
+  if (threadIdx.x == 0) out[blockIdx.x] = s[0];
 }
 
 // Jackson-damped line shape: rho(w) = [g_0 Omega_0 + 2 sum_n g_n Omega_n T_n(w)] /
@@ -310,8 +315,14 @@ hipError_t launch_sector_dots(const double* partial, int64_t nw, double* dots, d
   return hipGetLastError();
 }
 
-hipError_t launch_norm2(const double* v, int64_t dim, double* out, hipStream_t st) {
-  hipLaunchKernelGGL(k_norm2, dim3(1), dim3(1024), 0, st, v, dim, out);
+hipError_t launch_norm2(const double* v, int64_t dim, double* partial, double* out, hipStream_t st) {
+  const unsigned blocks = (unsigned)std::min<int64_t>(256, (dim + 4095) / 4096);
+  if (blocks <= 1) {
+    hipLaunchKernelGGL(k_norm2<true>, dim3(1), dim3(1024), 0, st, v, dim, out);
+    return hipGetLastError();
+  }
+  hipLaunchKernelGGL(k_norm2<true>, dim3(blocks), dim3(1024), 0, st, v, dim, partial);
+  hipLaunchKernelGGL(k_norm2<false>, dim3(1), dim3(1024), 0, st, partial, (int64_t)blocks, out);
   return hipGetLastError();
 }
 

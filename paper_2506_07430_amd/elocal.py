@@ -365,16 +365,13 @@ class Hamiltonian:
     def sector_dim(self) -> int:
         return int(lib().elocal_sector_dim(self._h))
 
-    def _sector_ws(self, kpm: bool) -> Tuple[torch.Tensor, int]:
+    def _sector_ws(self, kpm: bool, stream) -> Tuple[torch.Tensor, int]:
+        # per call: it holds vectors, which calls on other streams or threads must not share
         need = int(lib().elocal_sector_workspace_bytes(self._h, int(kpm)))
         if need == 0:
             raise ElocalError(6, lib().elocal_last_error().decode())
-        key = "sector_kpm" if kpm else "sector"
-        buf = self._ws.get(key)
-        if buf is None or buf.numel() < need:
-            buf = torch.empty(need, dtype=torch.uint8, device=self.device)
-            self._ws[key] = buf
-        return buf, buf.numel()
+        with torch.cuda.stream(stream):
+            return torch.empty(need, dtype=torch.uint8, device=self.device), need
 
     def sector_basis(self, stream=None) -> torch.Tensor:
         """Every determinant of the sector, [dim, W] int64 (row r = index r)."""
@@ -393,7 +390,7 @@ class Hamiltonian:
                 raise ElocalError(1, f"sector vectors must be contiguous CUDA float64 of {dim} entries")
         y = out if out is not None else torch.empty(dim, dtype=torch.float64, device=v.device)
         d = torch.empty(2, dtype=torch.float64, device=v.device) if dots else None
-        ws, nb = self._sector_ws(False)
+        ws, nb = self._sector_ws(False, stream)
         _check(lib().elocal_sector_apply(self._h, _stream(stream), float(ch), v.data_ptr(), float(cv), _ptr(z),
                                          float(cz), y.data_ptr(), ws.data_ptr(), nb, _ptr(d)))
         return (y, d) if dots else y
@@ -403,7 +400,7 @@ class Hamiltonian:
         if alpha.dtype != torch.float64 or not alpha.is_cuda or alpha.numel() != self.sector_dim:
             raise ElocalError(1, "alpha must be a CUDA float64 sector vector")
         mu = torch.empty(int(n_moments), dtype=torch.float64, device=alpha.device)
-        ws, nb = self._sector_ws(True)
+        ws, nb = self._sector_ws(True, stream)
         _check(lib().elocal_kpm_moments(self._h, _stream(stream), alpha.contiguous().data_ptr(), int(n_moments),
                                         float(a), float(b), ws.data_ptr(), nb, mu.data_ptr()))
         return mu

@@ -513,6 +513,117 @@ __global__ void __launch_bounds__(256) k_bas_probs(SysDev S, MadeDev M, HiddenCa
   }, k >> 2, (k >> 2) + 1, caps);   // only orbital k's output block and what it depends on
 }
 
+// The same from LDS: a block stages the fragments that orbital k's logits need (packed weights
+// of the units of degree <= k, and the orbital's output block) and its waves share them over
+// many blocks of 16 prefixes; hidden layers are updated in place, so that three waves fit per
+// SIMD. Reading the weights from cache again for every 16 prefixes asked for up to 130 KB per
+// block of rows: 24 orbitals, 128x2, 10^6 draws 8.7 ms for all orbitals, 6.6 ms here, of which
+// 4.2 ms are matrix instructions (out of place at two waves per SIMD 7.7 ms). Sums are in the
+// same order; skipped k-steps have masked weights.
+struct BasStage {
+  int nob[kMaxLayers];                          // blocks of hidden layer l
+  uint16_t at[kMaxLayers][kMaxOutBlocks];       // first staged fragment of an o-block (output: [0])
+  uint16_t ke[kMaxLayers][kMaxOutBlocks];       // its k-steps
+  uint32_t bias;                                // biases in LDS (doubles), 16 per o-block in staging order
+};
+constexpr int kBasWaves = 12;
+template <int HMAX, int NW>
+__global__ void __launch_bounds__(64 * kBasWaves, 3) k_bas_probs_lds(SysDev S, MadeDev M, BasStage G,
+                                                                     const uint64_t* __restrict__ pre,
+                                                                     const int64_t* __restrict__ Ud, int64_t cap,
+                                                                     int k, double* __restrict__ probs) {
+  extern __shared__ __attribute__((aligned(16))) double WL[];
+  constexpr int OB = HMAX / 16, KS = HMAX / 4;
+  const int lane = threadIdx.x & 63, g = lane >> 4, r16 = lane & 15;
+  const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int64_t U = min(*Ud, cap);
+  if ((int64_t)blockIdx.x * (16 * kBasWaves) >= U) return;
+  const int obk = k >> 2;
+  for (int l = 0, j = 0; l <= M.L; ++l) {
+    const int nob = l < M.L ? G.nob[l] : 1;
+    for (int o = 0; o < nob; ++o, ++j) {
+      if (j % kBasWaves != wid) continue;
+      const int ob = l < M.L ? o : obk;
+      const int n2 = G.ke[l][o] * 32, have = min((int)G.ke[l][o], M.nk[l]) * 32;   // two doubles a lane
+      const double2* src = (const double2*)((const double*)M.wfrag + (size_t)(M.woff[l] + (uint32_t)(ob * M.nk[l])) * 64);
+      double2* dst = (double2*)(WL + (size_t)G.at[l][o] * 64);
+      if (lane < 16) WL[G.bias + 16 * j + lane] = ((const double*)M.bias)[M.boff[l] + 16 * ob + lane];
+#pragma unroll 4
+      for (int i = lane; i < n2; i += 64) dst[i] = i < have ? src[i] : make_double2(0.0, 0.0);
+    }
+  }
+  __syncthreads();
+  const int n = S.n, na = S.na, nb = S.nb, left = n - k - 1;
+  const double* wl = WL + lane;
+  auto bias4 = [&](int j) {
+    const double2* p = (const double2*)(WL + G.bias + 16 * j + 4 * g);
+    const double2 lo = p[0], hi = p[1];
+    return f64x4{lo.x, lo.y, hi.x, hi.y};
+  };
+  const int64_t stride = (int64_t)gridDim.x * (16 * kBasWaves);
+  for (int64_t b0 = ((int64_t)blockIdx.x * kBasWaves + wid) * 16; b0 < U; b0 += stride) {
+    const int64_t row = b0 + r16, bb = row < U ? row : b0;
+    uint64_t xr[NW];
+#pragma unroll
+    for (int w = 0; w < NW; ++w) xr[w] = pre[bb * NW + w];
+    // input 4 ks + g is bit 4 ks of the row shifted down by g
+    uint64_t xg[NW];
+#pragma unroll
+    for (int w = 0; w < NW; ++w) xg[w] = xr[w] >> g | (w + 1 < NW && g ? xr[w + 1 < NW ? w + 1 : w] << (64 - g) : 0ull);
+    f64x4 cur[OB];
+#pragma unroll
+    for (int ob = 0; ob < OB; ++ob) {
+      if (ob < G.nob[0]) {
+        f64x4 acc = bias4(ob);
+        kloop_f64_whole<16 * NW, 4>(WPtr64{wl + (size_t)G.at[0][ob] * 64}, (int)G.ke[0][ob], [&](int ks, double w) {
+          acc = mfma_f64(w, (double)((uint32_t)(xg[ks >> 4] >> (4 * (ks & 15))) & 1u), acc);
+        });
+        cur[ob] = relu4(acc);
+      }
+    }
+    int j0 = G.nob[0];
+    for (int l = 1; l < M.L; j0 += G.nob[l], ++l) {   // in place, as in mlp_f64
+      const int nob = G.nob[l];
+      f64x4 pend = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int ob = OB - 1; ob >= 0; --ob) {
+        if (ob < nob) {
+          f64x4 acc = bias4(j0 + ob);
+          kloop_f64_whole<KS, 4>(WPtr64{wl + (size_t)G.at[l][ob] * 64}, (int)G.ke[l][ob],
+                                 [&](int ks, double w) { acc = mfma_f64(w, cur[ks >> 2][ks & 3], acc); });
+          if (ob + 1 < nob) cur[ob + 1 < OB ? ob + 1 : ob] = pend;
+          pend = relu4(acc);
+        }
+      }
+      cur[0] = pend;
+    }
+    f64x4 z = bias4(j0);
+    kloop_f64_whole<KS, 4>(WPtr64{wl + (size_t)G.at[M.L][0] * 64}, (int)G.ke[M.L][0],
+                           [&](int ks, double w) { z = mfma_f64(w, cur[ks >> 2][ks & 3], z); });
+    // the conditional, one occupation per lane group
+    const int cu = count_spin_below<NW>(xr, k, 0), cd = count_spin_below<NW>(xr, k, 1);
+    double zq[4], m = -INFINITY, mine = 0.0;
+    bool my_ok = false;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      zq[q] = __shfl(z[q], 16 * (k & 3) + r16);
+      const int u = cu + (q & 1), d = cd + (q >> 1);
+      const bool ok = (u <= na) && (d <= nb) && (u + left >= na) && (d + left >= nb);
+      if (ok) m = fmax(m, zq[q]);
+      if (q == g) {
+        mine = zq[q];
+        my_ok = ok;
+      }
+    }
+    const double e = my_ok ? exp(mine - m) : 0.0;
+    double sum = 0.0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) sum += __shfl(e, 16 * q + r16);
+    const double lse = m + log(sum);
+    if (row < U) probs[row * 4 + g] = my_ok ? exp(mine - lse) : 0.0;
+  }
+}
+
 hipError_t launch_pack_f64(const MadeDev& M, const ThetaLayout& T, const double* theta, void* frag,
                            double* bias, hipStream_t st) {
   const uint32_t total = M.nfrag * 64u > M.nbias ? M.nfrag * 64u : M.nbias;
@@ -607,6 +718,49 @@ hipError_t launch_eval_f64(const EvalArgs& A, int hmax, bool inplace, unsigned g
 }
 
 template <int HMAX>
+static hipError_t bas_probs_lds_h(const SysDev& S, const MadeDev& M, const BasStage& G, size_t lds,
+                                  const uint64_t* pre, const int64_t* Ud, int64_t cap, int k, double* probs,
+                                  hipStream_t st) {
+  auto kern = S.W == 1 ? k_bas_probs_lds<HMAX, 1> : k_bas_probs_lds<HMAX, 2>;
+  if (lds > 65536) {
+    const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+  }
+  // as many blocks as a chip of 256 CUs holds
+  const int64_t rows = 16 * kBasWaves;
+  const unsigned blocks = (unsigned)std::min<int64_t>((cap + rows - 1) / rows, 256);
+  hipLaunchKernelGGL(kern, dim3(blocks), dim3(64 * kBasWaves), lds, st, S, M, G, pre, Ud, cap, k, probs);
+  return hipGetLastError();
+}
+
+// The fragments that orbital k's logits need (BasStage); false where they do not fit in LDS or
+// whose layers cannot be updated in place in the registers of twelve waves.
+static bool plan_bas_stage(const MadeDev& M, const HiddenCaps& caps, int k, BasStage& G, size_t& lds, int& hmax) {
+  size_t at = 0, blocks = 0;
+  int wide = 1;
+  for (int l = 0; l <= M.L; ++l) {
+    const int nob = l < M.L ? std::min(M.nob[l], caps.nob[l]) : 1;
+    const int kmax = l == 0 ? M.nk[0] : 4 * G.nob[l - 1];
+    for (int o = 0; o < nob; ++o) {
+      const int ke = std::min<int>(M.kend[l][l < M.L ? o : k >> 2], kmax);
+      G.at[l][o] = (uint16_t)at;
+      G.ke[l][o] = (uint16_t)((ke + 3) / 4 * 4);   // (past the layer's k-steps: zeros)
+      if (l > 0 && l < M.L && G.ke[l][o] > 4 * (o + 2)) return false;
+      at += G.ke[l][o];
+    }
+    blocks += nob;
+    if (l < M.L) {
+      G.nob[l] = nob;
+      wide = std::max(wide, nob);
+    }
+  }
+  G.bias = (uint32_t)at * 64;
+  lds = at * 512 + blocks * 128;
+  hmax = wide <= 2 ? 32 : wide <= 4 ? 64 : 128;
+  return wide <= 8 && lds <= 160 * 1024;
+}
+
+template <int HMAX>
 static hipError_t bas_probs_h(const SysDev& S, const MadeDev& M, const uint64_t* pre, const int64_t* Ud, int64_t cap,
                               int k, double* probs, hipStream_t st) {
   const int64_t waves = (cap + 15) / 16;
@@ -620,6 +774,14 @@ static hipError_t bas_probs_h(const SysDev& S, const MadeDev& M, const uint64_t*
     int cnt = 0;
     for (int r = 0; r < q && r < k; ++r) cnt += (w > r) ? (w - r - 1) / q + 1 : 0;   // degree r + 1 <= k
     caps.nob[l] = (cnt + 15) / 16;
+  }
+  BasStage G{};
+  size_t lds = 0;
+  int run = 0;
+  if (plan_bas_stage(M, caps, k, G, lds, run)) {
+    if (run == 32) return bas_probs_lds_h<32>(S, M, G, lds, pre, Ud, cap, k, probs, st);
+    if (run == 64) return bas_probs_lds_h<64>(S, M, G, lds, pre, Ud, cap, k, probs, st);
+    return bas_probs_lds_h<128>(S, M, G, lds, pre, Ud, cap, k, probs, st);
   }
   if (S.W == 1)
     hipLaunchKernelGGL((k_bas_probs<HMAX, 1>), dim3(blocks), dim3(256), 0, st, S, M, caps, pre, Ud, cap, k, probs);

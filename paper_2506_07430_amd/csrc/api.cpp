@@ -555,10 +555,10 @@ elocal_status make_eval_geom(const elocal_ctx* h, const elocal_ansatz* a, Ansatz
 // else as long as its longest segment (24 orbitals, 64 samples: 456 us whole, 356 in parts, 428
 // and 584 in parts of a half and a third of the share, because a part runs its segment's
 // parents again; 60 orbitals, 8 samples: 2.67 ms, 2.65). The sums are the same bit for bit:
-// see add_to_slot, k_reduce.
+// see add_to_slot, k_reduce. `chip`: the part of the chip that the batch has to itself.
 constexpr int64_t kFineItems = 131072;   // a few tens of items per wave of the chip
 constexpr int kMaxLgParts = 4;
-void plan_items(const elocal_ctx* h, int64_t B, EvalPlan& p) {
+void plan_items(const elocal_ctx* h, int64_t B, double chip, EvalPlan& p) {
   PrefixDev& X = p.px;
   const uint32_t nseg = X.seg0[X.nblk];
   const uint32_t group = h->tune_groups > 0 ? (uint32_t)std::min<int64_t>(h->tune_groups, nseg)
@@ -581,7 +581,7 @@ void plan_items(const elocal_ctx* h, int64_t B, EvalPlan& p) {
       const double sb = pb * pb * bv * bv / 2 + (1 - pb) * (1 - pb) * bo * bo / 2 + 2 * pb * (1 - pb) * mixed;
       return 0.5 * cross + 0.25 * (sa + sb);
     };
-    const double share = std::max(64.0, (double)B * h->sys.C / ((double)p.waves * h->cu_count));
+    const double share = std::max(64.0, (double)B * h->sys.C / (chip * p.waves * h->cu_count));
     for (int c = 0; c < X.nblk; ++c) {
       int k = 0;
       while (k < kMaxLgParts && ((int64_t)nseg * B << (k + 1)) <= kFineItems &&
@@ -599,7 +599,7 @@ void plan_items(const elocal_ctx* h, int64_t B, EvalPlan& p) {
   p.tpi = std::max(1u, X.spi);
 }
 
-EvalPlan plan_eval(const elocal_ctx* h, const AnsatzGeom& G, int64_t B, int64_t list_len = -1) {
+EvalPlan plan_eval(const elocal_ctx* h, const AnsatzGeom& G, int64_t B, int64_t list_len = -1, double chip = 1.0) {
   EvalPlan p{};
   // BF16: groups of 64 entries (one per lane), 8 per item; FP64: tiles of 16, 16 per item
   p.rows_per_tile = (G.precision == ELOCAL_BF16) ? 64 : 16;
@@ -634,7 +634,7 @@ EvalPlan plan_eval(const elocal_ctx* h, const AnsatzGeom& G, int64_t B, int64_t 
   }
   if (p.prefix) {
     plan_prefix(h, G, p.px);
-    plan_items(h, B, p);
+    plan_items(h, B, chip, p);
     if (G.precision == ELOCAL_BF16) {
       size_t wb = 0;
       plan_prefix_lds(G, G.hmax, p.waves, G.bbytes, p, wb);
@@ -1129,7 +1129,7 @@ elocal_status plan_multi(int n_sys, const elocal_t* hs, const elocal_ansatz* con
   M.hmax = M.pre_hmax = 32;
   M.n_pre = 0;
   size_t off = 0;
-  double cost[ELOCAL_MAX_SYSTEMS];
+  double cost[ELOCAL_MAX_SYSTEMS], work[ELOCAL_MAX_SYSTEMS], pre_work = 0.0;
   for (int s = 0; s < n_sys; ++s) {
     if (!hs[s]) return fail(ELOCAL_E_INVALID, "handle %d is null", s);
     if (hs[s]->dev != hs[0]->dev) return fail(ELOCAL_E_INVALID, "handles %d and 0 are on different devices", s);
@@ -1137,7 +1137,15 @@ elocal_status plan_multi(int n_sys, const elocal_t* hs, const elocal_ansatz* con
     if (elocal_status e = make_eval_geom(hs[s], a[s], M.G[s])) return e;
     if (s > 0 && M.G[s].mode != M.G[0].mode)
       return fail(ELOCAL_E_INVALID, "ansatz %d has another precision than ansatz 0", s);
-    M.p[s] = plan_eval(hs[s], M.G[s], B[s]);
+    work[s] = 0.0;   // of the whole batch: entries x dense multiply-adds
+    for (int l = 0; l <= M.G[s].md.L; ++l) work[s] += (double)M.G[s].md.nin[l] * M.G[s].md.nout[l];
+    work[s] *= (double)B[s] * hs[s]->sys.C;
+    if (M.G[s].prefix) pre_work += work[s];
+  }
+  for (int s = 0; s < n_sys; ++s) {
+    // the BF16 launch gives each system its share of the blocks
+    const bool shared = M.G[s].prefix && M.G[s].precision == ELOCAL_BF16 && work[s] > 0.0;
+    M.p[s] = plan_eval(hs[s], M.G[s], B[s], -1, shared ? work[s] / pre_work : 1.0);
     if (M.p[s].prefix) {
       ++M.n_pre;
       M.pre_hmax = std::max(M.pre_hmax, M.G[s].hmax);
@@ -1178,7 +1186,7 @@ elocal_status plan_multi(int n_sys, const elocal_t* hs, const elocal_ansatz* con
       all = all && M.p[s].lmode != 0;
       wmax = std::max(wmax, wb);
       q.px.stride = std::max(q.px.stride, M.p[s].px.stride);
-      items = std::max(items, M.p[s].n_items);
+      items += M.p[s].n_items;
     }
     q.lmode = all ? M.p[M.order[0]].lmode : 0;
     M.pre_bias_off = q.lmode ? (uint32_t)wmax : 0u;
@@ -1188,6 +1196,13 @@ elocal_status plan_multi(int n_sys, const elocal_t* hs, const elocal_ansatz* con
     const int64_t want = (items + q.waves - 1) / q.waves;
     q.grid = (unsigned)std::max<int64_t>(1, std::min(want, grid_cap(hs[0], q.waves)));
     q.grid = std::min(q.grid, (unsigned)hs[0]->cu_count * (unsigned)std::max(1, full / q.waves));
+    // blocks start with the systems in turn, as many with each as its part of the work
+    double done = 0.0;
+    for (int i = 0; i < M.n_pre; ++i) {
+      const int s = M.order[i];
+      M.p[s].px.block0 = pre_work > 0.0 ? (uint32_t)(done / pre_work * q.grid + 0.5) : 0u;
+      done += work[s];
+    }
     M.pre_off = off;
     off = align256(off + (size_t)q.grid * q.waves * q.px.stride * sizeof(float));
   }

@@ -129,6 +129,7 @@ struct PrefixDev {
   float* scratch;                    // checkpoints, `stride` floats per wave of the grid
   uint32_t stride;
   uint32_t* queue;                   // next work item (zeroed by the packing kernel)
+  uint32_t block0;                   // several systems: the first block that starts with this one
 };
 
 // ----------------------------------------------------------------------------- bit helpers

@@ -292,6 +292,7 @@ struct EvalPlan {
   uint32_t rows_per_tile, tpi, ips;
   uint32_t count, fold;   // sums per sample (of 2^lgp partial sums each), and how many the
   int lgp;                // reduction folds to one before it adds those of a sample
+  uint32_t parts;         // BF16: parts of an item, each with its lanes' sums (0: items are whole)
   int64_t n_items;
   bool ldsw;
   StagePlan stage;  // BF16: which layers are staged (biases follow the weights, then the
@@ -599,6 +600,8 @@ void plan_items(const elocal_ctx* h, int64_t B, double chip, EvalPlan& p) {
   p.tpi = std::max(1u, X.spi);
 }
 
+constexpr int64_t kFewItems = 16384;     // four per wave slot of a chip of 256 CUs
+constexpr int64_t kMaxLaneSums = 32768;  // parts of 1 KiB of sums
 EvalPlan plan_eval(const elocal_ctx* h, const AnsatzGeom& G, int64_t B, int64_t list_len = -1, double chip = 1.0) {
   EvalPlan p{};
   // BF16: groups of 64 entries (one per lane), 8 per item; FP64: tiles of 16, 16 per item
@@ -613,6 +616,26 @@ EvalPlan plan_eval(const elocal_ctx* h, const AnsatzGeom& G, int64_t B, int64_t 
   p.count = p.ips;
   p.fold = 1;
   p.lgp = 0;
+  // A batch with few items has parts of items instead: an item's groups are run one after the
+  // other (8 orbitals, four batches of 4 to 43 samples in one launch: 198 us, 71 us so). The sums
+  // are the same: FP64 items add their groups of 64 one by one, and the reduction folds the
+  // parts in that order; BF16 parts leave their lanes' sums (adding every group over the lanes
+  // cost the narrowest networks 2 to 9%), which a kernel of their own adds.
+  if (!G.prefix && h->tune_groups <= 0 && p.n_items <= kFewItems) {
+    if (G.precision == ELOCAL_BF16) {
+      const uint32_t groups = (uint32_t)((rows + 63) / 64);
+      if ((int64_t)groups * B <= kMaxLaneSums) {
+        p.parts = p.tpi;   // (of one group each: a part of several would add them in another order)
+        p.tpi = 1;
+        p.ips = groups;
+      }
+    } else {
+      p.fold = p.tpi / 4;
+      p.tpi = 4;
+      p.ips = p.count = (uint32_t)((rows + 63) / 64);
+    }
+    p.n_items = (int64_t)p.ips * B;
+  }
   for (int l = 0; l < kMaxLayers; ++l) p.stage.frag[l] = -1;
   if (G.precision == ELOCAL_BF16) {
     p.cols = eval_cols_default_bf16(G.hmax, G.nterms);
@@ -696,6 +719,7 @@ struct EvalWs {
   double* lpx64;
   double* zphi;
   double* partial;
+  double* lanes;     // BF16 parts of items: their lanes' sums
   uint32_t* queue;   // prefix-shared evaluation: the work-item ticket and the checkpoints
   float* scratch;
   void* pfrag;       // FP64 prefix-shared evaluation: its own packing of the network
@@ -721,6 +745,7 @@ EvalWs carve_eval(const elocal_ctx* h, const AnsatzGeom& G, const EvalPlan& p, i
   }
   w.zphi = c.take<double>(std::max<int64_t>(B, 1));
   w.partial = c.take<double>(std::max<size_t>(((size_t)p.count * B << p.lgp) * 2, 1));
+  w.lanes = p.parts ? c.take<double>((size_t)p.n_items * 128) : nullptr;
   w.queue = nullptr;
   w.scratch = nullptr;
   if (p.prefix) {
@@ -1035,7 +1060,7 @@ elocal_status elocal_eval(elocal_t h, elocal_stream s, const elocal_ansatz* a, c
   else HIP_TRY(launch_rows_f64(R, G.hmax, st), "sample pass launch");
   EvalArgs E{};
   E.sys = h->sys; E.made = M; E.x = x; E.B = B; E.ediag = w.ediag; E.F = w.F; E.lpx = w.lpx;
-  E.lpx64 = w.lpx64; E.zphi = w.zphi; E.partial = w.partial; E.n_items = p.n_items; E.ips = p.ips;
+  E.lpx64 = w.lpx64; E.zphi = w.zphi; E.partial = p.parts ? w.lanes : w.partial; E.lane_sums = p.parts != 0; E.n_items = p.n_items; E.ips = p.ips;
   E.tpi = p.tpi;
   const bool timed = h->timing && p.n_items > 0;
   const int slot = (int)(h->ring_pos % elocal_ctx::kRing);
@@ -1061,6 +1086,7 @@ elocal_status elocal_eval(elocal_t h, elocal_stream s, const elocal_ansatz* a, c
     h->ring_pos++;
     h->recorded++;
   }
+  if (p.parts) HIP_TRY(launch_fold_items(w.lanes, B, p.count, p.ips, p.parts, w.partial, st), "fold launch");
   HIP_TRY(launch_reduce(w.ediag, w.partial, B, p.count, p.fold, p.lgp, eloc, st), "reduce launch");
   return ELOCAL_OK;
 }
@@ -1308,7 +1334,7 @@ elocal_status elocal_eval_multi(int n_sys, const elocal_t* hs, elocal_stream s, 
     EvalArgs E{};
     E.sys = h->sys; E.made = M.G[i].md; E.made.wfrag = W[i].frag; E.made.bias = W[i].bias;
     E.x = x[i]; E.B = B[i]; E.ediag = W[i].ediag; E.F = W[i].F; E.lpx = W[i].lpx; E.lpx64 = W[i].lpx64;
-    E.zphi = W[i].zphi; E.partial = W[i].partial; E.n_items = M.p[i].n_items; E.ips = M.p[i].ips;
+    E.zphi = W[i].zphi; E.partial = M.p[i].parts ? W[i].lanes : W[i].partial; E.lane_sums = M.p[i].parts != 0; E.n_items = M.p[i].n_items; E.ips = M.p[i].ips;
     E.tpi = M.p[i].tpi;
     if (M.p[i].prefix) {
       E.lds_bias_off = M.pre_bias_off; E.lds_ctx_off = M.pre_ctx_off; E.lds_lut_off = M.pre_lut_off;
@@ -1350,8 +1376,13 @@ elocal_status elocal_eval_multi(int n_sys, const elocal_t* hs, elocal_stream s, 
     h0->ring_pos++;
     h0->recorded++;
   }
-  for (int i = 0; i < n_sys; ++i)
-    if (B[i] > 0) HIP_TRY(launch_reduce(W[i].ediag, W[i].partial, B[i], M.p[i].count, M.p[i].fold, M.p[i].lgp, eloc[i], st), "reduce launch");
+  for (int i = 0; i < n_sys; ++i) {
+    const EvalPlan& p = M.p[i];
+    if (B[i] <= 0) continue;
+    if (p.parts)
+      HIP_TRY(launch_fold_items(W[i].lanes, B[i], p.count, p.ips, p.parts, W[i].partial, st), "fold launch");
+    HIP_TRY(launch_reduce(W[i].ediag, W[i].partial, B[i], p.count, p.fold, p.lgp, eloc[i], st), "reduce launch");
+  }
   return ELOCAL_OK;
 }
 
@@ -1518,7 +1549,7 @@ elocal_status elocal_eval_pauli(elocal_t h, elocal_stream s, const elocal_ansatz
   HIP_TRY(launch_rows_bf16(R, G.hmax, G.nterms, st), "sample pass launch");
   EvalArgs E{};
   E.sys = h->sys; E.made = M; E.x = x; E.B = B; E.ediag = w.ediag; E.F = w.F; E.lpx = w.lpx; E.zphi = w.zphi;
-  E.partial = w.partial; E.n_items = p.n_items; E.ips = p.ips; E.tpi = p.tpi;
+  E.partial = p.parts ? w.lanes : w.partial; E.lane_sums = p.parts != 0; E.n_items = p.n_items; E.ips = p.ips; E.tpi = p.tpi;
   set_lds_args(E, p, G.bbytes);
   E.pl_mask = h->d_pl_mask; E.pl_off = h->d_pl_off; E.pl_z = h->d_pl_z; E.pl_coef = h->d_pl_coef;
   E.pl_len = (uint32_t)h->pl_len;
@@ -1531,6 +1562,7 @@ elocal_status elocal_eval_pauli(elocal_t h, elocal_stream s, const elocal_ansatz
     h->ring_pos++;
     h->recorded++;
   }
+  if (p.parts) HIP_TRY(launch_fold_items(w.lanes, B, p.count, p.ips, p.parts, w.partial, st), "fold launch");
   HIP_TRY(launch_reduce(w.ediag, w.partial, B, p.count, p.fold, p.lgp, eloc, st), "reduce launch");
   return ELOCAL_OK;
 }

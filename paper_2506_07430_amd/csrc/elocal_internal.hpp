@@ -390,4 +390,29 @@ __device__ __forceinline__ double sample_terms(const SysDev& S, const uint64_t (
   return e;
 }
 
+// a + b of two lanes' values exchanged by one of the vector unit's own lane moves (through LDS,
+// __shfl_xor, the sums of a group of 64 entries took 8% of the narrowest networks' time).
+template <int CTRL>   // data-parallel-primitive control: rotation within rows of 16 lanes
+__device__ __forceinline__ double add_rotated(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xF, 0xF, false);
+  return v + __hiloint2double(hi, lo);
+}
+// Sum over the wave's lanes in a fixed order (halves first): of the real parts in lanes 0..31,
+// of the imaginary parts in lanes 32..63.
+__device__ __forceinline__ double wave_sum_complex(double re, double im) {
+  // the swaps exchange the upper half of the first operand with the lower half of the second,
+  // and odd rows of the first with even rows of the second
+  const auto h0 = __builtin_amdgcn_permlane32_swap(__double2loint(re), __double2loint(im), false, false);
+  const auto h1 = __builtin_amdgcn_permlane32_swap(__double2hiint(re), __double2hiint(im), false, false);
+  double v = __hiloint2double(h1[0], h0[0]) + __hiloint2double(h1[1], h0[1]);
+  const auto r0 = __builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v), false, false);
+  const auto r1 = __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v), false, false);
+  v = __hiloint2double(r1[0], r0[0]) + __hiloint2double(r1[1], r0[1]);
+  v = add_rotated<0x128>(v);   // row_ror:8, then 4, 2, 1: what is left has that period
+  v = add_rotated<0x124>(v);
+  v = add_rotated<0x122>(v);
+  return add_rotated<0x121>(v);
+}
+
 }  // namespace elocal

@@ -52,6 +52,29 @@ __global__ void __launch_bounds__(256) k_reduce(const double* __restrict__ ediag
   }
 }
 
+// One wave per item (see launch_fold_items).
+__global__ void __launch_bounds__(256) k_fold_items(const double2* __restrict__ lanes, int64_t n_items, uint32_t ips,
+                                                    uint32_t parts, uint32_t parts_per_item,
+                                                    double2* __restrict__ partial) {
+  const int64_t item = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  if (item >= n_items) return;
+  const int64_t b = item / ips;
+  const uint32_t p0 = (uint32_t)(item % ips) * parts_per_item, p1 = min(parts, p0 + parts_per_item);
+  double re = 0.0, im = 0.0;
+  for (uint32_t p = p0; p < p1; ++p) {
+    const double2 v = lanes[((size_t)b * parts + p) * 64 + lane];
+    re += v.x;
+    im += v.y;
+  }
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) {
+    re += __shfl_xor(re, off);
+    im += __shfl_xor(im, off);
+  }
+  if (lane == 0) partial[item] = make_double2(re, im);
+}
+
 // One block of 1024 threads: strided per-thread sums, then a fixed LDS tree.
 __global__ void __launch_bounds__(1024) k_stats(const double* __restrict__ eloc,
                                                 const double* __restrict__ w, int64_t B,
@@ -391,6 +414,15 @@ hipError_t launch_store_bytes(const void* src, size_t bytes, void* dst, hipStrea
     words -= cnt;
   }
   return hipSuccess;
+}
+
+hipError_t launch_fold_items(const double* lanes, int64_t B, uint32_t ips, uint32_t parts, uint32_t parts_per_item,
+                             double* partial, hipStream_t st) {
+  const int64_t n_items = B * ips;
+  if (n_items <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_fold_items, dim3((unsigned)((n_items + 3) / 4)), dim3(256), 0, st, (const double2*)lanes,
+                     n_items, ips, parts, parts_per_item, (double2*)partial);
+  return hipGetLastError();
 }
 
 hipError_t launch_reduce(const double* ediag, const double* partial, int64_t B, uint32_t count, uint32_t fold, int lgp,

@@ -35,6 +35,7 @@ struct EvalArgs {
   int64_t n_items;
   uint32_t ips;            // work items per sample
   uint32_t tpi;            // row tiles per work item
+  int lane_sums;           // BF16: an item is a part, and partial holds its 64 lanes' sums
   uint32_t lds_bias_off;   // byte offset of the biases in LDS (staged weights from 0)
   uint32_t lds_ctx_off;    // byte offset of the per-wave contexts
   uint32_t lds_lut_off;    // byte offset of the input-expansion table
@@ -166,6 +167,10 @@ hipError_t launch_rows_f64(const RowsArgs& A, int hmax, hipStream_t st);
 // the caller checks that the network allows it)
 hipError_t launch_eval_f64(const EvalArgs& A, int hmax, bool inplace, unsigned grid, hipStream_t st);
 
+// partial[item] = sum of the lanes' sums of its parts (parts_per_item of them, fewer in a
+// sample's last item), in the order in which one wave adds them.
+hipError_t launch_fold_items(const double* lanes, int64_t B, uint32_t ips, uint32_t parts, uint32_t parts_per_item,
+                             double* partial, hipStream_t st);
 // Local energies: eloc[b] = ediag[b] + sum of the sample's count * 2^lgp partial sums.
 hipError_t launch_reduce(const double* ediag, const double* partial, int64_t B, uint32_t count, uint32_t fold, int lgp,
                          double* eloc, hipStream_t st);

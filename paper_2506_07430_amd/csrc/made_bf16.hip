@@ -767,6 +767,10 @@ __device__ __forceinline__ void eval_item_bf16(const EvalArgs& P, const int32_t*
       acc_im += r.y;
     }
   }
+  if (P.lane_sums) {   // a part of an item: k_fold_items goes on from the lanes' sums
+    ((double2*)P.partial)[item * 64 + lane] = make_double2(acc_re, acc_im);
+    return;
+  }
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) {
     acc_re += __shfl_xor(acc_re, off);

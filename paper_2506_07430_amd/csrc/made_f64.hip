@@ -11,6 +11,7 @@
 // 16-unit blocks of the previous layer; the rest of its weights are masked).
 #include "elocal_internal.hpp"
 #include "kernels.hpp"
+#include "made_f64.hpp"
 
 namespace elocal {
 
@@ -339,19 +340,22 @@ __global__ void __launch_bounds__(256) k_rows_f64(RowsArgs P) {
 
 struct WaveCtx64 {
   SampleCtx c;
-  double lpx[kMaxOrb];
 };
 
 template <int NW>
 struct SampleState64 {
   int64_t b;
   uint64_t xs[NW];
-  double sig_x, ed;
+  double sig_x, ed, sfx;   // sfx: the sample's log p summed from this lane's orbital on
   const double* Fs;
 };
 
-// One work item = one sample and P.tpi tiles of 16 list entries; the 64 lanes of a tile
-// share its 16 rows (lane group g holds output units 4g..4g+3 of each 16-unit block).
+// One work item = one sample and P.tpi tiles of 16 list entries, in groups of 64: every lane
+// generates one entry; the network runs on the group's tiles in turn (lane group g holds output
+// units 4g..4g+3 of each 16-unit block), from the output block of a tile's first changed
+// orbital on; every lane then forms the term of its own entry. With a tile's entries generated,
+// and its terms formed, by all four lane groups at once the smallest networks were bound by
+// that: 8 orbitals, width 32, 1024 samples 110 us, 78 us.
 template <int HMAX, int NW, bool INPLACE = false, bool OUT_LDS = false>
 __device__ __forceinline__ void eval_item_f64(const EvalArgs& P, const double* __restrict__ WL, WaveCtx64& wc,
                                               int64_t item, SampleState64<NW>& st, int lane) {
@@ -367,7 +371,13 @@ __device__ __forceinline__ void eval_item_f64(const EvalArgs& P, const double* _
 #pragma unroll
     for (int w = 0; w < NW; ++w) st.xs[w] = P.x[b * NW + w];
     build_ctx<NW>(S, st.xs, wc.c, lane);
-    if (lane < n) wc.lpx[lane] = P.lpx64[b * n + lane];
+    double v = lane < n ? P.lpx64[b * n + lane] : 0.0;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const double u = __shfl_down(v, off);
+      if (lane + off < 64) v += u;
+    }
+    st.sfx = v;
     wave_sync_lds64();
     st.sig_x = 1.0 / (1.0 + exp(-P.zphi[b]));
     st.ed = P.ediag[b];
@@ -375,59 +385,64 @@ __device__ __forceinline__ void eval_item_f64(const EvalArgs& P, const double* _
     st.b = b;
   }
   const uint64_t(&xs)[NW] = st.xs;
-  double acc_re = 0.0, acc_im = 0.0;
-  for (uint32_t tile = 0; tile < P.tpi; ++tile) {
-    const uint32_t t0 = 1u + (seg * P.tpi + tile) * 16u;
-    if (t0 >= S.C) break;
-    const uint32_t t = t0 + r16;
-    uint64_t xp[NW];
+  const uint32_t first = 1u + seg * P.tpi * 16u, end = min(S.C, first + P.tpi * 16u);
+  double total = 0.0;   // lanes 0..31 the real part, lanes 32..63 the imaginary part
+  for (uint32_t t0 = first; t0 < end; t0 += 64u) {
+    const uint32_t t = t0 + lane;
+    uint64_t xo[NW];
     double hv = 0.0;
-    if (t < S.C) {
+    if (t < end) {
       const Excitation e = unrank(S, wc.c, t);
-      const int sg = apply_excitation<NW>(xs, e, xp);
-      if (g == 0) {
-        const double v = excitation_value(S, e, st.Fs, st.ed);
-        hv = sg < 0 ? -v : v;
-      }
+      const int sg = apply_excitation<NW>(xs, e, xo);
+      const double v = excitation_value(S, e, st.Fs, st.ed);
+      hv = sg < 0 ? -v : v;
     } else {
 #pragma unroll
-      for (int w = 0; w < NW; ++w) xp[w] = xs[w];
+      for (int w = 0; w < NW; ++w) xo[w] = xs[w];
     }
-    const int p0 = first_diff_orbital<NW>(xs, xp, n);
-    double dA = 0.0, zp = 0.0;
-    mlp_f64<HMAX, NW, false, INPLACE, OUT_LDS>(M, WL, xp, lane, [&](int ob, const f64x4& a) {
-      const int p = 4 * ob + g;
-      if (p < n && p >= p0) dA += cond_logp64<NW>(xp, p, n, na, nb, a) - wc.lpx[p];
-      if (ob == ob_phi && g == g_phi) zp = a[0];
-    });
-    dA += __shfl_xor(dA, 16);
-    dA += __shfl_xor(dA, 32);
-    zp = __shfl(zp, g_phi * 16 + r16);
-    if (g == 0) {
-      const double dphi = 2.0 * M_PI * (1.0 / (1.0 + exp(-zp)) - st.sig_x);
-      double sn, cs;
-      sincos(dphi, &sn, &cs);
-      const double mag = hv * exp(0.5 * dA);
-      acc_re += mag * cs;
-      acc_im += mag * sn;
-    }
-  }
+    const int p0o = first_diff_orbital<NW>(xs, xo, n);
+    const double sfx_own = __shfl(st.sfx, min(p0o, 63));
+    const int p0_row = row_min(p0o);
+    double dA_own = 0.0, zp_own = 0.0;
+#pragma unroll 1
+    for (int h = 0; h < 4 && t0 + 16u * h < end; ++h) {
+      uint64_t xr[NW];
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    acc_re += __shfl_xor(acc_re, off);
-    acc_im += __shfl_xor(acc_im, off);
+      for (int w = 0; w < NW; ++w) xr[w] = __shfl(xo[w], 16 * h + r16);
+      const int p0 = __shfl(p0o, 16 * h + r16);
+      const int ob0 = sgpr(min(__builtin_amdgcn_readlane(p0_row, 16 * h) >> 2, ob_phi));
+      RowCursor<NW> rc = cursor_at<NW>(xr, min(4 * ob0 + g, n - 1));
+      double dA = 0.0, zp = 0.0;
+      mlp_f64<HMAX, NW, false, INPLACE, OUT_LDS>(M, WL, xr, lane, [&](int ob, const f64x4& a) {
+        const int p = 4 * ob + g;
+        if (p < n) {
+          const int left = n - p - 1;
+          const double lp = cond_step64<NW>(rc, na - left, nb - left, na, nb, a);
+          if (p >= p0) dA += lp;
+        }
+        if (ob == ob_phi && g == g_phi) zp = a[0];
+      }, ob0);
+      dA += __shfl_xor(dA, 16);
+      dA += __shfl_xor(dA, 32);
+      zp = __shfl(zp, g_phi * 16 + r16);
+      if (g == h) {
+        dA_own = dA - (p0o < n ? sfx_own : 0.0);
+        zp_own = zp;
+      }
+    }
+    double2 r = make_double2(0.0, 0.0);
+    if (hv != 0.0) r = ratio_term64(hv, zp_own, st.sig_x, dA_own);
+    // group by group, so that the sum does not depend on how many groups an item has
+    total += wave_sum_complex(r.x, r.y);
   }
-  if (lane == 0) {
-    P.partial[2 * item] = acc_re;
-    P.partial[2 * item + 1] = acc_im;
-  }
+  if ((lane & 31) == 0) P.partial[2 * item + (lane >> 5)] = total;
 }
 
 // With LDSO the output layer's packed weights are first copied to LDS (dynamic shared
 // memory of nob[L] * nk[L] fragments). The in-place variant is built for two waves per
 // SIMD (256 registers per lane).
 template <int HMAX, int NW, bool LDSO, bool INPLACE>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(INPLACE ? 2 : 1)))
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(HMAX == 32 ? 4 : INPLACE ? 2 : 1)))
 k_eval_f64(EvalArgs P) {
   __shared__ WaveCtx64 ctxs[4];
   extern __shared__ __attribute__((aligned(16))) double wout[];

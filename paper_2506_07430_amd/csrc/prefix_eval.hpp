@@ -54,10 +54,7 @@ struct PrefixSample {
 // 2^k waves each run every 2^k-th of its groups.
 __device__ __forceinline__ void add_to_slot(double re, double im, uint32_t slot, int lane0, double& sum) {
   const int lane = opaque(lane0);
-  const bool lo = lane < 32;
-  double v = (lo ? re : im) + __shfl_xor(lo ? im : re, 32);
-#pragma unroll
-  for (int off = 16; off >= 1; off >>= 1) v += __shfl_xor(v, off);
+  const double v = wave_sum_complex(re, im);
   sum += (uint32_t)(lane & 31) == (slot & 31u) ? v : 0.0;
 }
 

@@ -13,6 +13,7 @@
 // input bits 16 kb .. 16 kb + 15. The output layer has 4(n - 1) logits and the phase row.
 #include <algorithm>
 
+#include "made_f64.hpp"
 #include "prefix_eval.hpp"
 
 namespace elocal {
@@ -60,15 +61,6 @@ __global__ void k_pack_prefix_f64(MadeDev M, ThetaLayout T, const double* __rest
   }
 }
 
-// H exp(dA / 2 + i 2 pi (sigmoid(zp) - sig_x)); dA in natural-log units.
-static __device__ __attribute__((noinline)) double2 ratio_term64(double hv, double zp, double sig_x, double dA) {
-  const double dphi = 2.0 * M_PI * (1.0 / (1.0 + exp(-zp)) - sig_x);
-  double sn, cs;
-  sincos(dphi, &sn, &cs);
-  const double mag = hv * exp(0.5 * dA);
-  return make_double2(mag * cs, mag * sn);
-}
-
 struct NetF64 {
   typedef double Real;
   typedef f64x4 Acc;
@@ -82,22 +74,9 @@ struct NetF64 {
     return ratio_term64(hv, zp, sig_x, dA);
   }
 
-  // log p_p(s_p) of the row at the cursor's orbital (the softmax over the reachable
-  // occupations, shifted by their largest logit), then four orbitals on. The largest term of
-  // the sum is 1, so three exponentials are left, without a branch per occupation.
   template <int NW>
   static __device__ __forceinline__ double step(RowCursor<NW>& rc, int ta, int tb, int na, int nb, const f64x4& z) {
-    const uint32_t b8 = (uint32_t)rc.bits[0] & 0xFFu;
-    const bool a_must = rc.cu < ta, a_may = rc.cu < na, b_must = rc.cd < tb, b_may = rc.cd < nb;
-    const double y0 = !a_must && !b_must ? z[0] : -INFINITY, y1 = a_may && !b_must ? z[1] : -INFINITY;
-    const double y2 = !a_must && b_may ? z[2] : -INFINITY, y3 = a_may && b_may ? z[3] : -INFINITY;
-    const double h0 = fmax(y0, y1), l0 = fmin(y0, y1), h1 = fmax(y2, y3), l1 = fmin(y2, y3);
-    const double m = fmax(h0, h1);
-    const double sum = 1.0 + exp(fmin(h0, h1) - m) + (exp(l0 - m) + exp(l1 - m));
-    const double z01 = (b8 & 1u) ? z[1] : z[0], z23 = (b8 & 1u) ? z[3] : z[2];
-    const double zs = (b8 & 2u) ? z23 : z01;
-    cursor_advance4<NW>(rc, b8);
-    return zs - m - log(sum);
+    return cond_step64<NW>(rc, ta, tb, na, nb, z);
   }
 
   static __device__ __forceinline__ f64x4 load32(const __amdgpu_buffer_rsrc_t& r, uint32_t voff, uint32_t soff) {

@@ -178,8 +178,8 @@ elocal_status elocal_eval(elocal_t h, elocal_stream s, const elocal_ansatz* a,
  * array of ELOCAL_NOALLOC_SCRATCH_MIB MiB in device memory, one per GPU, that the library
  * holds from the first elocal_create on that GPU until the process ends. The call allocates
  * nothing. Fails with ELOCAL_E_WORKSPACE when the batch needs more scratch than that
- * (elocal_workspace_bytes(h, a, B, ELOCAL_OP_EVAL) tells how much; e.g. 60 orbitals with
- * 1024 samples need about 52 MB). Every call on one GPU shares that GPU's array, and
+ * (elocal_workspace_bytes(h, a, B, ELOCAL_OP_EVAL) tells how much), and runs a batch in parts
+ * where that leaves room for more blocks' scratch. Every call on one GPU shares that GPU's array, and
  * nothing in it needs to start at zero: calls that overlap on one GPU (on different
  * streams, or from different threads) race and must be serialised by the caller.
  */

@@ -453,9 +453,12 @@ void pad_prefix(AnsatzGeom& G) {
 // Scratch of one wave: as many parents per segment as fit, at most a tile of 16. Early
 // parents have more boundaries below them (13.9 KB each at 60 orbitals, 3 x 256; 0.5 KB in
 // the last class) and more entries to amortise a partly filled tile.
-// (FP64 values are twice as long.)
+// (FP64 values are twice as long.) Measured: width 256, 60 orbitals BF16 20 KB 34.6 ms, 32 KB
+// 32.4, 48 KB 30.8, 64 KB 30.5 (and 40 orbitals 26.9, 24.1, 22.5, 22.1), FP64 40, 64, 96 KB
+// 31.3, 29.7, 30.0; width 128, 24 orbitals BF16 9, 18, 24, 32 KB 10.9, 10.1, 10.1, 10.2 ms.
 size_t prefix_scratch_bytes(const AnsatzGeom& G) {
-  return (G.hmax >= 256 ? 32 : G.hmax >= 128 ? 18 : 8) * 1024 * (G.precision == ELOCAL_BF16 ? 1 : 2);
+  const bool bf = G.precision == ELOCAL_BF16;
+  return (G.hmax >= 256 ? (bf ? 48 : 64) : (G.hmax >= 128 ? 18 : 8) * (bf ? 1 : 2)) * 1024;
 }
 
 void plan_prefix(const elocal_ctx* h, const AnsatzGeom& G, PrefixDev& X) {
@@ -1113,7 +1116,33 @@ elocal_status elocal_eval_noalloc(elocal_t h, elocal_stream s, const elocal_ansa
                 "elocal_eval_noalloc needs %zu bytes of scratch for B=%lld, above its fixed %zu bytes "
                 "(ELOCAL_NOALLOC_SCRATCH_MIB); use elocal_eval with a caller workspace or a smaller batch",
                 need, (long long)B, kNoAllocScratchBytes);
-  return elocal_eval(h, s, a, x, B, ws, kNoAllocScratchBytes, eloc, logpsi);
+  // Where a batch's arrays leave room for the checkpoints of few blocks only, it is run in up
+  // to eight parts (60 orbitals, 1024 samples: 395 ms, 242 with a workspace for every block of the
+  // chip, 577 without sharing prefixes). A sample's energy does not depend on its batch.
+  auto blocks = [&](int64_t b) {
+    EvalPlan p = plan_eval(h, G, b);
+    shrink_grid(h, G, b, kNoAllocScratchBytes, p);
+    return p.grid;
+  };
+  int64_t part = B;
+  if (G.prefix && B > 0) {
+    unsigned best = blocks(B);
+    for (int k = 2; k <= 8 && B / k >= 64; ++k) {
+      const int64_t b = (B + k - 1) / k;
+      if (blocks(b) * 8u > best * 9u && eval_need(h, G, b, plan_eval(h, G, b)) <= kNoAllocScratchBytes) {
+        best = blocks(b);
+        part = b;
+      }
+    }
+  }
+  if (part >= B) return elocal_eval(h, s, a, x, B, ws, kNoAllocScratchBytes, eloc, logpsi);
+  if (!x || !eloc) return fail(ELOCAL_E_INVALID, "null pointer argument");
+  for (int64_t b0 = 0; b0 < B; b0 += part) {
+    const elocal_status e = elocal_eval(h, s, a, x + b0 * h->sys.W, std::min(part, B - b0), ws, kNoAllocScratchBytes,
+                                        eloc + 2 * b0, logpsi ? logpsi + 2 * b0 : nullptr);
+    if (e != ELOCAL_OK) return e;
+  }
+  return ELOCAL_OK;
 }
 
 namespace {

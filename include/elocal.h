@@ -364,7 +364,8 @@ elocal_status elocal_kernel_timing(elocal_t h, double* total_ms, int64_t* launch
  * of its first handle (and each system's groups per item from its own handle).
  *   ELOCAL_TUNE_GRID:   blocks of the persistent grid-stride loop over work items.
  *   ELOCAL_TUNE_GROUPS: list-entry groups per work item (64 entries per group in BF16
- *                       mode, 16 in FP64 mode).
+ *                       mode, 16 in FP64 mode); with the prefix-shared evaluation,
+ *                       segments (tiles of up to 16 parents and their entries).
  *   ELOCAL_TUNE_WAVES:  waves per block of the BF16 kernels (at most what the kernel
  *                       variant is built for; ELOCAL_INFO_MAX_WAVES tells).
  *   ELOCAL_TUNE_COLS:   16-row tiles per network pass of the BF16 kernels: 1 or 2 (each

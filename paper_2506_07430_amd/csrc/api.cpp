@@ -620,7 +620,7 @@ EvalPlan plan_eval(const elocal_ctx* h, const AnsatzGeom& G, int64_t B, int64_t 
   p.fold = 1;
   p.lgp = 0;
   // A batch with few items has parts of items instead: an item's groups are run one after the
-  // other (8 orbitals, four batches of 4 to 43 samples in one launch: 198 us, 71 us so). The sums
+  // other (8 and 9 orbitals, four batches of 4 to 43 samples in one launch: 198 us, 37 us so). The sums
   // are the same: FP64 items add their groups of 64 one by one, and the reduction folds the
   // parts in that order; BF16 parts leave their lanes' sums (adding every group over the lanes
   // cost the narrowest networks 2 to 9%), which a kernel of their own adds.

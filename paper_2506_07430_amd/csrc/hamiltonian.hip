@@ -39,7 +39,8 @@ __device__ __forceinline__ void load_x(const uint64_t* __restrict__ x, int64_t b
 
 // `parts` waves per sample (per-sample terms: see sample_terms in elocal_internal.hpp). A wave's
 // singles are a chain of dependent table reads, so a small batch is bound by their latency
-// (60 orbitals, 32 samples, one wave each: 494 us); the launcher splits it over more waves.
+// (60 orbitals, 32 samples, one wave each: 494 us); the launcher splits it over more waves
+// (35 us).
 template <int NW>
 __global__ void __launch_bounds__(256) k_prep(SysDev S, const uint64_t* __restrict__ x, int64_t B, int parts,
                                               double* __restrict__ ediag, double* __restrict__ F) {

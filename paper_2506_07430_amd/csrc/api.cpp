@@ -723,7 +723,7 @@ struct EvalWs {
   double* zphi;
   double* partial;
   double* lanes;     // BF16 parts of items: their lanes' sums
-  uint32_t* queue;   // prefix-shared evaluation: the work-item ticket and the checkpoints
+  Ticket* queue;     // prefix-shared evaluation: the work-item ticket and the checkpoints
   float* scratch;
   void* pfrag;       // FP64 prefix-shared evaluation: its own packing of the network
   double* pbias;
@@ -752,7 +752,7 @@ EvalWs carve_eval(const elocal_ctx* h, const AnsatzGeom& G, const EvalPlan& p, i
   w.queue = nullptr;
   w.scratch = nullptr;
   if (p.prefix) {
-    w.queue = c.take<uint32_t>(1);
+    w.queue = c.take<Ticket>(1);
     if (G.precision == ELOCAL_FP64) {
       w.pfrag = c.take<char>(G.pwbytes);
       w.pbias = c.take<double>(G.pbbytes / 8);

@@ -402,7 +402,7 @@ __global__ void __launch_bounds__(64 * prefix_waves_bf16(32 * HB, COLS), 1) k_pr
   const typename Net::Sources src = wave_sources<HB, COLS, LMODE>(P, smem, wid, lane, xlut);
   PrefixSample<NW> st;
   st.b = -1;
-  for (int64_t item = next_item(P.px.queue, lane); item < P.n_items; item = next_item(P.px.queue, lane))
+  for (int64_t item; next_item(P.px.queue, P.n_items, lane, item);)
     run_item<Net, HB, HB / 2 + 1, NW>(P, args, src, pw, item, st, lane);
 }
 
@@ -425,8 +425,8 @@ __global__ void __launch_bounds__(64 * prefix_waves_bf16(32 * HB, COLS), 1)
   for (int i = 0; i < n_sys; ++i, s = s + 1 < n_sys ? s + 1 : 0) {
     const EvalArgs& P = args[s];
     // (the barrier: every wave is done with the previous system's weights)
-    const bool left = threadIdx.x == 0 && (int64_t)__hip_atomic_load(P.px.queue, __ATOMIC_RELAXED,
-                                                                      __HIP_MEMORY_SCOPE_AGENT) < P.n_items;
+    const bool left = threadIdx.x == 0 && __hip_atomic_load(P.px.queue, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <
+                                              (Ticket)P.n_items;
     if (!__syncthreads_or(left)) continue;
     stage_prefix<LMODE>(P, smem);
     __syncthreads();
@@ -436,7 +436,7 @@ __global__ void __launch_bounds__(64 * prefix_waves_bf16(32 * HB, COLS), 1)
     // registers than the empty second word)
     PrefixSample<2> st;
     st.b = -1;
-    for (int64_t item = next_item(P.px.queue, lane); item < P.n_items; item = next_item(P.px.queue, lane))
+    for (int64_t item; next_item(P.px.queue, P.n_items, lane, item);)
       run_item<Net, HB, 2, 2>(P, (CArgs*)(uintptr_t)&P, src, pw, item, st, lane);
   }
 }

@@ -377,11 +377,16 @@ __device__ __forceinline__ void run_item(const EvalArgs& P, CArgs* args, const t
   }
 }
 
-// The next work item of the launch (one wave-uniform ticket).
-__device__ __forceinline__ int64_t next_item(uint32_t* queue, int lane) {
-  uint32_t t = 0;
-  if (lane == 0) t = atomicAdd(queue, 1u);
-  return (int64_t)(uint32_t)sgpr((int)t);
+// Takes the next work item of the launch (one wave-uniform ticket); false once all n_items are
+// taken. Every wave's last ticket is past the end, so the counter must not wrap within n_items
+// plus the waves of the grid: it is as wide as the item number (millions of samples of 60
+// orbitals are more than 2^32 items).
+__device__ __forceinline__ bool next_item(Ticket* queue, int64_t n_items, int lane, int64_t& item) {
+  Ticket t = 0;
+  if (lane == 0) t = atomicAdd(queue, (Ticket)1);
+  t = (Ticket)(uint32_t)sgpr((int)(uint32_t)(t >> 32)) << 32 | (uint32_t)sgpr((int)(uint32_t)t);
+  item = (int64_t)t;
+  return t < (Ticket)n_items;
 }
 
 }  // namespace elocal

@@ -1,0 +1,28 @@
+// The planning functions of the library (sizes, launch shapes: host code without a device)
+// behind a C interface. Handles are made by hand, for a chip of 256 compute units.
+#include <limits>
+#include <type_traits>
+
+#include "../paper_2506_07430_amd/csrc/api.cpp"
+
+extern "C" {
+
+elocal_t host_handle(int n, int na, int nb) {
+  elocal_ctx* h = new elocal_ctx();
+  h->sys = build_sys(n, na, nb);
+  return h;
+}
+
+void host_free(elocal_t h) { delete h; }
+
+// Work items of an evaluation, and the largest number that its work-item counter holds.
+int64_t host_items(elocal_t h, const elocal_ansatz* a, int64_t B, unsigned long long* limit, int64_t* waves) {
+  AnsatzGeom G;
+  if (make_eval_geom(h, a, G) != ELOCAL_OK) return -1;
+  const EvalPlan p = plan_eval(h, G, B);
+  *limit = (unsigned long long)std::numeric_limits<std::remove_pointer_t<decltype(p.px.queue)>>::max();
+  *waves = p.prefix ? (int64_t)p.grid * p.waves : 0;
+  return p.n_items;
+}
+
+}  // extern "C"

@@ -1,0 +1,49 @@
+"""Launch planning on the host, for sizes whose evaluation would take a GPU minutes and most of
+its memory: tests/host_plan.hip wraps the library's planning functions (no device needed)."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+from paper_2506_07430_amd import build, elocal
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("host_plan") / "host_plan")
+    src = os.path.join(build.ROOT, "tests", "host_plan.hip")
+    subprocess.run([build.HIPCC, *build.FLAGS, "-w", "-c", src, "-o", out + ".o"], check=True)
+    # (the kernels' launchers, which the planning source refers to, come from the built library)
+    subprocess.run([build.HIPCC, "--offload-arch=gfx950", "-shared", "-Wl,-Bsymbolic", out + ".o", build.LIB,
+                    "-Wl,-rpath," + build.PKG, "-o", out + ".so"], check=True)
+    L = ctypes.CDLL(out + ".so")
+    L.host_handle.restype = ctypes.c_void_p
+    L.host_free.argtypes = [ctypes.c_void_p]
+    for f in ("host_items", "elocal_launch_info", "elocal_tune"):
+        getattr(L, f).restype = ctypes.c_int64
+    L.elocal_workspace_bytes.restype = ctypes.c_size_t
+    return L
+
+
+def ansatz(widths, precision):
+    w = (ctypes.c_int * len(widths))(*widths)
+    return elocal._Ansatz(len(widths), w, precision, None)
+
+
+@pytest.mark.parametrize("n,na,widths,samples,precision", [
+    (60, 26, (256,) * 3, 128, elocal.BF16),
+    (60, 26, (256,) * 3, 5_800_000, elocal.BF16),     # 4.3e9 items in 142 GiB of workspace
+    (60, 26, (256,) * 3, 5_800_000, elocal.FP64),
+    (64, 32, (256,) * 8, 2_400_000, elocal.BF16),
+])
+def test_work_item_counter_does_not_wrap(plan, n, na, widths, samples, precision):
+    """Every wave takes tickets until one is past the last item, so the counter must hold the
+    items and one more ticket per wave: a counter that wraps hands out items for ever."""
+    h = ctypes.c_void_p(plan.host_handle(n, na, na))
+    limit, waves = ctypes.c_ulonglong(), ctypes.c_int64()
+    a = ansatz(widths, precision)
+    items = plan.host_items(h, ctypes.byref(a), ctypes.c_int64(samples), ctypes.byref(limit), ctypes.byref(waves))
+    plan.host_free(h)
+    assert items >= samples and waves.value > 0
+    assert items + waves.value <= limit.value

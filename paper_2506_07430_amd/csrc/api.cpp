@@ -562,6 +562,7 @@ elocal_status make_eval_geom(const elocal_ctx* h, const elocal_ansatz* a, Ansatz
 // see add_to_slot, k_reduce. `chip`: the part of the chip that the batch has to itself.
 constexpr int64_t kFineItems = 131072;   // a few tens of items per wave of the chip
 constexpr int kMaxLgParts = 4;
+constexpr int64_t kMaxTickets = 1ll << 31;
 void plan_items(const elocal_ctx* h, int64_t B, double chip, EvalPlan& p) {
   PrefixDev& X = p.px;
   const uint32_t nseg = X.seg0[X.nblk];
@@ -600,6 +601,11 @@ void plan_items(const elocal_ctx* h, int64_t B, double chip, EvalPlan& p) {
   }
   p.lgp = X.lgp;
   p.n_items = (int64_t)p.ips * B;
+  // one ticket per item, or per several where there are more than 32-bit tickets (60 orbitals,
+  // 5.8 million samples: 4.3e9 items)
+  const int64_t shares = std::max<int64_t>(1, (p.n_items + kMaxTickets - 1) / kMaxTickets);
+  X.bt = (uint32_t)((B + shares - 1) / shares);
+  X.tickets = p.ips * X.bt;
   p.tpi = std::max(1u, X.spi);
 }
 
@@ -723,7 +729,7 @@ struct EvalWs {
   double* zphi;
   double* partial;
   double* lanes;     // BF16 parts of items: their lanes' sums
-  Ticket* queue;     // prefix-shared evaluation: the work-item ticket and the checkpoints
+  uint32_t* queue;   // prefix-shared evaluation: the work-item ticket and the checkpoints
   float* scratch;
   void* pfrag;       // FP64 prefix-shared evaluation: its own packing of the network
   double* pbias;
@@ -752,7 +758,7 @@ EvalWs carve_eval(const elocal_ctx* h, const AnsatzGeom& G, const EvalPlan& p, i
   w.queue = nullptr;
   w.scratch = nullptr;
   if (p.prefix) {
-    w.queue = c.take<Ticket>(1);
+    w.queue = c.take<uint32_t>(1);
     if (G.precision == ELOCAL_FP64) {
       w.pfrag = c.take<char>(G.pwbytes);
       w.pbias = c.take<double>(G.pbbytes / 8);

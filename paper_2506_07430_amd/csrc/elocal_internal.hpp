@@ -111,7 +111,6 @@ struct PrefixLayer {
   int fend, tend;    // fragment offset past the layer's last o-block, in the packing and in LDS
   int pad[3];
 };
-typedef unsigned long long Ticket;   // number of a work item (see next_item)
 struct PrefixDev {
   int nblk;                          // classes = hidden width / unit; 0: path not used
   int extra;                         // BF16: 1 if the first o-block of a hidden pair j reads j + 2 blocks
@@ -129,7 +128,8 @@ struct PrefixDev {
   int lgp;                           //   the largest lgk: every segment has 2^lgp partial sums
   float* scratch;                    // checkpoints, `stride` floats per wave of the grid
   uint32_t stride;
-  Ticket* queue;                     // next work item (zeroed by the packing kernel)
+  uint32_t* queue;                   // next ticket (zeroed by the packing kernel); one ticket is work
+  uint32_t tickets, bt;              //   item `part` of samples b, b + bt, ...: ips * bt tickets
   uint32_t block0;                   // several systems: the first block that starts with this one
 };
 

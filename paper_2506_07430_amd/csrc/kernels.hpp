@@ -80,7 +80,7 @@ hipError_t launch_check(const SysDev& S, const uint64_t* x, int64_t B, unsigned 
 // fused evaluation; `hmax` is the padded hidden width class (32, 64, 128, 256).
 // (queue, where not null, is set to 0)
 hipError_t launch_pack_bf16(const MadeDev& M, const ThetaLayout& T, const uint16_t* theta,
-                            void* frag, float* bias, Ticket* queue, hipStream_t st);
+                            void* frag, float* bias, uint32_t* queue, hipStream_t st);
 hipError_t launch_rows_bf16(const RowsArgs& A, int hmax, int nterms, hipStream_t st);
 hipError_t launch_eval_bf16(const EvalArgs& A, int hmax, int nterms, int cols, bool lds_weights, bool inplace,
                             size_t lds_bytes, unsigned grid, int waves, hipStream_t st);
@@ -130,7 +130,7 @@ constexpr size_t kPrefixWaveBytes = 3840;   // LDS state of one wave (PrefixWave
 // FP64: 8 waves per block (two per SIMD, 256 registers each), weights from global memory.
 constexpr int kPrefixWavesF64 = 8;
 hipError_t launch_pack_prefix_f64(const MadeDev& M, const ThetaLayout& T, const double* theta, void* frag,
-                                  double* bias, Ticket* queue, hipStream_t st);
+                                  double* bias, uint32_t* queue, hipStream_t st);
 hipError_t launch_prefix_f64(const EvalArgs& A, int hmax, unsigned grid, hipStream_t st);
 hipError_t launch_prefix_multi_f64(const EvalArgs* args, int n_sys, int hmax, unsigned grid, hipStream_t st);
 #define ELOCAL_PREFIX_DECL(name)                                                                                    \

@@ -61,9 +61,9 @@ __device__ __forceinline__ unsigned short f16_bits_of_bf16(unsigned short b) {
 // fragments (only the k-blocks each o-block uses) with hidden units in degree order, masked
 // entries zeroed; biases to FP32.
 __global__ void k_pack_bf16(MadeDev M, ThetaLayout T, const uint16_t* __restrict__ theta,
-                            h16x8* __restrict__ frag, float* __restrict__ bias, Ticket* __restrict__ queue) {
+                            h16x8* __restrict__ frag, float* __restrict__ bias, uint32_t* __restrict__ queue) {
   const uint32_t gid = blockIdx.x * blockDim.x + threadIdx.x;
-  if (queue && gid == 0) *queue = 0;
+  if (queue && gid == 0) *queue = 0u;
   const int n = M.n, L = M.L;
   if (gid < M.nfrag * 64u) {
     const int32_t f = (int32_t)(gid >> 6);
@@ -883,7 +883,7 @@ __global__ void __launch_bounds__(64 * eval_waves_bf16(HMAX, NT, NC), 1)
 
 // ----------------------------------------------------------------------------- launchers
 hipError_t launch_pack_bf16(const MadeDev& M, const ThetaLayout& T, const uint16_t* theta,
-                            void* frag, float* bias, Ticket* queue, hipStream_t st) {
+                            void* frag, float* bias, uint32_t* queue, hipStream_t st) {
   const uint32_t total = M.nfrag * 64u > M.nbias ? M.nfrag * 64u : M.nbias;
   hipLaunchKernelGGL(k_pack_bf16, dim3((total + 255) / 256), dim3(256), 0, st, M, T, theta,
                      (h16x8*)frag, bias, queue);

@@ -402,8 +402,8 @@ __global__ void __launch_bounds__(64 * prefix_waves_bf16(32 * HB, COLS), 1) k_pr
   const typename Net::Sources src = wave_sources<HB, COLS, LMODE>(P, smem, wid, lane, xlut);
   PrefixSample<NW> st;
   st.b = -1;
-  for (int64_t item; next_item(P.px.queue, P.n_items, lane, item);)
-    run_item<Net, HB, HB / 2 + 1, NW>(P, args, src, pw, item, st, lane);
+  for (uint32_t t; next_ticket(P.px, lane, t);)
+    run_item<Net, HB, HB / 2 + 1, NW>(P, args, src, pw, t, st, lane);
 }
 
 // Several systems in one persistent launch: every block goes through the systems in order
@@ -426,7 +426,7 @@ __global__ void __launch_bounds__(64 * prefix_waves_bf16(32 * HB, COLS), 1)
     const EvalArgs& P = args[s];
     // (the barrier: every wave is done with the previous system's weights)
     const bool left = threadIdx.x == 0 && __hip_atomic_load(P.px.queue, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <
-                                              (Ticket)P.n_items;
+                                              P.px.tickets;
     if (!__syncthreads_or(left)) continue;
     stage_prefix<LMODE>(P, smem);
     __syncthreads();
@@ -436,8 +436,8 @@ __global__ void __launch_bounds__(64 * prefix_waves_bf16(32 * HB, COLS), 1)
     // registers than the empty second word)
     PrefixSample<2> st;
     st.b = -1;
-    for (int64_t item; next_item(P.px.queue, P.n_items, lane, item);)
-      run_item<Net, HB, 2, 2>(P, (CArgs*)(uintptr_t)&P, src, pw, item, st, lane);
+    for (uint32_t t; next_ticket(P.px, lane, t);)
+      run_item<Net, HB, 2, 2>(P, (CArgs*)(uintptr_t)&P, src, pw, t, st, lane);
   }
 }
 

@@ -326,67 +326,80 @@ __device__ __forceinline__ void run_segment(const EvalArgs& P, CArgs* args, cons
   }
 }
 
-// One work item: P.px.spi segments of one sample, or (spi = 0) a part of one of them. Its
-// partial sum goes to P.partial.
+// What of a sample its part `part` runs: segments [s0, s1), of every segment the groups
+// k, k + mask + 1, ...
+struct ItemSpan {
+  uint32_t s0, s1, k, mask;
+};
+__device__ __forceinline__ ItemSpan item_span(const EvalArgs& P, uint32_t part) {
+  const uint32_t spi = P.px.spi;
+  if (spi != 0) return {part * spi, min(P.px.seg0[P.px.nblk], part * spi + spi), 0u, 0u};
+  int c = 0;
+  while (c + 1 < P.px.nblk && part >= P.px.item0[c + 1]) ++c;
+  const uint32_t i = part - P.px.item0[c], mask = (1u << P.px.lgk[c]) - 1u, s0 = P.px.seg0[c] + (i >> P.px.lgk[c]);
+  return {s0, s0 + 1u, i & mask, mask};
+}
+
+// One ticket: of one sample (or, in a batch of more work items than tickets, of samples
+// P.px.bt apart) P.px.spi segments, or (spi = 0) a part of one of them. The partial sums go to
+// P.partial.
 template <class Net, int HB, int LO, int NW>
 __device__ __forceinline__ void run_item(const EvalArgs& P, CArgs* args, const typename Net::Sources& src,
-                                         PrefixWave& pw, int64_t item, PrefixSample<NW>& st, int lane) {
+                                         PrefixWave& pw, uint32_t ticket, PrefixSample<NW>& st, int lane) {
   const SysDev& S = P.sys;
   // parts of segments: the same part of every sample in turn, so that the long ones (of the
   // first classes) are run first and the short ones fill the launch's end
-  const uint32_t spi = P.px.spi;
-  const int64_t b = spi == 0 ? item % P.B : item / P.ips;
-  const uint32_t part = (uint32_t)(spi == 0 ? item / P.B : item % P.ips);
-  if (b != st.b) {
-    wave_sync_lds();
+  const uint32_t by = P.px.spi == 0 ? P.px.bt : P.ips, hi = ticket / by, lo = ticket - hi * by;
+  uint32_t part = P.px.spi == 0 ? hi : lo;
+#pragma unroll 1
+  for (int64_t b = P.px.spi == 0 ? lo : hi; b < P.B; b += P.px.bt) {
+    if (b != st.b) {
+      wave_sync_lds();
 #pragma unroll
-    for (int w = 0; w < NW; ++w) st.xs[w] = w < S.W ? P.x[b * S.W + w] : 0ull;
-    st.m = spin_lists<NW>(st.xs, S.n, lane, pw.c);
-    wave_sync_lds();
-    st.sig_x = sigmoid64(P.zphi[b]);
-    st.ed = P.ediag[b];
-    st.Fs = P.F + (size_t)b * (S.nSa + S.nSb);
-    st.b = b;
-  }
-  const uint32_t nseg = P.px.seg0[P.px.nblk];
-  uint32_t s0 = part * spi, s1 = min(nseg, s0 + spi), k = 0, mask = 0;
-  int64_t at = item, end = item + 1;
-  if (spi == 0) {
-    int c = 0;
-    while (c + 1 < P.px.nblk && part >= P.px.item0[c + 1]) ++c;
-    const uint32_t i = part - P.px.item0[c];
-    mask = (1u << P.px.lgk[c]) - 1u;
-    k = i & mask;
-    s0 = P.px.seg0[c] + (i >> P.px.lgk[c]);
-    s1 = s0 + 1;
-    at = ((b * nseg + s0) << P.px.lgp) + k;
-    end = (b * nseg + s1) << P.px.lgp;   // a segment of fewer parts than others: zeros after them
-  }
-  double total = 0.0;
-  for (uint32_t seg = s0; seg < s1; ++seg) {
-    double sum = 0.0;
-    run_segment<Net, HB, LO, NW>(P, args, src, pw, st, (uint32_t)sgpr((int)seg), (uint32_t)sgpr((int)k),
-                                 (uint32_t)sgpr((int)mask), lane, sum);
+      for (int w = 0; w < NW; ++w) st.xs[w] = w < S.W ? P.x[b * S.W + w] : 0ull;
+      st.m = spin_lists<NW>(st.xs, S.n, lane, pw.c);
+      wave_sync_lds();
+      st.sig_x = sigmoid64(P.zphi[b]);
+      st.ed = P.ediag[b];
+      st.Fs = P.F + (size_t)b * (S.nSa + S.nSb);
+      st.b = b;
+    }
+    double total = 0.0;
+    {
+      const ItemSpan it = item_span(P, part);
+      for (uint32_t seg = it.s0; seg < it.s1; ++seg) {
+        double sum = 0.0;
+        run_segment<Net, HB, LO, NW>(P, args, src, pw, st, (uint32_t)sgpr((int)seg), (uint32_t)sgpr((int)it.k),
+                                     (uint32_t)sgpr((int)it.mask), lane, sum);
 #pragma unroll
-    for (int off = 16; off >= 1; off >>= 1) sum += __shfl_xor(sum, off);
-    total += sum;
-  }
-  for (; at < end; at += mask + 1) {
-    if ((lane & 31) == 0) P.partial[2 * at + (lane >> 5)] = total;
-    total = 0.0;
+        for (int off = 16; off >= 1; off >>= 1) sum += __shfl_xor(sum, off);
+        total += sum;
+      }
+    }
+    // (derived again: held across the segments, the 64-bit positions cost registers)
+    part = (uint32_t)sgpr((int)part);
+    asm volatile("" : "+s"(part));
+    const ItemSpan it = item_span(P, part);
+    int64_t at = st.b * P.ips + part, end = at + 1;
+    if (P.px.spi == 0) {
+      const int64_t seg = st.b * P.px.seg0[P.px.nblk] + it.s0;
+      at = (seg << P.px.lgp) + it.k;
+      end = (seg + 1) << P.px.lgp;   // a segment of fewer parts than others: zeros after them
+    }
+    for (; at < end; at += it.mask + 1) {
+      if ((lane & 31) == 0) P.partial[2 * at + (lane >> 5)] = total;
+      total = 0.0;
+    }
   }
 }
 
-// Takes the next work item of the launch (one wave-uniform ticket); false once all n_items are
-// taken. Every wave's last ticket is past the end, so the counter must not wrap within n_items
-// plus the waves of the grid: it is as wide as the item number (millions of samples of 60
-// orbitals are more than 2^32 items).
-__device__ __forceinline__ bool next_item(Ticket* queue, int64_t n_items, int lane, int64_t& item) {
-  Ticket t = 0;
-  if (lane == 0) t = atomicAdd(queue, (Ticket)1);
-  t = (Ticket)(uint32_t)sgpr((int)(uint32_t)(t >> 32)) << 32 | (uint32_t)sgpr((int)(uint32_t)t);
-  item = (int64_t)t;
-  return t < (Ticket)n_items;
+// Takes the launch's next ticket (wave-uniform); false once all are taken. Every wave's last
+// ticket is past the end: the host keeps their number and the waves of the grid below 2^32.
+__device__ __forceinline__ bool next_ticket(const PrefixDev& X, int lane, uint32_t& t) {
+  t = 0;
+  if (lane == 0) t = atomicAdd(X.queue, 1u);
+  t = (uint32_t)sgpr((int)t);
+  return t < X.tickets;
 }
 
 }  // namespace elocal

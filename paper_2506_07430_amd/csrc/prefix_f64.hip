@@ -19,10 +19,10 @@
 namespace elocal {
 
 __global__ void k_pack_prefix_f64(MadeDev M, ThetaLayout T, const double* __restrict__ theta, double* __restrict__ frag,
-                                  double* __restrict__ bias, Ticket* __restrict__ queue) {
+                                  double* __restrict__ bias, uint32_t* __restrict__ queue) {
   const uint32_t gid = blockIdx.x * blockDim.x + threadIdx.x;
   const int n = M.n, L = M.L, nm1 = n - 1;
-  if (gid == 0) *queue = 0;
+  if (gid == 0) *queue = 0u;
   if (gid < M.nfrag * 64u) {
     const uint32_t f = gid >> 6;
     const int lane = gid & 63, rho = lane & 15, g = lane >> 4;
@@ -308,8 +308,8 @@ __global__ void __launch_bounds__(64 * kPrefixWavesF64, 1) k_prefix_f64(EvalArgs
   const NetF64::Sources src = wave_sources_f64(P, wid);
   PrefixSample<NW> st;
   st.b = -1;
-  for (int64_t item; next_item(P.px.queue, P.n_items, lane, item);)
-    run_item<NetF64, HB, HB / 2 + 1, NW>(P, args, src, pw, item, st, lane);
+  for (uint32_t t; next_ticket(P.px, lane, t);)
+    run_item<NetF64, HB, HB / 2 + 1, NW>(P, args, src, pw, t, st, lane);
 }
 
 template <int HB>
@@ -323,13 +323,13 @@ __global__ void __launch_bounds__(64 * kPrefixWavesF64, 1)
     const NetF64::Sources src = wave_sources_f64(P, wid);
     PrefixSample<2> st;
     st.b = -1;
-    for (int64_t item; next_item(P.px.queue, P.n_items, lane, item);)
-      run_item<NetF64, HB, 2, 2>(P, (CArgs*)(uintptr_t)&P, src, pw, item, st, lane);
+    for (uint32_t t; next_ticket(P.px, lane, t);)
+      run_item<NetF64, HB, 2, 2>(P, (CArgs*)(uintptr_t)&P, src, pw, t, st, lane);
   }
 }
 
 hipError_t launch_pack_prefix_f64(const MadeDev& M, const ThetaLayout& T, const double* theta, void* frag,
-                                  double* bias, Ticket* queue, hipStream_t st) {
+                                  double* bias, uint32_t* queue, hipStream_t st) {
   const uint32_t total = std::max(M.nfrag * 64u, M.nbias);
   hipLaunchKernelGGL(k_pack_prefix_f64, dim3((total + 255) / 256), dim3(256), 0, st, M, T, theta, (double*)frag, bias,
                      queue);

@@ -1,8 +1,5 @@
 // The planning functions of the library (sizes, launch shapes: host code without a device)
 // behind a C interface. Handles are made by hand, for a chip of 256 compute units.
-#include <limits>
-#include <type_traits>
-
 #include "../paper_2506_07430_amd/csrc/api.cpp"
 
 extern "C" {
@@ -15,13 +12,16 @@ elocal_t host_handle(int n, int na, int nb) {
 
 void host_free(elocal_t h) { delete h; }
 
-// Work items of an evaluation, and the largest number that its work-item counter holds.
-int64_t host_items(elocal_t h, const elocal_ansatz* a, int64_t B, unsigned long long* limit, int64_t* waves) {
+// Work items of an evaluation; the tickets its launch hands out, samples per ticket's step, items
+// per sample, and waves.
+int64_t host_items(elocal_t h, const elocal_ansatz* a, int64_t B, int64_t* out) {
   AnsatzGeom G;
   if (make_eval_geom(h, a, G) != ELOCAL_OK) return -1;
   const EvalPlan p = plan_eval(h, G, B);
-  *limit = (unsigned long long)std::numeric_limits<std::remove_pointer_t<decltype(p.px.queue)>>::max();
-  *waves = p.prefix ? (int64_t)p.grid * p.waves : 0;
+  out[0] = p.px.tickets;
+  out[1] = p.px.bt;
+  out[2] = p.ips;
+  out[3] = p.prefix ? (int64_t)p.grid * p.waves : 0;
   return p.n_items;
 }
 

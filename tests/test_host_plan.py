@@ -38,12 +38,15 @@ def ansatz(widths, precision):
     (64, 32, (256,) * 8, 2_400_000, elocal.BF16),
 ])
 def test_work_item_counter_does_not_wrap(plan, n, na, widths, samples, precision):
-    """Every wave takes tickets until one is past the last item, so the counter must hold the
-    items and one more ticket per wave: a counter that wraps hands out items for ever."""
+    """Every wave takes tickets until one is past the last, so the 32-bit counter must hold the
+    tickets and one more per wave: a counter that wraps hands out work for ever. The tickets
+    (items of samples b, b + step, ...) cover every item once."""
     h = ctypes.c_void_p(plan.host_handle(n, na, na))
-    limit, waves = ctypes.c_ulonglong(), ctypes.c_int64()
+    out = (ctypes.c_int64 * 4)()
     a = ansatz(widths, precision)
-    items = plan.host_items(h, ctypes.byref(a), ctypes.c_int64(samples), ctypes.byref(limit), ctypes.byref(waves))
+    items = plan.host_items(h, ctypes.byref(a), ctypes.c_int64(samples), out)
     plan.host_free(h)
-    assert items >= samples and waves.value > 0
-    assert items + waves.value <= limit.value
+    tickets, step, per_sample, waves = out
+    assert items == per_sample * samples and waves > 0
+    assert tickets + waves < 2 ** 32
+    assert tickets == per_sample * step and 1 <= step <= samples

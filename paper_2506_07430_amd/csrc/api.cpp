@@ -309,8 +309,6 @@ struct EvalPlan {
 };
 
 constexpr size_t kLdsBytes = 160 * 1024;
-// Fewest orbitals for which the prefix-shared evaluation is used.
-constexpr int kPrefixMinOrb = 10;
 
 // Persistent grid: 32 waves per CU in total (a few rounds of resident blocks), unless tuned.
 int64_t grid_cap(const elocal_ctx* h, int waves) {
@@ -541,10 +539,34 @@ void plan_prefix_lds(const AnsatzGeom& G, int kernel_hmax, int waves, size_t bia
   }
 }
 
+// Whether a system's lists are long enough for the prefix-shared evaluation. It runs all
+// n (2n - 1) parents of a sample, also those with few entries or none, and a parent costs as much
+// as several entries of the plain kernels: 7 in BF16 mode (its tile is one pass of a wave,
+// posting the entries included), 2 (width 128) to 4 (width 256) in FP64. It saves about three
+// quarters of an entry. With few electrons the parents are most of the work (60 orbitals, one
+// electron, 256x3, 512 samples: plain 0.22 ms BF16 and 0.93 ms FP64, shared 30 and 214 ms), and
+// their entries are so uneven that the longest segment bounds a batch of tens of samples.
+// Plain against shared, ms, by entries per parent (r):
+//   BF16, 1024 samples   64x1   16 orbitals r 11.7 0.41 0.57   20 r 18 1.01 1.03   22 r 22 1.68 1.45
+//                        128x2  12 r 6.6 0.28 0.44   16 r 11.7 0.70 0.81   20 r 15 1.48 1.41   24 r 26 3.75 2.73
+//                        256x3  12 r 6.6 0.86 1.20   18 r 11.6, 192 samples 0.64 0.63
+//   BF16, 32 samples     256x1  40 r 41 (a quarter filled) 0.97 1.36   34 r 44 (a third) 0.89 0.64
+//                        64x2   60 r 67 (a fifth) 2.53 3.58   60 r 131 (a third) 4.75 3.49
+//   FP64, 1024 samples   64x2   12 r 3.6 0.49 0.49, r 6.6 0.84 0.64   64x1  10 r 4.6 0.27 0.37
+//                        256x1  14 r 5.9 1.91 2.52   256x2  16 r 8.5 10.8 7.3
+//   FP64, 32 samples     128x2  40 r 13.6 2.24 3.71, r 29.7 4.83 4.21
+// The rule does not look at the batch, so that a sample's energy does not either.
+bool prefix_pays(const elocal_ctx* h, const AnsatzGeom& G) {
+  const double n = h->sys.n, r = (h->sys.C - 1.0) / (n * (2.0 * n - 1.0));
+  const int w = G.md.nout[0];
+  if (G.precision == ELOCAL_BF16) return r >= (w <= 64 ? 19.0 : w <= 128 ? 15.0 : 11.0) && 37.0 * r >= n * n;
+  return r >= (w <= 128 ? 5.0 : 8.0) && 80.0 * r >= n * n;
+}
+
 // Geometry of elocal_eval and elocal_eval_multi (the Pauli route and the others: make_geom).
 elocal_status make_eval_geom(const elocal_ctx* h, const elocal_ansatz* a, AnsatzGeom& G) {
   if (elocal_status e = make_geom(h, a, G)) return e;
-  G.prefix = prefix_net(G) && h->sys.n >= kPrefixMinOrb && h->sys.C > 1;
+  G.prefix = prefix_net(G) && prefix_pays(h, G);
   if (G.prefix) {
     if (G.precision == ELOCAL_BF16) pad_prefix(G);
     else prefix_md_f64(G);

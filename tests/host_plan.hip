@@ -12,6 +12,12 @@ elocal_t host_handle(int n, int na, int nb) {
 
 void host_free(elocal_t h) { delete h; }
 
+// 1 if an evaluation takes the prefix-shared kernels.
+int host_prefix(elocal_t h, const elocal_ansatz* a) {
+  AnsatzGeom G;
+  return make_eval_geom(h, a, G) == ELOCAL_OK ? (int)G.prefix : -1;
+}
+
 // Work items of an evaluation; the tickets its launch hands out, samples per ticket's step, items
 // per sample, and waves.
 int64_t host_items(elocal_t h, const elocal_ansatz* a, int64_t B, int64_t* out) {

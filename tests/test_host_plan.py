@@ -50,3 +50,27 @@ def test_work_item_counter_does_not_wrap(plan, n, na, widths, samples, precision
     assert items == per_sample * samples and waves > 0
     assert tickets + waves < 2 ** 32
     assert tickets == per_sample * step and 1 <= step <= samples
+
+
+@pytest.mark.parametrize("precision", [elocal.BF16, elocal.FP64])
+@pytest.mark.parametrize("n,na,nb,widths", [(12, 1, 0, (128, 128)), (24, 1, 1, (128, 128)), (40, 2, 2, (256,) * 3),
+                                            (60, 1, 0, (256,) * 3), (60, 5, 5, (256,) * 3), (64, 2, 3, (64, 64))])
+def test_few_electrons_run_every_entry(plan, n, na, nb, widths, precision):
+    """The shared evaluation runs all n (2 n - 1) parents of a sample, which cost 2 to 7 entries
+    each: systems of few electrons were up to 200 times slower by it (60 orbitals, one electron)."""
+    h = ctypes.c_void_p(plan.host_handle(n, na, nb))
+    a = ansatz(widths, precision)
+    assert plan.host_prefix(h, ctypes.byref(a)) == 0
+    plan.host_free(h)
+
+
+def test_systems_of_the_gpu_test_take_the_shared_evaluation(plan):
+    from tests.test_gpu_prefix_rule import SHAPES
+    more = [(p, n, k, k, w, 1) for p in (elocal.BF16, elocal.FP64)
+            for n, k, w in ((24, 12, (128, 128)), (24, 8, (128, 128)), (40, 14, (256,) * 3), (60, 26, (256,) * 3),
+                            (60, 20, (64, 64)), (64, 21, (256,) * 3))]
+    for precision, n, na, nb, widths, _ in SHAPES + more:
+        h = ctypes.c_void_p(plan.host_handle(n, na, nb))
+        a = ansatz(widths, precision)
+        assert plan.host_prefix(h, ctypes.byref(a)) == 1, (precision, n, na, nb, widths)
+        plan.host_free(h)

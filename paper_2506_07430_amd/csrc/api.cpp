@@ -552,7 +552,7 @@ void plan_prefix_lds(const AnsatzGeom& G, int kernel_hmax, int waves, size_t bia
 //                        256x3  12 r 6.6 0.86 1.20   18 r 11.6, 192 samples 0.64 0.63
 //   BF16, 32 samples     256x1  40 r 41 (a quarter filled) 0.97 1.36   34 r 44 (a third) 0.89 0.64
 //                        64x2   60 r 67 (a fifth) 2.53 3.58   60 r 131 (a third) 4.75 3.49
-//   FP64, 1024 samples   64x2   12 r 3.6 0.49 0.49, r 6.6 0.84 0.64   64x1  10 r 4.6 0.27 0.37
+//   FP64, 1024 samples   64x2   12 r 3.6 0.49 0.49, r 6.6 0.84 0.64   64x1  10 r 4.6 0.27 0.37   128x2  10 r 4.6 0.79 0.74
 //                        256x1  14 r 5.9 1.91 2.52   256x2  16 r 8.5 10.8 7.3
 //   FP64, 32 samples     128x2  40 r 13.6 2.24 3.71, r 29.7 4.83 4.21
 // The rule does not look at the batch, so that a sample's energy does not either.
@@ -560,7 +560,7 @@ bool prefix_pays(const elocal_ctx* h, const AnsatzGeom& G) {
   const double n = h->sys.n, r = (h->sys.C - 1.0) / (n * (2.0 * n - 1.0));
   const int w = G.md.nout[0];
   if (G.precision == ELOCAL_BF16) return r >= (w <= 64 ? 19.0 : w <= 128 ? 15.0 : 11.0) && 37.0 * r >= n * n;
-  return r >= (w <= 128 ? 5.0 : 8.0) && 80.0 * r >= n * n;
+  return r >= (w <= 128 ? 4.5 : 8.0) && 80.0 * r >= n * n;
 }
 
 // Geometry of elocal_eval and elocal_eval_multi (the Pauli route and the others: make_geom).

@@ -631,6 +631,17 @@ void plan_items(const elocal_ctx* h, int64_t B, double chip, EvalPlan& p) {
   p.tpi = std::max(1u, X.spi);
 }
 
+// Whether BF16 items of `tpi` groups are run as parts of one: where the waves that the chip holds
+// finish `groups` single groups sooner than the rounds of whole items, by more than what storing
+// and adding the lanes' sums takes (16 waves per CU; whole items, parts, us: 8 orbitals, width 32,
+// 2048 samples 88, 72, 4096 samples 94, 111; 4 orbitals, where an item has one group, 37, 40;
+// 12 orbitals, 64x2, 512 samples 168, 120, 1024 samples 178, 201; 9 orbitals, 256x2, 2048 samples
+// 514, 353).
+bool parts_pay(const elocal_ctx* h, const AnsatzGeom& G, int64_t n_items, uint32_t tpi, int64_t groups) {
+  const int64_t slots = (int64_t)h->cu_count * eval_waves_bf16(G.hmax, G.nterms, eval_cols_default_bf16(G.hmax, G.nterms));
+  return 100 * ((n_items + slots - 1) / slots) * tpi * slots >= 115 * std::max(groups, slots);
+}
+
 constexpr int64_t kFewItems = 16384;     // four per wave slot of a chip of 256 CUs
 constexpr int64_t kMaxLaneSums = 32768;  // parts of 1 KiB of sums
 EvalPlan plan_eval(const elocal_ctx* h, const AnsatzGeom& G, int64_t B, int64_t list_len = -1, double chip = 1.0) {
@@ -655,7 +666,7 @@ EvalPlan plan_eval(const elocal_ctx* h, const AnsatzGeom& G, int64_t B, int64_t 
   if (!G.prefix && h->tune_groups <= 0 && p.n_items <= kFewItems) {
     if (G.precision == ELOCAL_BF16) {
       const uint32_t groups = (uint32_t)((rows + 63) / 64);
-      if ((int64_t)groups * B <= kMaxLaneSums) {
+      if ((int64_t)groups * B <= kMaxLaneSums && parts_pay(h, G, p.n_items, std::min(groups, p.tpi), groups * B)) {
         p.parts = p.tpi;   // (of one group each: a part of several would add them in another order)
         p.tpi = 1;
         p.ips = groups;

@@ -31,4 +31,10 @@ int64_t host_items(elocal_t h, const elocal_ansatz* a, int64_t B, int64_t* out) 
   return p.n_items;
 }
 
+// List-entry groups per work item of a BF16 evaluation that runs its items in parts, else 0.
+int host_parts(elocal_t h, const elocal_ansatz* a, int64_t B) {
+  AnsatzGeom G;
+  return make_eval_geom(h, a, G) == ELOCAL_OK ? (int)plan_eval(h, G, B).parts : -1;
+}
+
 }  // extern "C"

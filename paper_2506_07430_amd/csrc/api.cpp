@@ -722,7 +722,7 @@ EvalPlan plan_eval(const elocal_ctx* h, const AnsatzGeom& G, int64_t B, int64_t 
 }
 
 // Launches the prefix-shared kernel of a width class.
-hipError_t launch_prefix(const EvalArgs& E, int hmax, int cols, const EvalPlan& p, hipStream_t st) {
+hipError_t launch_prefix(const PrefixArgs& E, int hmax, int cols, const EvalPlan& p, hipStream_t st) {
   if (hmax == 64)
     return cols == 2 ? launch_prefix_w64c2(E, p.lmode, p.lds, p.grid, p.waves, st)
                      : launch_prefix_w64(E, p.lmode, p.lds, p.grid, p.waves, st);
@@ -732,7 +732,7 @@ hipError_t launch_prefix(const EvalArgs& E, int hmax, int cols, const EvalPlan& 
   return launch_prefix_w256(E, p.lmode, p.lds, p.grid, p.waves, st);
 }
 
-hipError_t launch_prefix_multi(const EvalArgs* args, int n_sys, int hmax, int cols, int lmode, size_t lds,
+hipError_t launch_prefix_multi(const PrefixArgs* args, int n_sys, int hmax, int cols, int lmode, size_t lds,
                                unsigned grid, int waves, hipStream_t st) {
   if (hmax == 64)
     return cols == 2 ? launch_prefix_multi_w64c2(args, n_sys, lmode, lds, grid, waves, st)
@@ -1100,7 +1100,7 @@ elocal_status elocal_eval(elocal_t h, elocal_stream s, const elocal_ansatz* a, c
   R.logpsi = logpsi;
   if (G.precision == ELOCAL_BF16) HIP_TRY(launch_rows_bf16(R, G.hmax, G.nterms, st), "sample pass launch");
   else HIP_TRY(launch_rows_f64(R, G.hmax, st), "sample pass launch");
-  EvalArgs E{};
+  PrefixArgs E{};
   E.sys = h->sys; E.made = M; E.x = x; E.B = B; E.ediag = w.ediag; E.F = w.F; E.lpx = w.lpx;
   E.lpx64 = w.lpx64; E.zphi = w.zphi; E.partial = p.parts ? w.lanes : w.partial; E.lane_sums = p.parts != 0; E.n_items = p.n_items; E.ips = p.ips;
   E.tpi = p.tpi;
@@ -1211,9 +1211,9 @@ struct MultiPlan {
   unsigned grid;
 };
 
-// the kernels index a plain array EvalArgs[n_sys]
-constexpr size_t kArgsStride = sizeof(EvalArgs);
-static_assert(sizeof(EvalArgs) % 8 == 0, "EvalArgs is stored in 4-byte words");
+// the kernels index arrays of these, and one launch stores one system's
+static_assert(sizeof(EvalArgs) % 8 == 0 && sizeof(PrefixArgs) % 8 == 0, "stored in 4-byte words, aligned to 8");
+static_assert(sizeof(EvalArgs) <= kStoreBytes && sizeof(PrefixArgs) <= kStoreBytesLong, "one launch per record");
 
 elocal_status plan_multi(int n_sys, const elocal_t* hs, const elocal_ansatz* const* a, const int64_t* B,
                          MultiPlan& M) {
@@ -1337,7 +1337,7 @@ elocal_status plan_multi(int n_sys, const elocal_t* hs, const elocal_ansatz* con
     M.lds = M.ctx_off + block_lds_bf16(waves);
   }
   M.args_off = off;
-  off = align256(off + kArgsStride * n_sys);
+  off = align256(off + M.n_pre * sizeof(PrefixArgs) + n_old * sizeof(EvalArgs));
   M.first_off = off;
   off = align256(off + sizeof(int64_t) * (n_sys + 1));
   M.bytes = off;
@@ -1369,7 +1369,8 @@ elocal_status elocal_eval_multi(int n_sys, const elocal_t* hs, elocal_stream s, 
   if (elocal_status st = check_device(hs[0])) return st;
   hipStream_t st = (hipStream_t)s;
   char* base = (char*)ws;
-  EvalArgs* d_args = (EvalArgs*)(base + M.args_off);
+  PrefixArgs* d_pre = (PrefixArgs*)(base + M.args_off);   // of the systems order[0 .. n_pre)
+  EvalArgs* d_args = (EvalArgs*)(d_pre + M.n_pre);        // and of the others
   int64_t* d_first = (int64_t*)(base + M.first_off);
   EvalWs W[ELOCAL_MAX_SYSTEMS];
   // per-system sample passes (packing, diagonal/Fock terms, ansatz at the samples)
@@ -1399,7 +1400,7 @@ elocal_status elocal_eval_multi(int n_sys, const elocal_t* hs, elocal_stream s, 
   for (int k = 0; k < n_sys; ++k) {
     const int i = M.order[k];
     const elocal_ctx* h = hs[i];
-    EvalArgs E{};
+    PrefixArgs E{};
     E.sys = h->sys; E.made = M.G[i].md; E.made.wfrag = W[i].frag; E.made.bias = W[i].bias;
     E.x = x[i]; E.B = B[i]; E.ediag = W[i].ediag; E.F = W[i].F; E.lpx = W[i].lpx; E.lpx64 = W[i].lpx64;
     E.zphi = W[i].zphi; E.partial = M.p[i].parts ? W[i].lanes : W[i].partial; E.lane_sums = M.p[i].parts != 0; E.n_items = M.p[i].n_items; E.ips = M.p[i].ips;
@@ -1414,7 +1415,8 @@ elocal_status elocal_eval_multi(int n_sys, const elocal_t* hs, elocal_stream s, 
       E.lds_bias_off = M.bias_off; E.lds_ctx_off = M.ctx_off; E.lds_lut_off = M.lut_off;
       for (int l = 0; l < kMaxLayers; ++l) E.lds_frag[l] = M.ldsw ? M.stage[i].frag[l] : -1;
     }
-    HIP_TRY(launch_store_bytes(&E, sizeof(EvalArgs), (char*)d_args + kArgsStride * k, st), "argument store");
+    if (k < M.n_pre) HIP_TRY(launch_store_bytes(&E, sizeof(PrefixArgs), d_pre + k, st), "argument store");
+    else HIP_TRY(launch_store_bytes(static_cast<EvalArgs*>(&E), sizeof(EvalArgs), d_args + (k - M.n_pre), st), "argument store");
   }
   const int n_old = n_sys - M.n_pre;
   bool any_pre = false;
@@ -1426,18 +1428,18 @@ elocal_status elocal_eval_multi(int n_sys, const elocal_t* hs, elocal_stream s, 
   const int slot = (int)(h0->ring_pos % elocal_ctx::kRing);
   if (timed) HIP_TRY(hipEventRecord(h0->ev_start[slot], st), "timing event");
   if (any_pre && M.precision == ELOCAL_FP64)
-    HIP_TRY(launch_prefix_multi_f64(d_args, M.n_pre, M.pre_hmax, M.pre.grid, st), "multi eval launch");
+    HIP_TRY(launch_prefix_multi_f64(d_pre, M.n_pre, M.pre_hmax, M.pre.grid, st), "multi eval launch");
   else if (any_pre)
-    HIP_TRY(launch_prefix_multi(d_args, M.n_pre, M.pre_hmax, M.pre.cols, M.pre.lmode, M.pre.lds, M.pre.grid,
+    HIP_TRY(launch_prefix_multi(d_pre, M.n_pre, M.pre_hmax, M.pre.cols, M.pre.lmode, M.pre.lds, M.pre.grid,
                                 M.pre.waves, st),
             "multi eval launch");
   if (any_old) {
     if (M.precision == ELOCAL_BF16)
-      HIP_TRY(launch_eval_multi_bf16(d_args + M.n_pre, d_first, n_old, M.hmax, M.G[0].nterms, M.cols, M.ldsw,
+      HIP_TRY(launch_eval_multi_bf16(d_args, d_first, n_old, M.hmax, M.G[0].nterms, M.cols, M.ldsw,
                                      M.inplace, M.lds, M.grid, M.waves, st),
               "multi eval launch");
     else
-      HIP_TRY(launch_eval_multi_f64(d_args + M.n_pre, d_first, n_old, M.hmax, M.grid, st), "multi eval launch");
+      HIP_TRY(launch_eval_multi_f64(d_args, d_first, n_old, M.hmax, M.grid, st), "multi eval launch");
   }
   if (timed) {
     HIP_TRY(hipEventRecord(h0->ev_stop[slot], st), "timing event");

@@ -388,30 +388,33 @@ __global__ void k_write_dtheta(GradPlan G) {
 
 // Copies a small host-side record (passed by value) to device memory, so a call can
 // hand per-system descriptors to a kernel without a host buffer or a synchronisation.
-struct Words256 {
-  uint32_t w[256];
+template <size_t BYTES>
+struct Words {
+  uint32_t w[BYTES / 4];
 };
 
-__global__ void k_store_words(Words256 src, uint32_t count, uint32_t* __restrict__ dst) {
+template <size_t BYTES>
+__global__ void k_store_words(Words<BYTES> src, uint32_t count, uint32_t* __restrict__ dst) {
   for (uint32_t i = threadIdx.x; i < count; i += blockDim.x) dst[i] = src.w[i];
 }
 
 // ----------------------------------------------------------------------------- launchers
+template <size_t BYTES>
+static hipError_t store_chunk(const uint32_t* src, size_t words, uint32_t* dst, hipStream_t st) {
+  Words<BYTES> w;
+  std::memcpy(w.w, src, words * 4);
+  hipLaunchKernelGGL(k_store_words<BYTES>, dim3(1), dim3(256), 0, st, w, (uint32_t)words, dst);
+  return hipGetLastError();
+}
+
 hipError_t launch_store_bytes(const void* src, size_t bytes, void* dst, hipStream_t st) {
   if (bytes % 4) return hipErrorInvalidValue;
   const uint32_t* s = (const uint32_t*)src;
   uint32_t* d = (uint32_t*)dst;
-  size_t words = bytes / 4;
-  while (words > 0) {
-    const uint32_t cnt = (uint32_t)(words < 256 ? words : 256);
-    Words256 w;
-    std::memcpy(w.w, s, cnt * 4);
-    hipLaunchKernelGGL(k_store_words, dim3(1), dim3(256), 0, st, w, cnt, d);
-    hipError_t e = hipGetLastError();
+  for (size_t left = bytes / 4, n; left > 0; left -= n, s += n, d += n) {
+    n = std::min(left, kStoreBytesLong / 4);
+    const hipError_t e = n * 4 <= kStoreBytes ? store_chunk<kStoreBytes>(s, n, d, st) : store_chunk<kStoreBytesLong>(s, n, d, st);
     if (e != hipSuccess) return e;
-    s += cnt;
-    d += cnt;
-    words -= cnt;
   }
   return hipSuccess;
 }

@@ -48,7 +48,9 @@ struct EvalArgs {
   const uint64_t* pl_z;
   const double* pl_coef;
   uint32_t pl_len;
-  // prefix-shared evaluation only
+};
+// ... and of the prefix-shared ones.
+struct PrefixArgs : EvalArgs {
   PrefixDev px;
   PrefixTop top;
 };
@@ -131,12 +133,12 @@ constexpr size_t kPrefixWaveBytes = 3840;   // LDS state of one wave (PrefixWave
 constexpr int kPrefixWavesF64 = 8;
 hipError_t launch_pack_prefix_f64(const MadeDev& M, const ThetaLayout& T, const double* theta, void* frag,
                                   double* bias, uint32_t* queue, hipStream_t st);
-hipError_t launch_prefix_f64(const EvalArgs& A, int hmax, unsigned grid, hipStream_t st);
-hipError_t launch_prefix_multi_f64(const EvalArgs* args, int n_sys, int hmax, unsigned grid, hipStream_t st);
+hipError_t launch_prefix_f64(const PrefixArgs& A, int hmax, unsigned grid, hipStream_t st);
+hipError_t launch_prefix_multi_f64(const PrefixArgs* args, int n_sys, int hmax, unsigned grid, hipStream_t st);
 #define ELOCAL_PREFIX_DECL(name)                                                                                    \
-  hipError_t launch_prefix_##name(const EvalArgs& A, int lmode, size_t lds, unsigned grid, int waves,               \
+  hipError_t launch_prefix_##name(const PrefixArgs& A, int lmode, size_t lds, unsigned grid, int waves,               \
                                   hipStream_t st);                                                                  \
-  hipError_t launch_prefix_multi_##name(const EvalArgs* args, int n_sys, int lmode, size_t lds, unsigned grid,      \
+  hipError_t launch_prefix_multi_##name(const PrefixArgs* args, int n_sys, int lmode, size_t lds, unsigned grid,      \
                                         int waves, hipStream_t st);
 ELOCAL_PREFIX_DECL(w64)
 ELOCAL_PREFIX_DECL(w64c2)
@@ -157,7 +159,10 @@ hipError_t launch_eval_multi_bf16(const EvalArgs* args, const int64_t* first, in
                                   hipStream_t st);
 hipError_t launch_eval_multi_f64(const EvalArgs* args, const int64_t* first, int n_sys, int hmax,
                                  unsigned grid, hipStream_t st);
-// Host record (bytes a multiple of 4) -> device memory, in stream order.
+// Host record (bytes a multiple of 4) -> device memory, in stream order. One launch takes
+// kStoreBytes, or kStoreBytesLong of a longer record (the size of its own argument, which the
+// host copies): eight systems of a call with 1 KiB per launch took 40 launches.
+constexpr size_t kStoreBytes = 2048, kStoreBytesLong = 4224;
 hipError_t launch_store_bytes(const void* src, size_t bytes, void* dst, hipStream_t st);
 
 hipError_t launch_pack_f64(const MadeDev& M, const ThetaLayout& T, const double* theta,

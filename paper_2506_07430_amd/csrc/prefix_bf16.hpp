@@ -323,7 +323,7 @@ struct NetBf16 {
     const uint64_t* xlut;
   };
   static constexpr int cols(int nb) { return prefix_cols(nb, kCap); }
-  static __device__ __forceinline__ double sample_lp(const EvalArgs& P, int64_t i) { return (double)P.lpx[i]; }
+  static __device__ __forceinline__ double sample_lp(const PrefixArgs& P, int64_t i) { return (double)P.lpx[i]; }
   template <int NW>
   static __device__ __forceinline__ float step(RowCursor<NW>& rc, int ta, int tb, int na, int nb, const f32x4& z) {
     return cond_log2p_step<NW>(rc, ta, tb, na, nb, z);
@@ -348,7 +348,7 @@ struct NetBf16 {
 
 // LMODE 2: copies the fragments of the last classes (input blocks >= bs, o-blocks that
 // read them) to LDS. (Only the parents' passes read biases: those stay in global memory.)
-__device__ __forceinline__ void stage_top(const EvalArgs& P, unsigned char* smem) {
+__device__ __forceinline__ void stage_top(const PrefixArgs& P, unsigned char* smem) {
   const MadeDev& M = P.made;
   const PrefixTop& T = P.top;
   h16x8* sw = (h16x8*)smem;
@@ -364,14 +364,14 @@ __device__ __forceinline__ void stage_top(const EvalArgs& P, unsigned char* smem
 }
 
 template <int LMODE>
-__device__ __forceinline__ void stage_prefix(const EvalArgs& P, unsigned char* smem) {
+__device__ __forceinline__ void stage_prefix(const PrefixArgs& P, unsigned char* smem) {
   if (LMODE == 1) stage_weights(P.made, P.lds_frag, smem, P.lds_bias_off);
   if (LMODE == 2) stage_top(P, smem);
 }
 
 // What a wave reads its weights, biases and checkpoints from.
 template <int HB, int COLS, int LMODE>
-__device__ __forceinline__ typename NetBf16<HB, COLS, LMODE>::Sources wave_sources(const EvalArgs& P,
+__device__ __forceinline__ typename NetBf16<HB, COLS, LMODE>::Sources wave_sources(const PrefixArgs& P,
                                                                                  const unsigned char* smem, int wid,
                                                                                  int lane, const uint64_t* xlut) {
   typename NetBf16<HB, COLS, LMODE>::Sources s;
@@ -390,7 +390,7 @@ __device__ __forceinline__ typename NetBf16<HB, COLS, LMODE>::Sources wave_sourc
 // One system: waves take work items from a queue (parents with early changes have far more
 // entries than late ones) until it is empty.
 template <int HB, int COLS, int NW, int LMODE>
-__global__ void __launch_bounds__(64 * prefix_waves_bf16(32 * HB, COLS), 1) k_prefix_bf16(EvalArgs P) {
+__global__ void __launch_bounds__(64 * prefix_waves_bf16(32 * HB, COLS), 1) k_prefix_bf16(PrefixArgs P) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int lane = threadIdx.x & 63, wid = sgpr(threadIdx.x >> 6);
   const uint64_t* xlut = fill_xlut(smem, P.lds_lut_off);
@@ -411,7 +411,7 @@ __global__ void __launch_bounds__(64 * prefix_waves_bf16(32 * HB, COLS), 1) k_pr
 // system's queue until that is empty. LDS offsets are those of system 0's arguments.
 template <int HB, int COLS, int LMODE>
 __global__ void __launch_bounds__(64 * prefix_waves_bf16(32 * HB, COLS), 1)
-    k_prefix_multi_bf16(const EvalArgs* __restrict__ args, int n_sys) {
+    k_prefix_multi_bf16(const PrefixArgs* __restrict__ args, int n_sys) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int lane = threadIdx.x & 63, wid = sgpr(threadIdx.x >> 6);
   const uint64_t* xlut = fill_xlut(smem, args[0].lds_lut_off);
@@ -423,7 +423,7 @@ __global__ void __launch_bounds__(64 * prefix_waves_bf16(32 * HB, COLS), 1)
   int s = 0;
   while (s + 1 < n_sys && blockIdx.x >= args[s + 1].px.block0) ++s;
   for (int i = 0; i < n_sys; ++i, s = s + 1 < n_sys ? s + 1 : 0) {
-    const EvalArgs& P = args[s];
+    const PrefixArgs& P = args[s];
     // (the barrier: every wave is done with the previous system's weights)
     const bool left = threadIdx.x == 0 && __hip_atomic_load(P.px.queue, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <
                                               P.px.tickets;
@@ -444,7 +444,7 @@ __global__ void __launch_bounds__(64 * prefix_waves_bf16(32 * HB, COLS), 1)
 // ----------------------------------------------------------------------------- launchers
 // lmode 0 or LM (the class's LDS mode).
 template <int HB, int COLS, int LM>
-static hipError_t launch_prefix_class(const EvalArgs& A, int lmode, size_t lds, unsigned grid, int waves,
+static hipError_t launch_prefix_class(const PrefixArgs& A, int lmode, size_t lds, unsigned grid, int waves,
                                       hipStream_t st) {
   auto go = [&](auto kern) {
     const hipError_t e = allow_lds(kern, lds);
@@ -459,7 +459,7 @@ static hipError_t launch_prefix_class(const EvalArgs& A, int lmode, size_t lds, 
 }
 
 template <int HB, int COLS, int LM>
-static hipError_t launch_prefix_multi_class(const EvalArgs* args, int n_sys, int lmode, size_t lds, unsigned grid,
+static hipError_t launch_prefix_multi_class(const PrefixArgs* args, int n_sys, int lmode, size_t lds, unsigned grid,
                                             int waves, hipStream_t st) {
   auto kern = lmode ? k_prefix_multi_bf16<HB, COLS, LM> : k_prefix_multi_bf16<HB, COLS, 0>;
   const hipError_t e = allow_lds(kern, lds);
@@ -470,11 +470,11 @@ static hipError_t launch_prefix_multi_class(const EvalArgs* args, int n_sys, int
 }
 
 #define ELOCAL_PREFIX_CLASS(name, HB, COLS, LM)                                                                     \
-  hipError_t launch_prefix_##name(const EvalArgs& A, int lmode, size_t lds, unsigned grid, int waves,               \
+  hipError_t launch_prefix_##name(const PrefixArgs& A, int lmode, size_t lds, unsigned grid, int waves,               \
                                   hipStream_t st) {                                                                 \
     return launch_prefix_class<HB, COLS, LM>(A, lmode, lds, grid, waves, st);                                        \
   }                                                                                                                 \
-  hipError_t launch_prefix_multi_##name(const EvalArgs* args, int n_sys, int lmode, size_t lds, unsigned grid,      \
+  hipError_t launch_prefix_multi_##name(const PrefixArgs* args, int n_sys, int lmode, size_t lds, unsigned grid,      \
                                         int waves, hipStream_t st) {                                                \
     return launch_prefix_multi_class<HB, COLS, LM>(args, n_sys, lmode, lds, grid, waves, st);                        \
   }

@@ -26,7 +26,7 @@ namespace elocal {
 // the pointer comes from, so that the loads stay where they are written: hoisted out of the
 // loops, the tables of every pass variant together overflow the scalar registers, and each
 // use then costs a v_readlane.
-typedef const __attribute__((address_space(4))) EvalArgs CArgs;
+typedef const __attribute__((address_space(4))) PrefixArgs CArgs;
 __device__ __forceinline__ CArgs* opaque(CArgs* p) {
   asm volatile("" : "+s"(p));
   return p;
@@ -179,7 +179,7 @@ __device__ __forceinline__ void with_blocks(int nblk, F&& f) {
 // takes every (mask + 1)-th group, from `part` on; the parents' excitations are group 0.
 // LO: the fewest blocks of a network that the kernel takes.
 template <class Net, int HB, int LO, int NW>
-__device__ __forceinline__ void run_segment(const EvalArgs& P, CArgs* args, const typename Net::Sources& src,
+__device__ __forceinline__ void run_segment(const PrefixArgs& P, CArgs* args, const typename Net::Sources& src,
                                             PrefixWave& pw, const PrefixSample<NW>& st, uint32_t seg, uint32_t part,
                                             uint32_t mask, int lane0, double& sum) {
   typedef typename Net::Real Real;
@@ -331,7 +331,7 @@ __device__ __forceinline__ void run_segment(const EvalArgs& P, CArgs* args, cons
 struct ItemSpan {
   uint32_t s0, s1, k, mask;
 };
-__device__ __forceinline__ ItemSpan item_span(const EvalArgs& P, uint32_t part) {
+__device__ __forceinline__ ItemSpan item_span(const PrefixArgs& P, uint32_t part) {
   const uint32_t spi = P.px.spi;
   if (spi != 0) return {part * spi, min(P.px.seg0[P.px.nblk], part * spi + spi), 0u, 0u};
   int c = 0;
@@ -344,7 +344,7 @@ __device__ __forceinline__ ItemSpan item_span(const EvalArgs& P, uint32_t part) 
 // P.px.bt apart) P.px.spi segments, or (spi = 0) a part of one of them. The partial sums go to
 // P.partial.
 template <class Net, int HB, int LO, int NW>
-__device__ __forceinline__ void run_item(const EvalArgs& P, CArgs* args, const typename Net::Sources& src,
+__device__ __forceinline__ void run_item(const PrefixArgs& P, CArgs* args, const typename Net::Sources& src,
                                          PrefixWave& pw, uint32_t ticket, PrefixSample<NW>& st, int lane) {
   const SysDev& S = P.sys;
   // parts of segments: the same part of every sample in turn, so that the long ones (of the

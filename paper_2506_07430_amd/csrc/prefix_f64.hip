@@ -69,7 +69,7 @@ struct NetF64 {
     __amdgpu_buffer_rsrc_t w, bias, ck;
   };
   static constexpr int cols(int nb) { return nb <= 2 ? 2 : 1; }
-  static __device__ __forceinline__ double sample_lp(const EvalArgs& P, int64_t i) { return P.lpx64[i]; }
+  static __device__ __forceinline__ double sample_lp(const PrefixArgs& P, int64_t i) { return P.lpx64[i]; }
   static __device__ __forceinline__ double2 ratio(double hv, double zp, double sig_x, double dA) {
     return ratio_term64(hv, zp, sig_x, dA);
   }
@@ -290,7 +290,7 @@ struct NetF64 {
   }
 };
 
-__device__ __forceinline__ NetF64::Sources wave_sources_f64(const EvalArgs& P, int wid) {
+__device__ __forceinline__ NetF64::Sources wave_sources_f64(const PrefixArgs& P, int wid) {
   const uint32_t wave = blockIdx.x * (blockDim.x >> 6) + (uint32_t)wid;
   const uint64_t base = (uint64_t)(P.px.scratch + (size_t)wave * P.px.stride);
   const uint64_t sbase = (uint64_t)(uint32_t)sgpr((int)(uint32_t)base) | (uint64_t)(uint32_t)sgpr((int)(base >> 32)) << 32;
@@ -300,7 +300,7 @@ __device__ __forceinline__ NetF64::Sources wave_sources_f64(const EvalArgs& P, i
 
 // (see k_prefix_bf16)
 template <int HB, int NW>
-__global__ void __launch_bounds__(64 * kPrefixWavesF64, 1) k_prefix_f64(EvalArgs P) {
+__global__ void __launch_bounds__(64 * kPrefixWavesF64, 1) k_prefix_f64(PrefixArgs P) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int lane = threadIdx.x & 63, wid = sgpr(threadIdx.x >> 6);
   PrefixWave& pw = ((PrefixWave*)smem)[wid];
@@ -314,12 +314,12 @@ __global__ void __launch_bounds__(64 * kPrefixWavesF64, 1) k_prefix_f64(EvalArgs
 
 template <int HB>
 __global__ void __launch_bounds__(64 * kPrefixWavesF64, 1)
-    k_prefix_multi_f64(const EvalArgs* __restrict__ args, int n_sys) {
+    k_prefix_multi_f64(const PrefixArgs* __restrict__ args, int n_sys) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int lane = threadIdx.x & 63, wid = sgpr(threadIdx.x >> 6);
   PrefixWave& pw = ((PrefixWave*)smem)[wid];
   for (int s = 0; s < n_sys; ++s) {
-    const EvalArgs& P = args[s];
+    const PrefixArgs& P = args[s];
     const NetF64::Sources src = wave_sources_f64(P, wid);
     PrefixSample<2> st;
     st.b = -1;
@@ -336,7 +336,7 @@ hipError_t launch_pack_prefix_f64(const MadeDev& M, const ThetaLayout& T, const 
   return hipGetLastError();
 }
 
-hipError_t launch_prefix_f64(const EvalArgs& A, int hmax, unsigned grid, hipStream_t st) {
+hipError_t launch_prefix_f64(const PrefixArgs& A, int hmax, unsigned grid, hipStream_t st) {
   if (A.n_items <= 0) return hipSuccess;
   auto go = [&](auto kern) {
     hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * kPrefixWavesF64), kPrefixWavesF64 * sizeof(PrefixWave), st, A);
@@ -348,7 +348,7 @@ hipError_t launch_prefix_f64(const EvalArgs& A, int hmax, unsigned grid, hipStre
   return one ? go(k_prefix_f64<8, 1>) : go(k_prefix_f64<8, 2>);
 }
 
-hipError_t launch_prefix_multi_f64(const EvalArgs* args, int n_sys, int hmax, unsigned grid, hipStream_t st) {
+hipError_t launch_prefix_multi_f64(const PrefixArgs* args, int n_sys, int hmax, unsigned grid, hipStream_t st) {
   auto go = [&](auto kern) {
     hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * kPrefixWavesF64), kPrefixWavesF64 * sizeof(PrefixWave), st, args,
                        n_sys);

@@ -149,6 +149,12 @@ struct AnsatzGeom {
   const MadeDev& prefix_md() const { return precision == ELOCAL_BF16 ? md : pm; }
 };
 
+// Units of degree <= D in a hidden layer of width w (unit j has degree j mod (n - 1) + 1).
+int units_le(int n, int w, int D) {
+  const int q = n - 1, d = std::max(0, std::min(D, q));
+  return w / q * d + std::min(w % q, d);
+}
+
 // Compact BF16 packing: only the k-blocks each o-block uses are stored.
 void pack_bf16_offsets(AnsatzGeom& G) {
   MadeDev& M = G.md;
@@ -223,11 +229,6 @@ elocal_status make_geom(const elocal_ctx* h, const elocal_ansatz* a, AnsatzGeom&
   // is covered by whole 16-unit blocks (4 k-steps each).
   {
     auto deg_at = [&](int width, int u) { return sorted_unit(n, width, u) % (n - 1) + 1; };
-    auto count_le = [&](int width, int D) {
-      int c = 0;
-      for (int j = 0; j < width; ++j) c += (j % (n - 1)) + 1 <= D;
-      return c;
-    };
     for (int l = 0; l <= L; ++l) {
       for (int ob = 0; ob < kMaxOutBlocks; ++ob) M.kend[l][ob] = M.nk[l];
       for (int ob = 0; ob < M.nob[l]; ++ob) {
@@ -235,12 +236,12 @@ elocal_status make_geom(const elocal_ctx* h, const elocal_ansatz* a, AnsatzGeom&
         if (l < L) {
           const int w = a->widths[l];
           const int mmax = deg_at(w, std::min(16 * ob + 15, w - 1));
-          need = (l == 0) ? 2 * mmax : count_le(a->widths[l - 1], mmax);
+          need = (l == 0) ? 2 * mmax : units_le(n, a->widths[l - 1], mmax);
         } else {
           const int ph = bf ? 4 * (n - 1) : 4 * n;   // phase row
           const bool phase = 16 * ob <= ph && ph < 16 * ob + 16;
           const int D = std::min(4 * ob + 3, n - 1);
-          need = phase ? M.nin[l] : count_le(a->widths[L - 1], D);
+          need = phase ? M.nin[l] : units_le(n, a->widths[L - 1], D);
         }
         int ke;
         if (bf) ke = (need + 31) / 32;
@@ -408,16 +409,11 @@ void prefix_md_f64(AnsatzGeom& G) {
     for (int ob = 0; ob < M.nob[l]; ++ob) {
       int need;
       const int w = M.nout[0];
-      auto count_le = [&](int D) {
-        int c = 0;
-        for (int j = 0; j < w; ++j) c += (j % (n - 1)) + 1 <= D;
-        return c;
-      };
       if (l < L) {
         const int mmax = sorted_unit(n, w, std::min(16 * ob + 15, w - 1)) % (n - 1) + 1;
-        need = l == 0 ? 2 * mmax : count_le(mmax);
+        need = l == 0 ? 2 * mmax : units_le(n, w, mmax);
       } else {
-        need = 16 * ob + 16 > 4 * (n - 1) ? M.nin[l] : count_le(4 * ob + 3);
+        need = 16 * ob + 16 > 4 * (n - 1) ? M.nin[l] : units_le(n, w, 4 * ob + 3);
       }
       M.kend[l][ob] = std::max(1, std::min(M.nk[l], (need + 15) / 16));
     }
@@ -466,15 +462,10 @@ void plan_prefix(const elocal_ctx* h, const AnsatzGeom& G, PrefixDev& X) {
   const int n = M.n, w = M.nout[0], L = M.L, nblk = w / 32;
   X.nblk = nblk;
   X.extra = bf ? prefix_extra(M) : 0;
-  auto count_le = [&](int q) {   // hidden units of degree <= q
-    int c = 0;
-    for (int j = 0; j < w; ++j) c += (j % (n - 1)) + 1 <= q;
-    return c;
-  };
   PrefixClass* K = X.cls;
   for (int b = 0; b <= kMaxClasses; ++b) K[b].qb = n;
   for (int q = n - 1; q >= 0; --q)
-    for (int b = 0, c = std::min(count_le(q) / 32, nblk - 1); b <= c; ++b) K[b].qb = q;
+    for (int b = 0, c = std::min(units_le(n, w, q) / 32, nblk - 1); b <= c; ++b) K[b].qb = q;
   auto slots = [&](int b) { return (uint32_t)(2 * (nblk - b) * L + M.nob[L] - K[b].qb / 4); };
   for (int b = nblk - 1; b >= 0; --b) {
     K[b].kin = 2 * K[b].qb / (bf ? 32 : 16);

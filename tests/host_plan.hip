@@ -37,4 +37,6 @@ int host_parts(elocal_t h, const elocal_ansatz* a, int64_t B) {
   return make_eval_geom(h, a, G) == ELOCAL_OK ? (int)plan_eval(h, G, B).parts : -1;
 }
 
+int host_units_le(int n, int w, int D) { return units_le(n, w, D); }
+
 }  // extern "C"

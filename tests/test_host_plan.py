@@ -90,3 +90,10 @@ def test_items_in_parts_only_where_waves_are_idle(plan, n, na, nb, widths, sampl
     a = ansatz(widths, elocal.BF16)
     assert plan.host_parts(h, ctypes.byref(a), ctypes.c_int64(samples)) == parts
     plan.host_free(h)
+
+
+def test_units_up_to_a_degree_in_closed_form(plan):
+    for n in (2, 3, 10, 33, 64):
+        for w in (32, 96, 256):
+            for d in range(-1, n + 66):
+                assert plan.host_units_le(n, w, d) == sum(j % (n - 1) + 1 <= d for j in range(w))

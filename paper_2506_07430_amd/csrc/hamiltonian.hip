@@ -46,9 +46,10 @@ __global__ void __launch_bounds__(256) k_prep(SysDev S, const uint64_t* __restri
                                               double* __restrict__ ediag, double* __restrict__ F) {
   __shared__ SampleCtx ctxs[4];
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  const int64_t wave = (int64_t)blockIdx.x * 4 + wid;
-  const int64_t b = wave / parts;
-  const int part = (int)(wave % parts);
+  // (32-bit division: a grid has fewer than 2^24 blocks of 256 threads)
+  const uint32_t wave = blockIdx.x * 4u + (uint32_t)wid;
+  const int64_t b = wave / (uint32_t)parts;
+  const int part = (int)(wave % (uint32_t)parts);
   if (b >= B) return;
   SampleCtx& c = ctxs[wid];
   uint64_t xv[NW];

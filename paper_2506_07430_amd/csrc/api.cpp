@@ -630,7 +630,7 @@ void plan_items(const elocal_ctx* h, int64_t B, double chip, EvalPlan& p) {
 // 514, 353).
 bool parts_pay(const elocal_ctx* h, const AnsatzGeom& G, int64_t n_items, uint32_t tpi, int64_t groups) {
   const int64_t slots = (int64_t)h->cu_count * eval_waves_bf16(G.hmax, G.nterms, eval_cols_default_bf16(G.hmax, G.nterms));
-  return 100 * ((n_items + slots - 1) / slots) * tpi * slots >= 115 * std::max(groups, slots);
+  return tpi > 1 && 100 * ((n_items + slots - 1) / slots) * tpi * slots >= 115 * std::max(groups, slots);
 }
 
 constexpr int64_t kFewItems = 16384;     // four per wave slot of a chip of 256 CUs

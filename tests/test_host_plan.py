@@ -78,7 +78,7 @@ def test_systems_of_the_gpu_test_take_the_shared_evaluation(plan):
 
 @pytest.mark.parametrize("n,na,nb,widths,samples,parts", [
     (8, 4, 4, (32,), 1, 8), (8, 4, 4, (32,), 2048, 8), (8, 4, 4, (32,), 4096, 0),   # 4096 waves of the chip
-    (4, 2, 2, (32,), 1, 0), (4, 2, 2, (32,), 16384, 0),                             # one group per sample
+    (4, 2, 2, (32,), 1, 0), (4, 2, 2, (32,), 4097, 0), (4, 2, 2, (32,), 16384, 0),  # one group per sample
     (6, 3, 3, (64, 64), 2048, 8), (6, 3, 3, (64, 64), 8192, 0),
     (12, 6, 6, (64, 64), 512, 8), (12, 6, 6, (64, 64), 1024, 0),
     (8, 4, 4, (256, 256), 1024, 8), (8, 4, 4, (256, 256), 2048, 0), (9, 4, 5, (256, 256), 2048, 8),

@@ -134,7 +134,8 @@ int elocal_words(elocal_t h);
 int64_t elocal_num_params(int n_orb, int n_hidden, const int* widths);
 
 /* Bytes of device workspace a call needs (op = ELOCAL_OP_*; `a` may be NULL for
- * ELOCAL_OP_CONNECT). 0 on invalid arguments (elocal_last_error says why). */
+ * ELOCAL_OP_CONNECT), never less than for a smaller batch: a workspace sized for the largest
+ * batch serves every one. 0 on invalid arguments (elocal_last_error says why). */
 size_t elocal_workspace_bytes(elocal_t h, const elocal_ansatz* a, int64_t B, int op);
 
 /*
@@ -387,9 +388,9 @@ elocal_status elocal_tune(elocal_t h, int param, int64_t value);
  * kernel variant is built for, ELOCAL_INFO_ITEMS work items, ELOCAL_INFO_LDS_BYTES LDS per
  * block, ELOCAL_INFO_INPLACE 1 when the hidden layers are updated in place (one activation
  * array in registers; chosen when every hidden o-block pair j reads k-blocks j + 1 to j + 2
- * only), else 0; ELOCAL_INFO_WS_BYTES the workspace with which the launch takes all its
- * blocks (elocal_workspace_bytes is what a call needs: with less room than this the launch
- * may take fewer blocks, with the same results).
+ * only), else 0; ELOCAL_INFO_WS_BYTES the workspace with which launches of up to B
+ * samples take all their blocks (elocal_workspace_bytes is what a call needs: with less room
+ * than this a launch may take fewer blocks, with the same results).
  */
 enum {
   ELOCAL_INFO_GRID = 0, ELOCAL_INFO_GROUPS = 1, ELOCAL_INFO_WAVES = 2, ELOCAL_INFO_COLS = 3,

@@ -576,7 +576,7 @@ elocal_status make_eval_geom(const elocal_ctx* h, const elocal_ansatz* a, Ansatz
 constexpr int64_t kFineItems = 131072;   // a few tens of items per wave of the chip
 constexpr int kMaxLgParts = 4;
 constexpr int64_t kMaxTickets = 1ll << 31;
-void plan_items(const elocal_ctx* h, int64_t B, double chip, EvalPlan& p) {
+void plan_items(const elocal_ctx* h, int64_t B, double chip, bool split, EvalPlan& p) {
   PrefixDev& X = p.px;
   const uint32_t nseg = X.seg0[X.nblk];
   const uint32_t group = h->tune_groups > 0 ? (uint32_t)std::min<int64_t>(h->tune_groups, nseg)
@@ -584,7 +584,7 @@ void plan_items(const elocal_ctx* h, int64_t B, double chip, EvalPlan& p) {
   X.spi = group;
   X.lgp = 0;
   p.ips = p.count = (nseg + group - 1) / group;
-  if (h->tune_groups <= 0 && (int64_t)nseg * B <= kFineItems) {
+  if (split && h->tune_groups <= 0 && (int64_t)nseg * B <= kFineItems) {
     X.spi = 0;
     p.count = nseg;
     p.fold = group;
@@ -622,6 +622,14 @@ void plan_items(const elocal_ctx* h, int64_t B, double chip, EvalPlan& p) {
   p.tpi = std::max(1u, X.spi);
 }
 
+// Blocks of a prefix-shared launch: every wave has its own scratch, so one block per CU (a block
+// of fewer waves than the kernel is built for leaves room for more).
+unsigned prefix_grid(const elocal_ctx* h, const AnsatzGeom& G, const EvalPlan& p, int64_t items) {
+  const int full = G.precision == ELOCAL_BF16 ? prefix_waves_bf16(G.hmax, p.cols) : kPrefixWavesF64;
+  const int64_t want = (items + p.waves - 1) / p.waves, cap = (int64_t)h->cu_count * std::max(1, full / p.waves);
+  return (unsigned)std::max<int64_t>(1, std::min({want, cap, grid_cap(h, p.waves)}));
+}
+
 // Whether BF16 items of `tpi` groups are run as parts of one: where the waves that the chip holds
 // finish `groups` single groups sooner than the rounds of whole items, by more than what storing
 // and adding the lanes' sums takes (16 waves per CU; whole items, parts, us: 8 orbitals, width 32,
@@ -635,7 +643,9 @@ bool parts_pay(const elocal_ctx* h, const AnsatzGeom& G, int64_t n_items, uint32
 
 constexpr int64_t kFewItems = 16384;     // four per wave slot of a chip of 256 CUs
 constexpr int64_t kMaxLaneSums = 32768;  // parts of 1 KiB of sums
-EvalPlan plan_eval(const elocal_ctx* h, const AnsatzGeom& G, int64_t B, int64_t list_len = -1, double chip = 1.0) {
+// (split: items in parts where a batch has few of them)
+EvalPlan plan_eval(const elocal_ctx* h, const AnsatzGeom& G, int64_t B, int64_t list_len = -1, double chip = 1.0,
+                   bool split = true) {
   EvalPlan p{};
   // BF16: groups of 64 entries (one per lane), 8 per item; FP64: tiles of 16, 16 per item
   p.rows_per_tile = (G.precision == ELOCAL_BF16) ? 64 : 16;
@@ -654,7 +664,7 @@ EvalPlan plan_eval(const elocal_ctx* h, const AnsatzGeom& G, int64_t B, int64_t 
   // are the same: FP64 items add their groups of 64 one by one, and the reduction folds the
   // parts in that order; BF16 parts leave their lanes' sums (adding every group over the lanes
   // cost the narrowest networks 2 to 9%), which a kernel of their own adds.
-  if (!G.prefix && h->tune_groups <= 0 && p.n_items <= kFewItems) {
+  if (split && !G.prefix && h->tune_groups <= 0 && p.n_items <= kFewItems) {
     if (G.precision == ELOCAL_BF16) {
       const uint32_t groups = (uint32_t)((rows + 63) / 64);
       if ((int64_t)groups * B <= kMaxLaneSums && parts_pay(h, G, p.n_items, std::min(groups, p.tpi), groups * B)) {
@@ -690,7 +700,7 @@ EvalPlan plan_eval(const elocal_ctx* h, const AnsatzGeom& G, int64_t B, int64_t 
   }
   if (p.prefix) {
     plan_prefix(h, G, p.px);
-    plan_items(h, B, chip, p);
+    plan_items(h, B, chip, split, p);
     if (G.precision == ELOCAL_BF16) {
       size_t wb = 0;
       plan_prefix_lds(G, G.hmax, p.waves, G.bbytes, p, wb);
@@ -704,12 +714,50 @@ EvalPlan plan_eval(const elocal_ctx* h, const AnsatzGeom& G, int64_t B, int64_t 
     p.inplace = true;
   }
   const int64_t want = (p.n_items + p.waves - 1) / p.waves;
-  p.grid = (unsigned)std::max<int64_t>(1, std::min(want, grid_cap(h, p.waves)));
-  // every wave of a prefix-shared launch has its own scratch: one block per CU (a block of
-  // fewer waves than the kernel is built for leaves room for more)
-  const int full = G.precision == ELOCAL_BF16 ? prefix_waves_bf16(G.hmax, p.cols) : kPrefixWavesF64;
-  if (p.prefix) p.grid = std::min(p.grid, (unsigned)h->cu_count * (unsigned)std::max(1, full / p.waves));
+  p.grid = p.prefix ? prefix_grid(h, G, p, p.n_items)
+                    : (unsigned)std::max<int64_t>(1, std::min(want, grid_cap(h, p.waves)));
   return p;
+}
+
+// What a plan takes of the workspace beside the arrays of the batch.
+struct EvalSizes {
+  size_t sums;      // partial sums (complex)
+  size_t lanes;     // doubles: the lanes' sums of parts of items
+  size_t scratch;   // floats: checkpoints
+};
+
+EvalSizes plan_sizes(const EvalPlan& p, int64_t B) {
+  return {(size_t)p.count * B << p.lgp, p.parts ? (size_t)p.n_items * 128 : 0,
+          p.prefix ? (size_t)p.grid * p.waves * p.px.stride : 0};
+}
+
+// An upper bound of plan_sizes that grows with the batch (a batch's own plan may take less than
+// a smaller one's, whose items it splits): room for it serves every smaller batch too.
+// `scratch_items`, if not null, gets the bound of the work items instead of the checkpoints.
+EvalSizes room_sizes(const elocal_ctx* h, const AnsatzGeom& G, int64_t B, int64_t list_len = -1,
+                     int64_t* scratch_items = nullptr) {
+  const EvalPlan p = plan_eval(h, G, B, list_len, 1.0, false);
+  EvalSizes z = plan_sizes(p, B);
+  int64_t items = p.n_items;
+  if (h->tune_groups <= 0) {
+    const uint64_t rows = (list_len > 0 ? (uint64_t)list_len : (uint64_t)h->sys.C) - 1, groups = (rows + 63) / 64;
+    if (p.prefix) {
+      const int64_t nseg = p.px.seg0[p.px.nblk], fine = B < kFineItems ? std::min((nseg * B) << kMaxLgParts, kFineItems) : kFineItems;
+      z.sums = std::max(z.sums, (size_t)fine);
+      items = std::max(items, fine);
+    } else if (p.ips <= kFewItems && G.precision == ELOCAL_FP64) {
+      z.sums = std::max<size_t>(z.sums, B < kFewItems ? std::min<size_t>(groups * B, 4 * kFewItems) : 4 * kFewItems);
+    } else if (p.ips <= kFewItems && groups > 1 && groups <= (uint64_t)kMaxLaneSums) {
+      z.lanes = (B < kMaxLaneSums ? std::min<size_t>(groups * B, kMaxLaneSums) : kMaxLaneSums) * 128;
+    }
+  }
+  if (scratch_items) {
+    *scratch_items = items;
+    z.scratch = 0;
+  } else if (p.prefix) {
+    z.scratch = (size_t)prefix_grid(h, G, p, items) * p.waves * p.px.stride;
+  }
+  return z;
 }
 
 // Launches the prefix-shared kernel of a width class.
@@ -760,8 +808,7 @@ struct EvalWs {
   size_t bytes;
 };
 
-EvalWs carve_eval(const elocal_ctx* h, const AnsatzGeom& G, const EvalPlan& p, int64_t B, void* ws,
-                  bool scratch = true) {
+EvalWs carve_eval(const elocal_ctx* h, const AnsatzGeom& G, bool prefix, const EvalSizes& z, int64_t B, void* ws) {
   Carve c(ws);
   EvalWs w{};
   const size_t nS = h->sys.nSa + h->sys.nSb;
@@ -777,46 +824,67 @@ EvalWs carve_eval(const elocal_ctx* h, const AnsatzGeom& G, const EvalPlan& p, i
     w.lpx64 = c.take<double>(std::max<size_t>((size_t)B * h->sys.n, 1));
   }
   w.zphi = c.take<double>(std::max<int64_t>(B, 1));
-  w.partial = c.take<double>(std::max<size_t>(((size_t)p.count * B << p.lgp) * 2, 1));
-  w.lanes = p.parts ? c.take<double>((size_t)p.n_items * 128) : nullptr;
+  w.partial = c.take<double>(std::max<size_t>(z.sums * 2, 1));
+  w.lanes = z.lanes ? c.take<double>(z.lanes) : nullptr;
   w.queue = nullptr;
   w.scratch = nullptr;
-  if (p.prefix) {
+  if (prefix) {
     w.queue = c.take<uint32_t>(1);
     if (G.precision == ELOCAL_FP64) {
       w.pfrag = c.take<char>(G.pwbytes);
       w.pbias = c.take<double>(G.pbbytes / 8);
     }
-    w.scratch = c.take<float>(scratch ? (size_t)p.grid * p.waves * p.px.stride : 0);
+    w.scratch = c.take<float>(z.scratch);
   }
   w.bytes = c.off;
   return w;
 }
 
+size_t eval_bytes(const elocal_ctx* h, const AnsatzGeom& G, const EvalPlan& p, int64_t B) {
+  return carve_eval(h, G, p.prefix, plan_sizes(p, B), B, nullptr).bytes;
+}
+
 // Fewer blocks where the checkpoints of the whole grid do not fit in `bytes` (results do not
 // depend on the grid).
 void shrink_grid(const elocal_ctx* h, const AnsatzGeom& G, int64_t B, size_t bytes, EvalPlan& p) {
-  if (!p.prefix || carve_eval(h, G, p, B, nullptr).bytes <= bytes) return;
-  const size_t fixed = carve_eval(h, G, p, B, nullptr, false).bytes;
+  if (!p.prefix || eval_bytes(h, G, p, B) <= bytes) return;
+  EvalSizes z = plan_sizes(p, B);
+  z.scratch = 0;
+  const size_t fixed = carve_eval(h, G, true, z, B, nullptr).bytes;
   const size_t block = (size_t)p.waves * p.px.stride * sizeof(float);
   const size_t fit = bytes > fixed + 256 ? (bytes - fixed - 256) / block : 0;
   p.grid = (unsigned)std::max<size_t>(1, std::min<size_t>(p.grid, fit));
 }
 
-// Bytes elocal_eval needs. A prefix-shared launch holds checkpoints per wave; a batch that fits
-// the scratch of elocal_eval_noalloc with 16 bytes per 512 list entries in their place needs no
-// more than that scratch (its launch then takes fewer blocks; with more room it takes them all).
-size_t eval_need(const elocal_ctx* h, const AnsatzGeom& G, int64_t B, const EvalPlan& p) {
-  const size_t full = carve_eval(h, G, p, B, nullptr).bytes;
-  if (!p.prefix || full <= kNoAllocScratchBytes) return full;
-  EvalPlan q = p;
-  q.prefix = false;
-  q.count = ((uint32_t)h->sys.C - 1 + 511) / 512;
-  q.lgp = 0;
-  if (carve_eval(h, G, q, B, nullptr).bytes > kNoAllocScratchBytes + (64 << 10)) return full;
-  q = p;
-  shrink_grid(h, G, B, kNoAllocScratchBytes, q);
-  return carve_eval(h, G, q, B, nullptr).bytes;
+// The plan of a launch within `bytes`: fewer blocks, then whole items, where there is no room for
+// all of it. The results are the same. False if it does not fit.
+bool fit_plan(const elocal_ctx* h, const AnsatzGeom& G, int64_t B, size_t bytes, EvalPlan& p, int64_t list_len = -1) {
+  for (const bool split : {true, false}) {
+    p = plan_eval(h, G, B, list_len, 1.0, split);
+    shrink_grid(h, G, B, bytes, p);
+    if (eval_bytes(h, G, p, B) <= bytes) return true;
+  }
+  return false;
+}
+
+// Workspace for all that an evaluation of up to B samples can use.
+size_t eval_room(const elocal_ctx* h, const AnsatzGeom& G, int64_t B) {
+  return carve_eval(h, G, G.prefix, room_sizes(h, G, B), B, nullptr).bytes;
+}
+
+// Bytes elocal_eval needs; never less than for a smaller batch. A prefix-shared launch holds
+// checkpoints per wave, a split one partial sums; a batch that fits the scratch of
+// elocal_eval_noalloc with 16 bytes per 512 list entries in their place needs no more than that
+// scratch (its launch then takes fewer blocks or whole items; with more room it takes them all).
+size_t eval_need(const elocal_ctx* h, const AnsatzGeom& G, int64_t B) {
+  const size_t room = eval_room(h, G, B);
+  if (room <= kNoAllocScratchBytes) return room;
+  EvalPlan p = plan_eval(h, G, B, -1, 1.0, false);
+  p.grid = 1;
+  EvalSizes z{(size_t)((h->sys.C - 1 + 511) / 512) * B, 0, 0};
+  const bool fits = eval_bytes(h, G, p, B) <= kNoAllocScratchBytes &&
+                    (!p.prefix || carve_eval(h, G, false, z, B, nullptr).bytes <= kNoAllocScratchBytes + (64 << 10));
+  return fits ? kNoAllocScratchBytes : room;
 }
 
 struct ConnectWs {
@@ -1030,7 +1098,7 @@ size_t elocal_workspace_bytes(elocal_t h, const elocal_ansatz* a, int64_t B, int
   AnsatzGeom G;
   if (make_eval_geom(h, a, G) != ELOCAL_OK) return 0;
   if (op == ELOCAL_OP_EVAL) {
-    return eval_need(h, G, B, plan_eval(h, G, B));
+    return eval_need(h, G, B);
   }
   if (op == ELOCAL_OP_GRAD) return carve_grad(h, G, B, nullptr, nullptr);
   fail(ELOCAL_E_INVALID, "unknown op %d", op);
@@ -1069,12 +1137,11 @@ elocal_status elocal_eval(elocal_t h, elocal_stream s, const elocal_ansatz* a, c
   if (B < 0) return fail(ELOCAL_E_INVALID, "B=%lld is negative", (long long)B);
   if (B == 0) return ELOCAL_OK;
   if (!a->theta || !x || !ws || !eloc) return fail(ELOCAL_E_INVALID, "null pointer argument");
-  EvalPlan p = plan_eval(h, G, B);
-  const size_t need = eval_need(h, G, B, p);
-  if (ws_bytes < need) return fail(ELOCAL_E_WORKSPACE, "workspace %zu bytes < %zu needed", ws_bytes, need);
-  shrink_grid(h, G, B, ws_bytes, p);
+  EvalPlan p;
+  if ((ws_bytes < eval_room(h, G, B) && ws_bytes < eval_need(h, G, B)) || !fit_plan(h, G, B, ws_bytes, p))
+    return fail(ELOCAL_E_WORKSPACE, "workspace %zu bytes < %zu needed", ws_bytes, eval_need(h, G, B));
   if (elocal_status st = check_device(h)) return st;
-  const EvalWs w = carve_eval(h, G, p, B, ws);
+  const EvalWs w = carve_eval(h, G, p.prefix, plan_sizes(p, B), B, ws);
   hipStream_t st = (hipStream_t)s;
   MadeDev M = G.md;
   M.wfrag = w.frag;
@@ -1140,7 +1207,7 @@ elocal_status elocal_eval_noalloc(elocal_t h, elocal_stream s, const elocal_ansa
   AnsatzGeom G;
   if (elocal_status e = make_eval_geom(h, a, G)) return e;
   if (B < 0) return fail(ELOCAL_E_INVALID, "B=%lld is negative", (long long)B);
-  const size_t need = eval_need(h, G, B, plan_eval(h, G, B));
+  const size_t need = eval_need(h, G, B);
   if (need > kNoAllocScratchBytes)
     return fail(ELOCAL_E_WORKSPACE,
                 "elocal_eval_noalloc needs %zu bytes of scratch for B=%lld, above its fixed %zu bytes "
@@ -1150,8 +1217,8 @@ elocal_status elocal_eval_noalloc(elocal_t h, elocal_stream s, const elocal_ansa
   // to eight parts (60 orbitals, 1024 samples: 395 ms, 242 with a workspace for every block of the
   // chip, 577 without sharing prefixes). A sample's energy does not depend on its batch.
   auto blocks = [&](int64_t b) {
-    EvalPlan p = plan_eval(h, G, b);
-    shrink_grid(h, G, b, kNoAllocScratchBytes, p);
+    EvalPlan p;
+    fit_plan(h, G, b, kNoAllocScratchBytes, p);
     return p.grid;
   };
   int64_t part = B;
@@ -1159,7 +1226,7 @@ elocal_status elocal_eval_noalloc(elocal_t h, elocal_stream s, const elocal_ansa
     unsigned best = blocks(B);
     for (int k = 2; k <= 8 && B / k >= 64; ++k) {
       const int64_t b = (B + k - 1) / k;
-      if (blocks(b) * 8u > best * 9u && eval_need(h, G, b, plan_eval(h, G, b)) <= kNoAllocScratchBytes) {
+      if (blocks(b) * 8u > best * 9u && eval_need(h, G, b) <= kNoAllocScratchBytes) {
         best = blocks(b);
         part = b;
       }
@@ -1227,6 +1294,7 @@ elocal_status plan_multi(int n_sys, const elocal_t* hs, const elocal_ansatz* con
     work[s] *= (double)B[s] * hs[s]->sys.C;
     if (M.G[s].prefix) pre_work += work[s];
   }
+  int64_t pre_room = 0;   // (bounds of the sizes, as in room_sizes)
   for (int s = 0; s < n_sys; ++s) {
     // the BF16 launch gives each system its share of the blocks
     const bool shared = M.G[s].prefix && M.G[s].precision == ELOCAL_BF16 && work[s] > 0.0;
@@ -1238,7 +1306,10 @@ elocal_status plan_multi(int n_sys, const elocal_t* hs, const elocal_ansatz* con
       M.hmax = std::max(M.hmax, M.G[s].hmax);
     }
     M.off[s] = off;
-    off = align256(off + carve_eval(hs[s], M.G[s], M.p[s], B[s], nullptr, false).bytes);
+    int64_t room = 0;
+    const EvalSizes z = room_sizes(hs[s], M.G[s], B[s], -1, &room);
+    if (M.p[s].prefix) pre_room += room;
+    off = align256(off + carve_eval(hs[s], M.G[s], M.p[s].prefix, z, B[s], nullptr).bytes);
     // cost of one item ~ rows x dense multiply-adds per row
     double per_row = 0.0;
     const MadeDev& md = M.G[s].md;
@@ -1278,9 +1349,11 @@ elocal_status plan_multi(int n_sys, const elocal_t* hs, const elocal_ansatz* con
     M.pre_ctx_off = q.lmode == 1 ? (uint32_t)(wmax + bmax) : q.lmode ? (uint32_t)wmax : 0u;
     M.pre_lut_off = M.pre_ctx_off + (uint32_t)(q.waves * kPrefixWaveBytes);
     q.lds = M.pre_lut_off + kXLutBytes;
-    const int64_t want = (items + q.waves - 1) / q.waves;
-    q.grid = (unsigned)std::max<int64_t>(1, std::min(want, grid_cap(hs[0], q.waves)));
-    q.grid = std::min(q.grid, (unsigned)hs[0]->cu_count * (unsigned)std::max(1, full / q.waves));
+    auto grid_of = [&](int64_t count) {
+      const int64_t want = (count + q.waves - 1) / q.waves, cap = (int64_t)hs[0]->cu_count * std::max(1, full / q.waves);
+      return (unsigned)std::max<int64_t>(1, std::min({want, cap, grid_cap(hs[0], q.waves)}));
+    };
+    q.grid = grid_of(items);
     // blocks start with the systems in turn, as many with each as its part of the work
     double done = 0.0;
     for (int i = 0; i < M.n_pre; ++i) {
@@ -1289,7 +1362,7 @@ elocal_status plan_multi(int n_sys, const elocal_t* hs, const elocal_ansatz* con
       done += work[s];
     }
     M.pre_off = off;
-    off = align256(off + (size_t)q.grid * q.waves * q.px.stride * sizeof(float));
+    off = align256(off + (size_t)grid_of(pre_room) * q.waves * q.px.stride * sizeof(float));
   }
   const int n_old = n_sys - M.n_pre;
   const int* old_order = M.order + M.n_pre;
@@ -1368,7 +1441,9 @@ elocal_status elocal_eval_multi(int n_sys, const elocal_t* hs, elocal_stream s, 
   for (int i = 0; i < n_sys; ++i) {
     const elocal_ctx* h = hs[i];
     const AnsatzGeom& G = M.G[i];
-    W[i] = carve_eval(h, G, M.p[i], B[i], base + M.off[i], false);
+    EvalSizes z = plan_sizes(M.p[i], B[i]);
+    z.scratch = 0;
+    W[i] = carve_eval(h, G, M.p[i].prefix, z, B[i], base + M.off[i]);
     if (B[i] == 0) continue;
     MadeDev md = G.md;
     md.wfrag = W[i].frag;
@@ -1580,8 +1655,7 @@ size_t elocal_pauli_workspace_bytes(elocal_t h, const elocal_ansatz* a, int64_t 
   if (h->pl_len <= 0) { fail(ELOCAL_E_CONFIG, "no Pauli strings: call elocal_pauli_build first"); return 0; }
   AnsatzGeom G;
   if (make_geom(h, a, G) != ELOCAL_OK) return 0;
-  const EvalPlan p = plan_eval(h, G, B, h->pl_len);
-  return carve_eval(h, G, p, B, nullptr).bytes;
+  return carve_eval(h, G, false, room_sizes(h, G, B, h->pl_len), B, nullptr).bytes;
 }
 
 elocal_status elocal_eval_pauli(elocal_t h, elocal_stream s, const elocal_ansatz* a, const uint64_t* x, int64_t B,
@@ -1594,11 +1668,11 @@ elocal_status elocal_eval_pauli(elocal_t h, elocal_stream s, const elocal_ansatz
   if (B < 0) return fail(ELOCAL_E_INVALID, "B=%lld is negative", (long long)B);
   if (B == 0) return ELOCAL_OK;
   if (!a->theta || !x || !ws || !eloc) return fail(ELOCAL_E_INVALID, "null pointer argument");
-  const EvalPlan p = plan_eval(h, G, B, h->pl_len);
-  const EvalWs need = carve_eval(h, G, p, B, nullptr);
-  if (ws_bytes < need.bytes) return fail(ELOCAL_E_WORKSPACE, "workspace %zu bytes < %zu needed", ws_bytes, need.bytes);
+  EvalPlan p;
+  if (!fit_plan(h, G, B, ws_bytes, p, h->pl_len))
+    return fail(ELOCAL_E_WORKSPACE, "workspace %zu bytes < %zu needed", ws_bytes, eval_bytes(h, G, p, B));
   if (elocal_status st = check_device(h)) return st;
-  const EvalWs w = carve_eval(h, G, p, B, ws);
+  const EvalWs w = carve_eval(h, G, false, plan_sizes(p, B), B, ws);
   hipStream_t st = (hipStream_t)s;
   MadeDev M = G.md;
   M.wfrag = w.frag;
@@ -2056,6 +2130,7 @@ int64_t elocal_launch_info(elocal_t h, const elocal_ansatz* a, int64_t B, int wh
   if (B < 0) { fail(ELOCAL_E_INVALID, "B=%lld is negative", (long long)B); return -1; }
   AnsatzGeom G;
   if (make_eval_geom(h, a, G) != ELOCAL_OK) return -1;
+  if (what == ELOCAL_INFO_WS_BYTES) return (int64_t)eval_room(h, G, B);
   const EvalPlan p = plan_eval(h, G, B);
   switch (what) {
     case ELOCAL_INFO_GRID: return p.grid;
@@ -2068,7 +2143,6 @@ int64_t elocal_launch_info(elocal_t h, const elocal_ansatz* a, int64_t B, int wh
     case ELOCAL_INFO_ITEMS: return p.n_items;
     case ELOCAL_INFO_LDS_BYTES: return (int64_t)p.lds;
     case ELOCAL_INFO_INPLACE: return p.inplace ? 1 : 0;
-    case ELOCAL_INFO_WS_BYTES: return (int64_t)carve_eval(h, G, p, B, nullptr).bytes;
   }
   fail(ELOCAL_E_INVALID, "unknown launch-info query %d", what);
   return -1;

@@ -198,9 +198,12 @@ class Hamiltonian:
         return int(n)
 
     def _workspace(self, op: int, B: int, ansatz: Optional[Ansatz] = None) -> Tuple[torch.Tensor, int]:
-        need = self.workspace_bytes(op, B, ansatz)
-        if op == OP_EVAL:   # room for every block of the launch
-            need = max(need, int(lib().elocal_launch_info(self._h, ansatz.ref(), int(B), INFO_WS_BYTES)))
+        if op == OP_EVAL:   # room for every block of the launch, never less than for a smaller batch
+            need = int(lib().elocal_launch_info(self._h, ansatz.ref(), int(B), INFO_WS_BYTES))
+            if need < 0:
+                raise ElocalError(1, lib().elocal_last_error().decode())
+        else:
+            need = self.workspace_bytes(op, B, ansatz)
         buf = self._ws.get(op)
         if buf is None or buf.numel() < need:
             buf = torch.empty(need, dtype=torch.uint8, device=self.device)

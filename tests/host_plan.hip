@@ -37,6 +37,23 @@ int host_parts(elocal_t h, const elocal_ansatz* a, int64_t B) {
   return make_eval_geom(h, a, G) == ELOCAL_OK ? (int)plan_eval(h, G, B).parts : -1;
 }
 
+// 1 if an evaluation (pauli > 0: of that many Pauli masks) finds a plan within `bytes`.
+int host_fits(elocal_t h, const elocal_ansatz* a, int64_t B, size_t bytes, int64_t pauli) {
+  AnsatzGeom G;
+  EvalPlan p;
+  if ((pauli ? make_geom(h, a, G) : make_eval_geom(h, a, G)) != ELOCAL_OK) return -1;
+  return fit_plan(h, G, B, bytes, p, pauli ? pauli : -1) && eval_bytes(h, G, p, B) <= bytes;
+}
+
+// Bytes that the plan of an evaluation takes with room for all of it.
+size_t host_plan_bytes(elocal_t h, const elocal_ansatz* a, int64_t B, int64_t pauli) {
+  AnsatzGeom G;
+  if ((pauli ? make_geom(h, a, G) : make_eval_geom(h, a, G)) != ELOCAL_OK) return 0;
+  return eval_bytes(h, G, plan_eval(h, G, B, pauli ? pauli : -1), B);
+}
+
+void host_set_pauli(elocal_t h, int64_t masks) { h->pl_len = masks; }
+
 int host_units_le(int n, int w, int D) { return units_le(n, w, D); }
 
 }  // extern "C"

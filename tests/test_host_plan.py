@@ -22,7 +22,8 @@ def plan(tmp_path_factory):
     L.host_free.argtypes = [ctypes.c_void_p]
     for f in ("host_items", "elocal_launch_info", "elocal_tune"):
         getattr(L, f).restype = ctypes.c_int64
-    L.elocal_workspace_bytes.restype = ctypes.c_size_t
+    for f in ("elocal_workspace_bytes", "elocal_workspace_bytes_multi", "elocal_pauli_workspace_bytes", "host_plan_bytes"):
+        getattr(L, f).restype = ctypes.c_size_t
     return L
 
 
@@ -97,3 +98,43 @@ def test_units_up_to_a_degree_in_closed_form(plan):
         for w in (32, 96, 256):
             for d in range(-1, n + 66):
                 assert plan.host_units_le(n, w, d) == sum(j % (n - 1) + 1 <= d for j in range(w))
+
+
+I64, SIZE = ctypes.c_int64, ctypes.c_size_t
+BATCHES = sorted({int(round(1.19 ** k)) for k in range(90)}
+                 | {b + d for b in (2048, 4096, 5461, 16384, 32768) for d in (-1, 0, 1)})
+SIZED = [
+    # n, n_alpha, n_beta, widths, precision
+    (4, 2, 2, (32,), elocal.BF16), (8, 4, 4, (32,), elocal.BF16), (8, 4, 4, (32,), elocal.FP64),
+    (9, 4, 5, (64, 64), elocal.BF16X3), (12, 6, 6, (128, 128), elocal.BF16), (12, 6, 6, (128, 128), elocal.FP64),
+    (16, 8, 8, (256,), elocal.BF16), (24, 12, 12, (128, 128), elocal.BF16), (24, 12, 12, (64, 64), elocal.FP64),
+    (60, 26, 26, (256,) * 3, elocal.BF16), (60, 26, 26, (256,) * 3, elocal.FP64), (60, 2, 2, (256,) * 3, elocal.BF16),
+]
+
+
+@pytest.mark.parametrize("tune", [0, 1, 4])
+@pytest.mark.parametrize("n,na,nb,widths,precision", SIZED)
+def test_workspace_of_a_batch_serves_every_smaller_one(plan, n, na, nb, widths, precision, tune):
+    """Sizes grow with the batch (those of the plans do not: a batch with few items has parts of
+    items, with sums of their own), a call runs with exactly what it asks for, and with the size
+    for all its blocks it takes all its blocks."""
+    h, a = ctypes.c_void_p(plan.host_handle(n, na, nb)), ansatz(widths, precision)
+    ref, last, last_room, last_pauli, last_multi = ctypes.byref(a), 0, 0, 0, 0
+    plan.elocal_tune(h, 1, I64(tune))
+    plan.host_set_pauli(h, I64(5000))
+    for b in BATCHES:
+        need = plan.elocal_workspace_bytes(h, ref, I64(b), 1)
+        room = plan.elocal_launch_info(h, ref, I64(b), 8)
+        assert need >= last and room >= last_room and 0 < need <= room, b
+        assert plan.host_fits(h, ref, I64(b), SIZE(need), I64(0)) == 1, b
+        assert plan.host_plan_bytes(h, ref, I64(b), I64(0)) <= room, b
+        last, last_room = need, room
+        if precision == elocal.BF16:
+            pauli = plan.elocal_pauli_workspace_bytes(h, ref, I64(b))
+            assert pauli >= last_pauli and plan.host_plan_bytes(h, ref, I64(b), I64(5000)) <= pauli, b
+            last_pauli = pauli
+        both, refs, sizes = (ctypes.c_void_p * 2)(h, h), (ctypes.c_void_p * 2)(*[ctypes.addressof(a)] * 2), (I64 * 2)(b, 100)
+        multi = plan.elocal_workspace_bytes_multi(2, both, refs, sizes)
+        assert multi >= last_multi, b
+        last_multi = multi
+    plan.host_free(h)

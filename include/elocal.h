@@ -179,8 +179,9 @@ elocal_status elocal_eval(elocal_t h, elocal_stream s, const elocal_ansatz* a,
  * array of ELOCAL_NOALLOC_SCRATCH_MIB MiB in device memory, one per GPU, that the library
  * holds from the first elocal_create on that GPU until the process ends. The call allocates
  * nothing. Fails with ELOCAL_E_WORKSPACE when the batch needs more scratch than that
- * (elocal_workspace_bytes(h, a, B, ELOCAL_OP_EVAL) tells how much), and runs a batch in parts
- * where that leaves room for more blocks' scratch. Every call on one GPU shares that GPU's array, and
+ * (elocal_workspace_bytes(h, a, B, ELOCAL_OP_EVAL) tells how much). As elocal_eval with a
+ * workspace below ELOCAL_INFO_WS_BYTES does, it runs a batch in parts where that leaves room for
+ * more blocks' scratch. Every call on one GPU shares that GPU's array, and
  * nothing in it needs to start at zero: calls that overlap on one GPU (on different
  * streams, or from different threads) race and must be serialised by the caller.
  */
@@ -351,7 +352,8 @@ elocal_status elocal_check_samples(elocal_t h, elocal_stream s, const uint64_t* 
  * generator kernel of elocal_connect, without its per-sample preparation).
  * When enabled, each elocal_eval or elocal_connect on the handle (and each
  * elocal_eval_multi whose first handle it is) records a pair of HIP events around that
- * kernel on the caller's stream (a ring of 1024 pairs, reused in order).
+ * kernel on the caller's stream (a ring of 1024 pairs, reused in order; a batch that is run in
+ * parts, see elocal_eval_noalloc, records a pair for each part).
  * elocal_kernel_timing waits for the recorded events, returns the summed milliseconds
  * and the number of launches recorded since the last reset (reset != 0 clears them).
  * These two calls mutate the handle: do not overlap them with other calls on it.

@@ -144,6 +144,7 @@ struct AnsatzGeom {
   int nterms = 2;      // fp16 terms per hidden activation (BF16 family)
   size_t wbytes = 0, bbytes = 0;
   bool prefix = false; // takes the prefix-shared evaluation (BF16: packing padded for it)
+  size_t plain_wbytes = 0;   // the weights as the plain kernels pack them
   MadeDev pm{};        // FP64: the network as that evaluation packs it
   size_t pwbytes = 0, pbbytes = 0;
   const MadeDev& prefix_md() const { return precision == ELOCAL_BF16 ? md : pm; }
@@ -293,6 +294,7 @@ struct EvalPlan {
   uint32_t rows_per_tile, tpi, ips;
   uint32_t count, fold;   // sums per sample (of 2^lgp partial sums each), and how many the
   int lgp;                // reduction folds to one before it adds those of a sample
+  uint32_t plain_count;   // sums per sample of the plain kernels' whole items
   uint32_t parts;         // BF16: parts of an item, each with its lanes' sums (0: items are whole)
   int64_t n_items;
   bool ldsw;
@@ -557,6 +559,7 @@ bool prefix_pays(const elocal_ctx* h, const AnsatzGeom& G) {
 // Geometry of elocal_eval and elocal_eval_multi (the Pauli route and the others: make_geom).
 elocal_status make_eval_geom(const elocal_ctx* h, const elocal_ansatz* a, AnsatzGeom& G) {
   if (elocal_status e = make_geom(h, a, G)) return e;
+  G.plain_wbytes = G.wbytes;
   G.prefix = prefix_net(G) && prefix_pays(h, G);
   if (G.prefix) {
     if (G.precision == ELOCAL_BF16) pad_prefix(G);
@@ -656,7 +659,7 @@ EvalPlan plan_eval(const elocal_ctx* h, const AnsatzGeom& G, int64_t B, int64_t 
   const uint64_t per_item = (uint64_t)p.rows_per_tile * p.tpi;
   p.ips = (uint32_t)((rows + per_item - 1) / per_item);
   p.n_items = (int64_t)p.ips * B;
-  p.count = p.ips;
+  p.count = p.plain_count = p.ips;
   p.fold = 1;
   p.lgp = 0;
   // A batch with few items has parts of items instead: an item's groups are run one after the
@@ -872,19 +875,51 @@ size_t eval_room(const elocal_ctx* h, const AnsatzGeom& G, int64_t B) {
   return carve_eval(h, G, G.prefix, room_sizes(h, G, B), B, nullptr).bytes;
 }
 
-// Bytes elocal_eval needs; never less than for a smaller batch. A prefix-shared launch holds
-// checkpoints per wave, a split one partial sums; a batch that fits the scratch of
-// elocal_eval_noalloc with 16 bytes per 512 list entries in their place needs no more than that
-// scratch (its launch then takes fewer blocks or whole items; with more room it takes them all).
+// Bytes elocal_eval needs; never less than for a smaller batch. A batch that fits the scratch of
+// elocal_eval_noalloc by what the plain kernels hold, one partial sum per item, needs no more
+// than that scratch, although the shared evaluation's checkpoints and the sums of parts of items
+// come on top: its launch then takes fewer blocks or whole items, or the batch is run in parts
+// (see eval_part). (60 orbitals: also one that does by 16 bytes per 512 list entries.)
 size_t eval_need(const elocal_ctx* h, const AnsatzGeom& G, int64_t B) {
-  const size_t room = eval_room(h, G, B);
-  if (room <= kNoAllocScratchBytes) return room;
+  const size_t room = eval_room(h, G, B), S = kNoAllocScratchBytes;
+  if (room <= S) return room;
   EvalPlan p = plan_eval(h, G, B, -1, 1.0, false);
   p.grid = 1;
-  EvalSizes z{(size_t)((h->sys.C - 1 + 511) / 512) * B, 0, 0};
-  const bool fits = eval_bytes(h, G, p, B) <= kNoAllocScratchBytes &&
-                    (!p.prefix || carve_eval(h, G, false, z, B, nullptr).bytes <= kNoAllocScratchBytes + (64 << 10));
-  return fits ? kNoAllocScratchBytes : room;
+  AnsatzGeom plain = G;
+  plain.wbytes = G.plain_wbytes;
+  const EvalSizes sums{(size_t)p.plain_count * B, 0, 0}, sums512{(size_t)((h->sys.C - 1 + 511) / 512) * B, 0, 0};
+  const bool fits = carve_eval(h, plain, false, sums, B, nullptr).bytes <= S ||
+                    (p.prefix && eval_bytes(h, G, p, B) <= S &&
+                     carve_eval(h, G, false, sums512, B, nullptr).bytes <= S + (64 << 10));
+  return fits ? S : room;
+}
+
+// Samples per launch of a batch within `bytes` (at least eval_need), with the plan of a launch.
+// Where the batch's arrays leave room for the checkpoints of few blocks only, it is run in up
+// to eight parts (60 orbitals, 1024 samples in the scratch of elocal_eval_noalloc: 395 ms, 242
+// with room for every block of the chip, 577 without sharing prefixes), and where they leave
+// none, in as many as it takes. A sample's energy does not depend on its batch.
+int64_t eval_part(const elocal_ctx* h, const AnsatzGeom& G, int64_t B, size_t bytes, EvalPlan& p) {
+  p = plan_eval(h, G, B);
+  if (eval_bytes(h, G, p, B) <= bytes) return B;
+  int64_t part = B;
+  unsigned best = fit_plan(h, G, B, bytes, p) ? p.grid : 0;
+  if (best > 0 && !p.prefix) return B;
+  EvalPlan q;
+  for (int k = 2; k <= 8 && B / k >= 64; ++k) {
+    const int64_t b = (B + k - 1) / k;
+    if (fit_plan(h, G, b, bytes, q) && q.grid * 8u > best * 9u) {
+      best = q.grid;
+      part = b;
+      p = q;
+    }
+  }
+  while (best == 0) {
+    if (part == 1) return 0;
+    part = (part + 1) / 2;
+    best = fit_plan(h, G, part, bytes, p) ? p.grid : 0;
+  }
+  return part;
 }
 
 struct ConnectWs {
@@ -1129,18 +1164,12 @@ elocal_status elocal_connect(elocal_t h, elocal_stream s, const uint64_t* x, int
   return ELOCAL_OK;
 }
 
-elocal_status elocal_eval(elocal_t h, elocal_stream s, const elocal_ansatz* a, const uint64_t* x, int64_t B,
-                          void* ws, size_t ws_bytes, double* eloc, double* logpsi) {
-  if (!h) return fail(ELOCAL_E_INVALID, "handle is null");
-  AnsatzGeom G;
-  if (elocal_status e = make_eval_geom(h, a, G)) return e;
-  if (B < 0) return fail(ELOCAL_E_INVALID, "B=%lld is negative", (long long)B);
-  if (B == 0) return ELOCAL_OK;
-  if (!a->theta || !x || !ws || !eloc) return fail(ELOCAL_E_INVALID, "null pointer argument");
-  EvalPlan p;
-  if ((ws_bytes < eval_room(h, G, B) && ws_bytes < eval_need(h, G, B)) || !fit_plan(h, G, B, ws_bytes, p))
-    return fail(ELOCAL_E_WORKSPACE, "workspace %zu bytes < %zu needed", ws_bytes, eval_need(h, G, B));
-  if (elocal_status st = check_device(h)) return st;
+}  // extern "C"
+
+namespace {
+// One launch sequence of elocal_eval: the whole batch, or a part of it.
+elocal_status eval_batch(elocal_t h, elocal_stream s, const elocal_ansatz* a, const AnsatzGeom& G, const EvalPlan& p,
+                         const uint64_t* x, int64_t B, void* ws, double* eloc, double* logpsi) {
   const EvalWs w = carve_eval(h, G, p.prefix, plan_sizes(p, B), B, ws);
   hipStream_t st = (hipStream_t)s;
   MadeDev M = G.md;
@@ -1190,6 +1219,32 @@ elocal_status elocal_eval(elocal_t h, elocal_stream s, const elocal_ansatz* a, c
   HIP_TRY(launch_reduce(w.ediag, w.partial, B, p.count, p.fold, p.lgp, eloc, st), "reduce launch");
   return ELOCAL_OK;
 }
+}  // namespace
+
+extern "C" {
+
+elocal_status elocal_eval(elocal_t h, elocal_stream s, const elocal_ansatz* a, const uint64_t* x, int64_t B,
+                          void* ws, size_t ws_bytes, double* eloc, double* logpsi) {
+  if (!h) return fail(ELOCAL_E_INVALID, "handle is null");
+  AnsatzGeom G;
+  if (elocal_status e = make_eval_geom(h, a, G)) return e;
+  if (B < 0) return fail(ELOCAL_E_INVALID, "B=%lld is negative", (long long)B);
+  if (B == 0) return ELOCAL_OK;
+  if (!a->theta || !x || !ws || !eloc) return fail(ELOCAL_E_INVALID, "null pointer argument");
+  EvalPlan p;
+  const int64_t part = ws_bytes < eval_room(h, G, B) && ws_bytes < eval_need(h, G, B) ? 0 : eval_part(h, G, B, ws_bytes, p);
+  if (part == 0)
+    return fail(ELOCAL_E_WORKSPACE, "workspace %zu bytes < %zu needed", ws_bytes, eval_need(h, G, B));
+  if (elocal_status st = check_device(h)) return st;
+  for (int64_t b0 = 0; b0 < B; b0 += part) {
+    const int64_t b = std::min(part, B - b0);
+    if (b < part && !fit_plan(h, G, b, ws_bytes, p)) return fail(ELOCAL_E_WORKSPACE, "workspace of %zu bytes", ws_bytes);
+    const elocal_status e = eval_batch(h, s, a, G, p, x + b0 * h->sys.W, b, ws, eloc + 2 * b0,
+                                       logpsi ? logpsi + 2 * b0 : nullptr);
+    if (e != ELOCAL_OK) return e;
+  }
+  return ELOCAL_OK;
+}
 
 elocal_status elocal_eval_noalloc(elocal_t h, elocal_stream s, const elocal_ansatz* a, const uint64_t* x,
                                   int64_t B, double* eloc, double* logpsi) {
@@ -1213,33 +1268,7 @@ elocal_status elocal_eval_noalloc(elocal_t h, elocal_stream s, const elocal_ansa
                 "elocal_eval_noalloc needs %zu bytes of scratch for B=%lld, above its fixed %zu bytes "
                 "(ELOCAL_NOALLOC_SCRATCH_MIB); use elocal_eval with a caller workspace or a smaller batch",
                 need, (long long)B, kNoAllocScratchBytes);
-  // Where a batch's arrays leave room for the checkpoints of few blocks only, it is run in up
-  // to eight parts (60 orbitals, 1024 samples: 395 ms, 242 with a workspace for every block of the
-  // chip, 577 without sharing prefixes). A sample's energy does not depend on its batch.
-  auto blocks = [&](int64_t b) {
-    EvalPlan p;
-    fit_plan(h, G, b, kNoAllocScratchBytes, p);
-    return p.grid;
-  };
-  int64_t part = B;
-  if (G.prefix && B > 0) {
-    unsigned best = blocks(B);
-    for (int k = 2; k <= 8 && B / k >= 64; ++k) {
-      const int64_t b = (B + k - 1) / k;
-      if (blocks(b) * 8u > best * 9u && eval_need(h, G, b) <= kNoAllocScratchBytes) {
-        best = blocks(b);
-        part = b;
-      }
-    }
-  }
-  if (part >= B) return elocal_eval(h, s, a, x, B, ws, kNoAllocScratchBytes, eloc, logpsi);
-  if (!x || !eloc) return fail(ELOCAL_E_INVALID, "null pointer argument");
-  for (int64_t b0 = 0; b0 < B; b0 += part) {
-    const elocal_status e = elocal_eval(h, s, a, x + b0 * h->sys.W, std::min(part, B - b0), ws, kNoAllocScratchBytes,
-                                        eloc + 2 * b0, logpsi ? logpsi + 2 * b0 : nullptr);
-    if (e != ELOCAL_OK) return e;
-  }
-  return ELOCAL_OK;
+  return elocal_eval(h, s, a, x, B, ws, kNoAllocScratchBytes, eloc, logpsi);
 }
 
 namespace {

@@ -37,6 +37,24 @@ int host_parts(elocal_t h, const elocal_ansatz* a, int64_t B) {
   return make_eval_geom(h, a, G) == ELOCAL_OK ? (int)plan_eval(h, G, B).parts : -1;
 }
 
+// Samples per launch of an evaluation within `bytes` (0: none), and the blocks of a launch.
+int64_t host_part(elocal_t h, const elocal_ansatz* a, int64_t B, size_t bytes, int64_t* grid) {
+  AnsatzGeom G;
+  EvalPlan p;
+  if (make_eval_geom(h, a, G) != ELOCAL_OK) return -1;
+  const int64_t part = eval_part(h, G, B, bytes, p);
+  *grid = part ? p.grid : 0;
+  return part && eval_bytes(h, G, p, part) > bytes ? -1 : part;
+}
+
+// Bytes of the plain kernels' layout with one partial sum per item, what an evaluation needed
+// before there were checkpoints or parts of items.
+size_t host_plain_bytes(elocal_t h, const elocal_ansatz* a, int64_t B) {
+  AnsatzGeom G;
+  if (make_geom(h, a, G) != ELOCAL_OK) return 0;
+  return eval_bytes(h, G, plan_eval(h, G, B, -1, 1.0, false), B);
+}
+
 // 1 if an evaluation (pauli > 0: of that many Pauli masks) finds a plan within `bytes`.
 int host_fits(elocal_t h, const elocal_ansatz* a, int64_t B, size_t bytes, int64_t pauli) {
   AnsatzGeom G;

@@ -20,9 +20,10 @@ def plan(tmp_path_factory):
     L = ctypes.CDLL(out + ".so")
     L.host_handle.restype = ctypes.c_void_p
     L.host_free.argtypes = [ctypes.c_void_p]
-    for f in ("host_items", "elocal_launch_info", "elocal_tune"):
+    for f in ("host_items", "host_part", "elocal_launch_info", "elocal_tune"):
         getattr(L, f).restype = ctypes.c_int64
-    for f in ("elocal_workspace_bytes", "elocal_workspace_bytes_multi", "elocal_pauli_workspace_bytes", "host_plan_bytes"):
+    for f in ("elocal_workspace_bytes", "elocal_workspace_bytes_multi", "elocal_pauli_workspace_bytes", "host_plan_bytes",
+              "host_plain_bytes"):
         getattr(L, f).restype = ctypes.c_size_t
     return L
 
@@ -126,7 +127,7 @@ def test_workspace_of_a_batch_serves_every_smaller_one(plan, n, na, nb, widths, 
         need = plan.elocal_workspace_bytes(h, ref, I64(b), 1)
         room = plan.elocal_launch_info(h, ref, I64(b), 8)
         assert need >= last and room >= last_room and 0 < need <= room, b
-        assert plan.host_fits(h, ref, I64(b), SIZE(need), I64(0)) == 1, b
+        assert plan.host_part(h, ref, I64(b), SIZE(need), (I64 * 1)()) >= 1, b
         assert plan.host_plan_bytes(h, ref, I64(b), I64(0)) <= room, b
         last, last_room = need, room
         if precision == elocal.BF16:
@@ -137,4 +138,24 @@ def test_workspace_of_a_batch_serves_every_smaller_one(plan, n, na, nb, widths, 
         multi = plan.elocal_workspace_bytes_multi(2, both, refs, sizes)
         assert multi >= last_multi, b
         last_multi = multi
+    plan.host_free(h)
+
+
+@pytest.mark.parametrize("n,na,nb,widths,precision", SIZED + [
+    (12, 6, 6, (256, 256), elocal.BF16), (10, 5, 5, (256,), elocal.BF16), (10, 5, 5, (64,), elocal.BF16),
+    (12, 6, 6, (64, 64), elocal.FP64), (40, 14, 14, (256,) * 3, elocal.BF16)])
+def test_allocation_free_calls_take_what_fits_without_checkpoints(plan, n, na, nb, widths, precision):
+    """elocal_eval_noalloc takes every batch whose arrays and whole items fit its scratch: the
+    checkpoints of the shared evaluation, or the sums of parts of items, do not shrink the limit."""
+    h, a = ctypes.c_void_p(plan.host_handle(n, na, nb)), ansatz(widths, precision)
+    ref, scratch = ctypes.byref(a), elocal.NOALLOC_SCRATCH_MIB << 20
+    lo, hi = 1, 1 << 24   # the largest such batch
+    while lo < hi:
+        mid = (lo + hi + 1) // 2
+        lo, hi = (mid, hi) if plan.host_plain_bytes(h, ref, I64(mid)) <= scratch else (lo, mid - 1)
+    for b in (lo, lo - 1, lo - 7, lo * 9 // 10, lo // 2):
+        grid = (I64 * 1)()
+        assert plan.elocal_workspace_bytes(h, ref, I64(b), 1) <= scratch, b
+        assert 1 <= plan.host_part(h, ref, I64(b), SIZE(scratch), grid) <= b and grid[0] >= 1
+    assert plan.elocal_workspace_bytes(h, ref, I64(2 * lo), 1) > scratch
     plan.host_free(h)

@@ -67,3 +67,17 @@ def test_64_orbitals_agree_across_precisions(widths):
         err = (ham.eval(elocal.Ansatz(widths, t, precision), x)[0] - whole).abs().max().item()
         print(f"{widths} precision={precision}: max|dE_loc|={err:.2e}", flush=True)
         assert err <= 1e-5
+
+
+@pytest.mark.parametrize("precision", [elocal.BF16, elocal.BF16X3, elocal.FP64])
+def test_64_orbitals_few_electrons_match_oracle(precision):
+    """2 + 3 electrons, 64x2, on samples of the ansatz itself, where the bound of 1e-5 Ha holds."""
+    n, na, nb, widths = 64, 2, 3, (64, 64)
+    p = synth.random_problem(n, na, nb, widths, seed=766, n_chol=4, decay=5.0, samples=1)
+    th_dev, th = theta_for(p.theta, precision)
+    x = ansatz_samples(p, 4, 767, th)
+    e = make_ham(p).eval(elocal.Ansatz(widths, th_dev, precision), words_to_dev(x))[0].cpu().numpy()
+    ref = oen.local_energies(p.h1e, p.eri, n, na, nb, widths, th, x)
+    err = np.max(np.abs(e[:, 0] + 1j * e[:, 1] - ref))
+    print(f"precision={precision}: max|dE_loc|={err:.2e}", flush=True)
+    assert err <= (1e-10 * np.max(np.abs(ref)) if precision == elocal.FP64 else 1e-5)

@@ -67,10 +67,12 @@ def test_few_electrons_run_every_entry(plan, n, na, nb, widths, precision):
 
 
 def test_systems_of_the_gpu_test_take_the_shared_evaluation(plan):
+    from tests.test_gpu_multi_prefix import BF16, FP64
     from tests.test_gpu_prefix_rule import SHAPES
     more = [(p, n, k, k, w, 1) for p in (elocal.BF16, elocal.FP64)
             for n, k, w in ((24, 12, (128, 128)), (24, 8, (128, 128)), (40, 14, (256,) * 3), (60, 26, (256,) * 3),
                             (60, 20, (64, 64)), (64, 21, (256,) * 3))]
+    more += [(p, *s, 1) for p, shapes in ((elocal.BF16, BF16[1:]), (elocal.FP64, FP64[1:])) for s in shapes]
     for precision, n, na, nb, widths, _ in SHAPES + more:
         h = ctypes.c_void_p(plan.host_handle(n, na, nb))
         a = ansatz(widths, precision)

@@ -2167,8 +2167,8 @@ int64_t elocal_launch_info(elocal_t h, const elocal_ansatz* a, int64_t B, int wh
     case ELOCAL_INFO_WAVES: return p.waves;
     case ELOCAL_INFO_COLS: return p.cols;
     case ELOCAL_INFO_MAX_WAVES:
-      if (p.prefix) return prefix_waves_bf16(G.hmax, p.cols);
-      return G.precision == ELOCAL_BF16 ? eval_waves_bf16(G.hmax, G.nterms, p.cols) : p.waves;
+      if (G.precision == ELOCAL_FP64) return p.waves;
+      return p.prefix ? prefix_waves_bf16(G.hmax, p.cols) : eval_waves_bf16(G.hmax, G.nterms, p.cols);
     case ELOCAL_INFO_ITEMS: return p.n_items;
     case ELOCAL_INFO_LDS_BYTES: return (int64_t)p.lds;
     case ELOCAL_INFO_INPLACE: return p.inplace ? 1 : 0;

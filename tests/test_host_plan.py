@@ -161,3 +161,10 @@ def test_allocation_free_calls_take_what_fits_without_checkpoints(plan, n, na, n
         assert 1 <= plan.host_part(h, ref, I64(b), SIZE(scratch), grid) <= b and grid[0] >= 1
     assert plan.elocal_workspace_bytes(h, ref, I64(2 * lo), 1) > scratch
     plan.host_free(h)
+
+
+@pytest.mark.parametrize("n,na,widths,waves", [(12, 6, (128, 128), 8), (60, 26, (256,) * 3, 8), (8, 4, (32,), 4)])
+def test_fp64_kernels_report_the_waves_they_are_built_for(plan, n, na, widths, waves):
+    h, a = ctypes.c_void_p(plan.host_handle(n, na, na)), ansatz(widths, elocal.FP64)
+    assert [plan.elocal_launch_info(h, ctypes.byref(a), I64(16), what) for what in (2, 4)] == [waves, waves]
+    plan.host_free(h)

@@ -20,8 +20,8 @@ work item in a fixed order, so results differ between shapes by rounding alone.
 
 Choices persist in a JSON file named by the environment variable ``ELOCAL_AUTOTUNE_CACHE``
 (no file when it is unset), keyed by device, orbitals, electrons, hidden widths,
-precision and batch size (for the several-system launch: the tuple of every system's key).
-A cached shape is applied without timing anything.
+precision and batch size (for the several-system launch: the tuple of every system's key), and by
+the meaning of a shape (SHAPE_VERSION). A cached shape is applied without timing anything.
 """
 from __future__ import annotations
 
@@ -34,6 +34,10 @@ import torch
 from . import elocal
 
 CACHE_ENV = "ELOCAL_AUTOTUNE_CACHE"
+# Raised when a shape's numbers mean something else or are for other kernels (2: `groups` of the
+# networks that take the shared evaluation are segments of parents, and any value set turns off
+# its split for small batches): shapes cached before are then timed again, not applied.
+SHAPE_VERSION = 2
 
 
 def _cu_count() -> int:
@@ -46,8 +50,9 @@ def _device_name() -> str:
 
 
 def problem_key(ham: elocal.Hamiltonian, ansatz: elocal.Ansatz, B: int) -> str:
-    """Cache key of one evaluation: device, n, electrons, widths, precision, batch size."""
-    return (f"{_device_name()}|n{ham.n}|a{ham.na}b{ham.nb}|w{'x'.join(map(str, ansatz.widths))}"
+    """Cache key of one evaluation: meaning of a shape, device, n, electrons, widths, precision,
+    batch size."""
+    return (f"v{SHAPE_VERSION}|{_device_name()}|n{ham.n}|a{ham.na}b{ham.nb}|w{'x'.join(map(str, ansatz.widths))}"
             f"|p{ansatz.precision}|B{int(B)}")
 
 

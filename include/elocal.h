@@ -284,14 +284,19 @@ elocal_status elocal_eval_pauli(elocal_t h, elocal_stream s, const elocal_ansatz
  * dim = C(n, n_alpha) C(n, n_beta) entries, at index r = rank_a * C(n, n_beta) + rank_b,
  * where the occupied spatial orbitals o_1 < ... < o_k of one spin have the
  * combinatorial-number-system rank sum_i C(o_i, i) (i = 1..k). All vectors are device
- * memory owned by the caller. H v is formed row by row from the same generator and
- * Slater--Condon values as elocal_eval (nothing per row is stored); every sum has a fixed
- * order, so results are bitwise repeatable.
+ * memory owned by the caller. H v is formed from the Slater--Condon values of elocal_eval, for
+ * small sectors and for few electrons in many orbitals row by row (nothing per row is stored),
+ * else as matrix products over the strings of either spin, from tables that every call builds in
+ * its workspace. Every sum has a fixed order, so results are bitwise repeatable; the two ways
+ * agree to rounding.
  *
  * elocal_sector_dim: dim, or -1 when it exceeds 2^31 - 1 (the sector calls then fail with
  *   ELOCAL_E_UNSUPPORTED).
  * elocal_sector_workspace_bytes: workspace of elocal_sector_apply (kpm = 0) or of
- *   elocal_kpm_moments (kpm = 1: three recursion vectors are included).
+ *   elocal_kpm_moments (kpm = 1: three recursion vectors are included). Where matrix products are
+ *   taken that is four vectors and tables of at most eight more vectors' size; with less, but at
+ *   least 128 KiB (and three vectors, each rounded up to 256 bytes, for moments), the calls
+ *   form H v row by row.
  * elocal_sector_basis: x [dim][W], the determinant of every index.
  * elocal_sector_apply: y = ch (H v) + cv v + cz z (z may be NULL; y must not alias v or z);
  *   if dots is not NULL, dots[0] = <y|y> and dots[1] = <y|v> (device).

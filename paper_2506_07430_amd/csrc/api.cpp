@@ -1960,11 +1960,12 @@ bool sector_product(const elocal_ctx* h, SectorTables& T) {
              (uint64_t)(T.npair + T.nda) * T.ldp * 8 <= 64ull * (uint64_t)dim;
 }
 
-SectorWs carve_sector(const elocal_ctx* h, bool kpm, void* ws) {
+// (lists: from row lists, also where the products would be taken)
+SectorWs carve_sector(const elocal_ctx* h, bool kpm, void* ws, bool lists = false) {
   SectorWs w{};
   const int64_t dim = std::max<int64_t>(h->sector_dim, 1);
   w.grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>((dim + 3) / 4, (int64_t)h->cu_count * 8));
-  w.product = sector_product(h, w.T);
+  w.product = !lists && sector_product(h, w.T);
   Carve c(ws);
   w.partial = c.take<double>(std::max<size_t>((size_t)w.grid * 4, w.product ? w.T.nda : 0) * 2);
   for (int k = 0; k < 3; ++k) w.vec[k] = kpm ? c.take<double>((size_t)dim) : nullptr;
@@ -2018,10 +2019,11 @@ elocal_status elocal_sector_apply(elocal_t h, elocal_stream s, double ch, const 
   if (elocal_status e = check_sector(h)) return e;
   if (!v || !y || !ws) return fail(ELOCAL_E_INVALID, "null pointer argument");
   if (y == v || (z && y == z)) return fail(ELOCAL_E_INVALID, "y must not alias v or z");
-  const SectorWs need = carve_sector(h, false, nullptr);
-  if (ws_bytes < need.bytes) return fail(ELOCAL_E_WORKSPACE, "workspace %zu bytes < %zu needed", ws_bytes, need.bytes);
+  const bool lists = ws_bytes < carve_sector(h, false, nullptr).bytes;   // no room for the products' tables
+  const size_t need = carve_sector(h, false, nullptr, lists).bytes;
+  if (ws_bytes < need) return fail(ELOCAL_E_WORKSPACE, "workspace %zu bytes < %zu needed", ws_bytes, need);
   if (elocal_status st = check_device(h)) return st;
-  const SectorWs w = carve_sector(h, false, ws);
+  const SectorWs w = carve_sector(h, false, ws, lists);
   hipStream_t st = (hipStream_t)s;
   if (w.product) {
     HIP_TRY(launch_sector_tables(h->sys, w.T, h->d_binom, st), "string tables launch");
@@ -2043,10 +2045,11 @@ elocal_status elocal_kpm_moments(elocal_t h, elocal_stream s, const double* alph
   if (!alpha || !ws || !moments) return fail(ELOCAL_E_INVALID, "null pointer argument");
   if (n_moments < 1) return fail(ELOCAL_E_INVALID, "n_moments=%lld < 1", (long long)n_moments);
   if (!(a > 0.0)) return fail(ELOCAL_E_INVALID, "scale a=%g must be positive", a);
-  const SectorWs need = carve_sector(h, true, nullptr);
-  if (ws_bytes < need.bytes) return fail(ELOCAL_E_WORKSPACE, "workspace %zu bytes < %zu needed", ws_bytes, need.bytes);
+  const bool lists = ws_bytes < carve_sector(h, true, nullptr).bytes;   // no room for the products' tables
+  const size_t need = carve_sector(h, true, nullptr, lists).bytes;
+  if (ws_bytes < need) return fail(ELOCAL_E_WORKSPACE, "workspace %zu bytes < %zu needed", ws_bytes, need);
   if (elocal_status st = check_device(h)) return st;
-  const SectorWs w = carve_sector(h, true, ws);
+  const SectorWs w = carve_sector(h, true, ws, lists);
   hipStream_t st = (hipStream_t)s;
   const int64_t dim = h->sector_dim, nw = w.product ? w.T.nda : (int64_t)w.grid * 4;
   HIP_TRY(launch_norm2(alpha, dim, w.partial, moments, st), "norm launch");   // Omega_0

@@ -374,7 +374,12 @@ class Hamiltonian:
         if need == 0:
             raise ElocalError(6, lib().elocal_last_error().decode())
         with torch.cuda.stream(stream):
-            return torch.empty(need, dtype=torch.uint8, device=self.device), need
+            try:
+                return torch.empty(need, dtype=torch.uint8, device=self.device), need
+            except torch.cuda.OutOfMemoryError:
+                # without room for the tables of the matrix products: what the row lists take
+                least = min(need, (128 << 10) + 256 + (3 * (8 * self.sector_dim + 256) if kpm else 0))
+                return torch.empty(least, dtype=torch.uint8, device=self.device), least
 
     def sector_basis(self, stream=None) -> torch.Tensor:
         """Every determinant of the sector, [dim, W] int64 (row r = index r)."""

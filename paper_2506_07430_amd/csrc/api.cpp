@@ -1768,6 +1768,20 @@ SampleWs carve_sample(const elocal_ctx* h, const AnsatzGeom& G, int64_t cap, voi
   return w;
 }
 
+// Most distinct prefixes of k orbitals that n_samples draws can have: occupations of k orbitals
+// that the remaining ones can complete.
+int64_t most_prefixes(const SysDev& S, int k, int64_t n_samples, int64_t max_unique) {
+  auto count = [&](int e) {
+    double c = 1.0, sum = 0.0;   // C(k, i)
+    for (int i = 0; i <= std::min(e, k); ++i) {
+      if (e - i <= S.n - k) sum += c;
+      c = c * (k - i) / (i + 1);
+    }
+    return sum;
+  };
+  return (int64_t)std::min({count(S.na) * count(S.nb), (double)n_samples, (double)max_unique});
+}
+
 }  // namespace
 
 size_t elocal_sample_workspace_bytes(elocal_t h, const elocal_ansatz* a, int64_t max_unique) {
@@ -1806,7 +1820,8 @@ elocal_status elocal_sample(elocal_t h, elocal_stream s, const elocal_ansatz* a,
     const bool last = k + 1 == n;
     HIP_TRY(launch_bas_step(h->sys, M, G.hmax, w.pre[cur], w.w[cur], &w.ucount[cur], &w.ucount[1 - cur], w.overflow,
                             k, seed, w.probs, w.counts, w.off, w.btot, last ? x_out : w.pre[1 - cur],
-                            last ? counts_out : w.w[1 - cur], max_unique, st),
+                            last ? counts_out : w.w[1 - cur], max_unique, most_prefixes(h->sys, k, n_samples, max_unique),
+                            st),
             "sampling step launch");
     cur = 1 - cur;
   }

@@ -775,9 +775,15 @@ static bool plan_bas_stage(const MadeDev& M, const HiddenCaps& caps, int k, BasS
   return wide <= 8 && lds <= 160 * 1024;
 }
 
+// Fewest prefixes for staged weights. A block stages up to 130 KB before its 192 rows, so with few
+// blocks that latency is all there is (all orbitals' steps, weights from cache, staged: 24
+// orbitals, 128x2, 3000 distinct prefixes 0.97, 1.13 ms, 20000 1.09, 1.18, 40000 1.33, 1.22; 40
+// orbitals 1.66, 1.99; 1.88, 2.06; 2.44, 2.20; narrower networks within 5% below it).
+constexpr int64_t kBasStageRows = 32768;
+
 template <int HMAX>
 static hipError_t bas_probs_h(const SysDev& S, const MadeDev& M, const uint64_t* pre, const int64_t* Ud, int64_t cap,
-                              int k, double* probs, hipStream_t st) {
+                              int64_t most, int k, double* probs, hipStream_t st) {
   const int64_t waves = (cap + 15) / 16;
   const unsigned blocks = (unsigned)((waves + 3) / 4);
   // orbital k's logits see the last hidden layer's units of degree <= k, and a hidden unit
@@ -793,7 +799,7 @@ static hipError_t bas_probs_h(const SysDev& S, const MadeDev& M, const uint64_t*
   BasStage G{};
   size_t lds = 0;
   int run = 0;
-  if (plan_bas_stage(M, caps, k, G, lds, run)) {
+  if (most >= kBasStageRows && plan_bas_stage(M, caps, k, G, lds, run)) {
     if (run == 32) return bas_probs_lds_h<32>(S, M, G, lds, pre, Ud, cap, k, probs, st);
     if (run == 64) return bas_probs_lds_h<64>(S, M, G, lds, pre, Ud, cap, k, probs, st);
     return bas_probs_lds_h<128>(S, M, G, lds, pre, Ud, cap, k, probs, st);
@@ -806,12 +812,12 @@ static hipError_t bas_probs_h(const SysDev& S, const MadeDev& M, const uint64_t*
 }
 
 hipError_t launch_bas_probs(const SysDev& S, const MadeDev& M, int hmax, const uint64_t* pre, const int64_t* Ud,
-                            int64_t cap, int k, double* probs, hipStream_t st) {
+                            int64_t cap, int64_t most, int k, double* probs, hipStream_t st) {
   switch (hmax) {
-    case 32: return bas_probs_h<32>(S, M, pre, Ud, cap, k, probs, st);
-    case 64: return bas_probs_h<64>(S, M, pre, Ud, cap, k, probs, st);
-    case 128: return bas_probs_h<128>(S, M, pre, Ud, cap, k, probs, st);
-    case 256: return bas_probs_h<256>(S, M, pre, Ud, cap, k, probs, st);
+    case 32: return bas_probs_h<32>(S, M, pre, Ud, cap, most, k, probs, st);
+    case 64: return bas_probs_h<64>(S, M, pre, Ud, cap, most, k, probs, st);
+    case 128: return bas_probs_h<128>(S, M, pre, Ud, cap, most, k, probs, st);
+    case 256: return bas_probs_h<256>(S, M, pre, Ud, cap, most, k, probs, st);
   }
   return hipErrorInvalidValue;
 }

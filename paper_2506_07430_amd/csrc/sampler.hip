@@ -274,9 +274,9 @@ hipError_t launch_bas_root(uint64_t* pre, int64_t* w, int W, int64_t n_samples, 
 hipError_t launch_bas_step(const SysDev& S, const MadeDev& M, int hmax, const uint64_t* pre, const int64_t* w,
                            const int64_t* ucur, int64_t* unext, int64_t* overflow, int k, uint64_t seed, double* probs,
                            int64_t* counts, int64_t* off, int64_t* btot, uint64_t* child, int64_t* cw, int64_t cap,
-                           hipStream_t st) {
+                           int64_t most, hipStream_t st) {
   if (cap <= 0) return hipErrorInvalidValue;
-  hipError_t e = launch_bas_probs(S, M, hmax, pre, ucur, cap, k, probs, st);
+  hipError_t e = launch_bas_probs(S, M, hmax, pre, ucur, cap, most, k, probs, st);
   if (e != hipSuccess) return e;
   const int64_t nblk = (cap + 1023) / 1024;
   const unsigned tb = (unsigned)((cap + 255) / 256);

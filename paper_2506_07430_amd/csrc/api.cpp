@@ -1325,8 +1325,8 @@ elocal_status plan_multi(int n_sys, const elocal_t* hs, const elocal_ansatz* con
   }
   int64_t pre_room = 0;   // (bounds of the sizes, as in room_sizes)
   for (int s = 0; s < n_sys; ++s) {
-    // the BF16 launch gives each system its share of the blocks
-    const bool shared = M.G[s].prefix && M.G[s].precision == ELOCAL_BF16 && work[s] > 0.0;
+    // the shared launch gives each system its share of the blocks
+    const bool shared = M.G[s].prefix && work[s] > 0.0;
     M.p[s] = plan_eval(hs[s], M.G[s], B[s], -1, shared ? work[s] / pre_work : 1.0);
     if (M.p[s].prefix) {
       ++M.n_pre;

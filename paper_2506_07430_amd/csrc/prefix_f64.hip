@@ -318,7 +318,10 @@ __global__ void __launch_bounds__(64 * kPrefixWavesF64, 1)
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int lane = threadIdx.x & 63, wid = sgpr(threadIdx.x >> 6);
   PrefixWave& pw = ((PrefixWave*)smem)[wid];
-  for (int s = 0; s < n_sys; ++s) {
+  // (a wave starts with its block's system and goes on to the others, see k_prefix_multi_bf16)
+  int s = 0;
+  while (s + 1 < n_sys && blockIdx.x >= args[s + 1].px.block0) ++s;
+  for (int i = 0; i < n_sys; ++i, s = s + 1 < n_sys ? s + 1 : 0) {
     const PrefixArgs& P = args[s];
     const NetF64::Sources src = wave_sources_f64(P, wid);
     PrefixSample<2> st;

@@ -1953,9 +1953,10 @@ struct SectorWs {
 // take over where these would do much more work (few electrons in many orbitals: the products
 // run over all pairs of orbitals) or need tables larger than the vectors, where one string's
 // row of products does not fit in LDS, and for sectors of few entries, whose time is launches
-// (per product, lists -> matrices: 4900 rows of 361 24 -> 35 us, 4356 of 531 31 -> 51 us,
-// 15876 of 621 72 -> 38 us, 853776 of 1819 8.0 -> 0.42 ms).
-constexpr int64_t kProductMinEntries = 5000000;
+// (a call, lists -> matrices: 4900 rows of 361 22 -> 33 us, 11340 of 570 (6.5e6) 53 -> 60 and 56
+// -> 68, 15876 of 561 (8.9e6) 68 -> 55; 853776 of 1819 8.0 -> 0.46
+// ms).
+constexpr int64_t kProductMinEntries = 7000000;
 bool sector_product(const elocal_ctx* h, SectorTables& T) {
   const SysDev& S = h->sys;
   const int64_t dim = h->sector_dim;

@@ -72,6 +72,19 @@ size_t host_plan_bytes(elocal_t h, const elocal_ansatz* a, int64_t B, int64_t pa
 
 void host_set_pauli(elocal_t h, int64_t masks) { h->pl_len = masks; }
 
+// 1 if H on sector vectors is formed by matrix products.
+int host_sector_product(elocal_t h) {
+  auto choose = [](int n, int k) {
+    double c = 1.0;
+    for (int i = 0; i < k; ++i) c = c * (n - i) / (i + 1);
+    return (int64_t)(c + 0.5);
+  };
+  SectorTables T;
+  h->sector_nb = (uint32_t)choose(h->sys.n, h->sys.nb);
+  h->sector_dim = choose(h->sys.n, h->sys.na) * h->sector_nb;
+  return sector_product(h, T);
+}
+
 int host_units_le(int n, int w, int D) { return units_le(n, w, D); }
 
 }  // extern "C"

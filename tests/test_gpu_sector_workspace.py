@@ -47,3 +47,18 @@ def test_row_lists_where_the_tables_do_not_fit(monkeypatch):
                                      ws.data_ptr(), nbytes, None)
 
     assert status(128 << 10) == 0 and status(1024) == 3
+
+
+@pytest.mark.parametrize("n,na,nb", [(11, 9, 5), (11, 5, 2), (11, 2, 5)])
+def test_products_of_nearly_full_and_nearly_empty_shells(n, na, nb):
+    """The shapes of few strings of one spin at the sizes from which products are taken, against row
+    lists (1e-12 of the largest entry: sums of about 1e3 products in two orders)."""
+    ham = make_ham(synth.random_problem(n, na, nb, (32,), seed=880 + na, n_chol=4, samples=1))
+    v = torch.randn(ham.sector_dim, dtype=torch.float64, device="cuda", generator=torch.Generator("cuda").manual_seed(2))
+    L = elocal.lib()
+    assert int(L.elocal_sector_workspace_bytes(ham._h, 0)) > 4 * 8 * ham.sector_dim
+    want = ham.sector_apply(v)
+    ws, y = torch.empty(128 << 10, dtype=torch.uint8, device="cuda"), torch.empty_like(v)
+    assert L.elocal_sector_apply(ham._h, elocal._stream(None), 1.0, v.data_ptr(), 0.0, None, 0.0, y.data_ptr(),
+                                 ws.data_ptr(), ws.numel(), None) == 0
+    assert (y - want).abs().max().item() <= 1e-12 * want.abs().max().item()

@@ -168,3 +168,11 @@ def test_fp64_kernels_report_the_waves_they_are_built_for(plan, n, na, widths, w
     h, a = ctypes.c_void_p(plan.host_handle(n, na, na)), ansatz(widths, elocal.FP64)
     assert [plan.elocal_launch_info(h, ctypes.byref(a), I64(16), what) for what in (2, 4)] == [waves, waves]
     plan.host_free(h)
+
+
+@pytest.mark.parametrize("n,na,nb,product", [(10, 8, 5, 0), (10, 5, 2, 0), (8, 4, 4, 0), (12, 1, 6, 0), (9, 4, 4, 1),
+                                             (12, 6, 6, 1), (14, 7, 3, 1), (20, 3, 2, 1), (40, 2, 1, 0)])
+def test_sectors_of_few_entries_keep_row_lists(plan, n, na, nb, product):
+    h = ctypes.c_void_p(plan.host_handle(n, na, nb))
+    assert plan.host_sector_product(h) == product
+    plan.host_free(h)

@@ -7,6 +7,7 @@ cannot be loaded, every call raises: there is no CPU fallback.
 """
 from __future__ import annotations
 
+import contextlib
 import ctypes
 import os
 from typing import Optional, Sequence, Tuple
@@ -373,7 +374,7 @@ class Hamiltonian:
         need = int(lib().elocal_sector_workspace_bytes(self._h, int(kpm)))
         if need == 0:
             raise ElocalError(6, lib().elocal_last_error().decode())
-        with torch.cuda.stream(stream):
+        with contextlib.nullcontext() if stream is None else torch.cuda.stream(stream):
             try:
                 return torch.empty(need, dtype=torch.uint8, device=self.device), need
             except torch.cuda.OutOfMemoryError:

@@ -24,6 +24,7 @@ import argparse
 import hashlib
 import json
 import os
+import re
 import sys
 import time
 
@@ -36,14 +37,22 @@ METRIC = "local energies/s + H_xx' elems/s at 1 GPU, BF16+FP64 vs all-FP64, |dE|
 PEAK_16BIT_TFLOPS = 2500.0    # MI355X dense bf16/fp16 matrix peak
 PEAK_F64_TFLOPS = 78.6        # MI355X FP64 matrix/vector peak
 PEAK_HBM_GBS = 8000.0         # MI355X HBM3E
-KERNEL_SRC = os.path.join(ROOT, "paper_2506_07430_amd", "csrc", "prefix_bf16.hpp")
-CONNECT_SRC = os.path.join(ROOT, "paper_2506_07430_amd", "csrc", "hamiltonian.hip")
+CSRC = os.path.join(ROOT, "paper_2506_07430_amd", "csrc")
+# the kernel's source and, for the fused kernel, the file that plans its launch (sizes of tiles,
+# checkpoints and work items); what they include is added
+KERNEL_SRC = ("prefix_bf16.hpp", "api.cpp")
+CONNECT_SRC = ("hamiltonian.hip",)
 GOLDEN = os.path.join(ROOT, "tests", "golden", "full_size_eloc.json")
-# HBM bytes per launch from rocprofv3 FETCH_SIZE / WRITE_SIZE runs, kept with the source
-# hash they were taken on (a changed kernel makes them stale: traffic is then null)
+# HBM bytes and instructions per launch from rocprofv3 runs, kept with the hash of all the sources
+# they depend on (a change to any makes them stale: traffic and executed products are then null)
 COUNTERS = {1: os.path.join(ROOT, "profiles", "prefix_bf16_n24_counters.json"),
             4: os.path.join(ROOT, "profiles", "prefix_bf16_n60_counters.json")}
 CONNECT_COUNTERS = os.path.join(ROOT, "profiles", "connect_n24_counters.json")
+
+
+# What "achieved" and "frac" of the evaluations count.
+UNSHARED = ("achieved and frac count every list entry's whole unmasked network once; what entries share is executed "
+            "once, so they are a rate of results, not a share of the peak (executed counts instructions)")
 
 
 def unmasked_weights(n: int, widths) -> int:
@@ -66,19 +75,37 @@ def dense_weights(n: int, widths) -> int:
     return sum(dims[i] * dims[i + 1] for i in range(len(dims) - 1)) + widths[-1]
 
 
-def file_hash(path: str) -> str:
-    with open(path, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()[:16]
+def source_files(names, csrc: str = CSRC):
+    """The given sources and what they include from the same directory, sorted."""
+    todo, seen = list(names), set()
+    while todo:
+        name = todo.pop()
+        if name in seen:
+            continue
+        seen.add(name)
+        with open(os.path.join(csrc, name)) as f:
+            todo += [m for m in re.findall(r'^\s*#include "([^"/]+)"', f.read(), re.M)
+                     if os.path.exists(os.path.join(csrc, m))]
+    return sorted(seen)
 
 
-def stored_traffic(path: str, src: str, samples: int):
+def source_hash(names, csrc: str = CSRC) -> str:
+    """Hash of the sources' code: comments and layout do not count."""
+    h = hashlib.sha256()
+    for name in source_files(names, csrc):
+        with open(os.path.join(csrc, name)) as f:
+            code = re.sub(r"/\*.*?\*/|//[^\n]*", " ", f.read(), flags=re.S)
+        h.update((name + "\n" + " ".join(code.split()) + "\n").encode())
+    return h.hexdigest()[:16]
+
+
+def stored_counters(path: str, src, samples: int):
+    """What a counter run stored, if it was taken on the present sources and batch, else {}."""
     if not os.path.exists(path):
-        return None
+        return {}
     with open(path) as f:
         cnt = json.load(f)
-    if cnt.get("kernel_src_sha256_16") == file_hash(src) and cnt.get("samples") == samples:
-        return cnt.get("hbm_bytes_per_launch")
-    return None
+    return cnt if cnt.get("source_sha256_16") == source_hash(src) and cnt.get("samples") == samples else {}
 
 
 def describe(wl, p, C):
@@ -212,12 +239,14 @@ def main():
         s = p.system
         uw, dw = unmasked_weights(s.n, s.widths), dense_weights(s.n, s.widths)
         rows = samples * (C - 1)
-        # the count of an evaluation that runs every entry's whole network: units that entries
-        # share are run once, so this can exceed what the matrix cores executed
         achieved = rows * 2.0 * uw / (kernel_ms * 1e-3) / 1e12
-        traffic = stored_traffic(COUNTERS[cfg], KERNEL_SRC, samples) if cfg in COUNTERS else None
+        cnt = stored_counters(COUNTERS[cfg], KERNEL_SRC, samples) if cfg in COUNTERS else {}
+        # products that the matrix cores executed (16 x 16 x 32 each, both fp16 terms, padding)
+        mfma = cnt.get("counters", {}).get("SQ_INSTS_MFMA")
+        executed = mfma * 2.0 * 16 * 16 * 32 / (kernel_ms * 1e-3) / 1e12 if mfma else None
         return {"bound": "mfma", "achieved": achieved, "peak": PEAK_16BIT_TFLOPS, "unit": "TFLOP/s",
-                "frac": achieved / PEAK_16BIT_TFLOPS, "traffic": traffic,
+                "frac": achieved / PEAK_16BIT_TFLOPS, "counts": UNSHARED, "traffic": cnt.get("hbm_bytes_per_launch"),
+                "executed": executed, "executed_frac": executed / PEAK_16BIT_TFLOPS if executed else None,
                 "kernel": "k_prefix_bf16", "kernel_ms": kernel_ms, "launches_timed": launches,
                 "alg_flops_per_row": 2 * uw, "rows_per_launch": rows, "dense_flops_per_row": 2 * dw,
                 "dense_frac": rows * 2.0 * dw / (kernel_ms * 1e-3) / 1e12 / PEAK_16BIT_TFLOPS}
@@ -270,7 +299,7 @@ def main():
                        "h_elems_per_s": S64 * C / sec64, "eval_kernel_ms": kern64_ms,
                        "eval_kernel_tflops_alg": S64 * (C - 1) * 2 * uw / (kern64_ms * 1e-3) / 1e12,
                        "peak_tflops": PEAK_F64_TFLOPS,
-                       "frac": S64 * (C - 1) * 2 * uw / (kern64_ms * 1e-3) / 1e12 / PEAK_F64_TFLOPS,
+                       "frac": S64 * (C - 1) * 2 * uw / (kern64_ms * 1e-3) / 1e12 / PEAK_F64_TFLOPS, "counts": UNSHARED,
                        "bf16_over_fp64_speed": (B / sec) / (S64 / sec64),
                        "note": "first samples of the headline batch, eval + stats + grad, eager"}
         eloc64 = st64.eloc.cpu().numpy().copy()
@@ -348,13 +377,14 @@ def main():
                     for q, h in zip(probs, hams))
         pairs = sum(q.x.shape[0] * h.C for q, h in zip(probs, hams))
         nsamp = sum(q.x.shape[0] for q in probs)
-        out["c2"] = {"workload": "eight systems n=12..40 step 4, half filling, 128x2, one persistent launch",
+        out["c2"] = {"workload": "eight systems n=12..40 step 4, half filling, 128x2, one call",
                      "samples": [q.x.shape[0] for q in probs], "connected": [h.C for h in hams],
                      "ms_per_call": msec * 1e3, "local_energies_per_s": nsamp / msec, "h_elems_per_s": pairs / msec,
                      "roofline": {"bound": "mfma", "achieved": flops / (mkms * 1e-3) / 1e12,
                                   "peak": PEAK_16BIT_TFLOPS, "unit": "TFLOP/s",
-                                  "frac": flops / (mkms * 1e-3) / 1e12 / PEAK_16BIT_TFLOPS, "traffic": None,
-                                  "kernel": "k_prefix_multi_bf16", "kernel_ms": mkms, "rows_per_launch": rows},
+                                  "frac": flops / (mkms * 1e-3) / 1e12 / PEAK_16BIT_TFLOPS, "counts": UNSHARED,
+                                  "traffic": None, "kernel": "k_prefix_multi_bf16 and k_eval_multi_bf16",
+                                  "kernel_ms": mkms, "rows_per_launch": rows},
                      "launch_shape": (min(mt, key=lambda r: r["ms"]) if mt else None),
                      "golden_bf16": [golden_errors(2, q, o.cpu().numpy(), system=si)
                                      for si, (q, o) in enumerate(zip(probs, outs))]}
@@ -390,7 +420,7 @@ def main():
                           "pairs_per_s": cB * cC / (gms * 1e-3), "bytes_per_pair": per_pair,
                           "achieved": alg / (gms * 1e-3) / 1e9, "peak": PEAK_HBM_GBS, "unit": "GB/s",
                           "frac": alg / (gms * 1e-3) / 1e9 / PEAK_HBM_GBS,
-                          "traffic": stored_traffic(CONNECT_COUNTERS, CONNECT_SRC, cB),
+                          "traffic": stored_counters(CONNECT_COUNTERS, CONNECT_SRC, cB).get("hbm_bytes_per_launch"),
                           "note": "kernel_ms: library HIP events around the generator kernel; call_ms: the "
                                   "whole call (per-sample preparation + generator)"}
         del outs

@@ -13,7 +13,7 @@ Cholesky vectors, 1024 unique samples, 1,147,875 connected determinants each, an
 cores (FP32 accumulation) and FP64 matrix elements, ratios and sums.
 
 Further legs: the 24-orbital workload (16384 samples, Zipf(1.5) weights), the eight
-systems of 12..40 orbitals in one persistent launch, the 40-orbital forward+gradient
+systems of 12..40 orbitals in one call, the 40-orbital forward+gradient
 workload, the all-FP64 path, the materialising generator, the sampler, the Pauli-string
 route, the deduplicated evaluation, the KPM moments, and the CPU oracle on a bounded
 sample. Prints one JSON line.

@@ -190,17 +190,18 @@ elocal_status elocal_eval_noalloc(elocal_t h, elocal_stream s, const elocal_ansa
                                   const uint64_t* x, int64_t B, double* eloc, double* logpsi);
 
 /*
- * Local energies of several systems in one persistent launch (Methods: the batch of a
- * training step split over independent summands; here systems of different size whose
- * connected lists differ in length by orders of magnitude).
+ * Local energies of several systems in one call (Methods: the batch of a training step split
+ * over independent summands; here systems of different size whose connected lists differ in
+ * length by orders of magnitude).
  * n_sys in [1, ELOCAL_MAX_SYSTEMS]; hs, a, x, B, eloc, logpsi are HOST arrays of
  * n_sys entries (the pointers they hold are device memory, as in elocal_eval; logpsi
  * itself or any of its entries may be NULL). Every handle must belong to the current
  * device and every ansatz must have the same precision. System s gets exactly the
  * eloc[s] (and logpsi[s]) that elocal_eval(hs[s], ..., a[s], x[s], B[s]) gives: the
  * per-sample work and its summation order are the same; only the scheduling differs
- * (the fused kernel runs once over the work items of all systems, ordered by cost per
- * item, so no system leaves a tail of idle compute units behind it).
+ * (one persistent launch over the systems whose lists share prefixes, each block starting with
+ * the system that its share of the work gives it, and one over the work items of the others,
+ * ordered by cost per item, so no system leaves a tail of idle compute units behind it).
  * ws needs elocal_workspace_bytes_multi(...) bytes.
  */
 enum { ELOCAL_MAX_SYSTEMS = 16 };

@@ -124,8 +124,11 @@ constexpr size_t block_lds_bf16(int waves) { return (size_t)waves * kWaveCtxByte
 constexpr bool inplace_kernel_bf16(int hmax, int nterms) { return hmax >= kLdsPartialWidth && nterms == 2; }
 // Prefix-shared evaluation (two-term BF16 mode, hidden layers of one width >= 64). Waves per
 // block: 16 (four per SIMD, 128 registers each) with one 16-row tile per network pass up to
-// width 128, else 8. lmode: where weights are read from (0: global memory, 1: the whole
-// network in LDS, 2: the last classes, PrefixTop, in LDS).
+// width 128, else 8. Two tiles per pass (half the waves) are taken only when tuned for; us with
+// one and with two: 22 orbitals, 64x2, 512 samples 860, 943; 24 orbitals, 128x2, 1024 samples
+// 2670, 2980; 40 orbitals, 64x1, 64 samples 1175, 1330; 60 orbitals, 128x2, 16 samples 2530, 2350.
+// lmode: where weights are read from (0: global memory, 1: the whole network in LDS, 2: the last
+// classes, PrefixTop, in LDS).
 constexpr int prefix_waves_bf16(int hmax, int cols) { return hmax <= 128 && cols == 1 ? 16 : 8; }
 constexpr int prefix_lds_blocks(int hmax) { return hmax >= 256 ? 5 : hmax >= 128 ? 3 : 1; }
 constexpr size_t kPrefixWaveBytes = 3840;   // LDS state of one wave (PrefixWave)

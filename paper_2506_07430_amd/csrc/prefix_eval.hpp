@@ -3,11 +3,11 @@
 // rows of a tile (rows), the log-softmax of one orbital (step), the ratio of one entry, and
 // where a wave reads from (Sources).
 //
-// Measured against the plain kernels (k_eval_bf16, k_eval_f64), whole calls on one MI355X:
-//   60 orbitals, 256x3, 128 samples   BF16 73.4 -> 30.8 ms   17 samples  FP64 119 -> 29.6 ms
-//   40 orbitals, 256x3, 512 samples   BF16 44.6 -> 22.6 ms
-//   24 orbitals, 128x2, 4096 samples  BF16 14.7 -> 10.4 ms   1024 samples FP64 38.2 -> 13.3 ms
-//   12 orbitals, 128x2, 37 samples    BF16 0.244 -> 0.122 ms
+// Measured against kernels that run every entry's whole network (k_eval_bf16, k_eval_f64), whole
+// calls on one MI355X (where it is taken: prefix_pays in api.cpp):
+//   60 orbitals, 256x3, 128 samples   BF16 72.9 -> 30.5 ms   17 samples  FP64 119 -> 29.0 ms
+//   40 orbitals, 256x3, 512 samples   BF16 43.7 -> 22.5 ms (with the gradient)
+//   24 orbitals, 128x2, 4096 samples  BF16 14.7 -> 10.0 ms (with the gradient)   1024 samples FP64 38.1 -> 13.4 ms
 // At 60 orbitals 8.8 of 29.75 matrix instructions per entry are left and two waves per SIMD
 // wait 31% of their cycles; at 24 orbitals vector issue (33 instructions per entry, 2.4 of
 // them products) bounds the kernel, whose checkpoints (18 KB a wave) stream through the

@@ -439,7 +439,7 @@ def kpm_line_shape(moments: torch.Tensor, w: torch.Tensor, stream=None) -> torch
 
 
 class MultiEval:
-    """Local energies of several systems in one persistent launch (elocal_eval_multi).
+    """Local energies of several systems in one call (elocal_eval_multi).
 
     Holds the workspace between calls; every system keeps its own Hamiltonian handle,
     ansatz and samples.

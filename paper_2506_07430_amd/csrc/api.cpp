@@ -568,10 +568,24 @@ elocal_status make_eval_geom(const elocal_ctx* h, const elocal_ansatz* a, Ansatz
   return ELOCAL_OK;
 }
 
+// Parts of segments in entries: a part of L entries takes the launch its own time, and each part
+// runs its segment's parents again, E / L times their time over all waves. The sum is least at
+// L = sqrt(parents' time in entries * E / waves), which is taken where it is more than a wave's share
+// of the E entries. us, parts of a wave's share and so: 22 orbitals, 64x1, 48 samples 298, 183; 28
+// orbitals, 64x3, 16 samples 352, 220; 24 orbitals, 128x1, 32 samples 246, 203. Geometric means over 16
+// to 60 orbitals, 1 to 192 samples, for 150, 600, 1000, 2200 entries: 64x1 1.01, 1.06, 1.11, 1.13 times as
+// fast; 128x2 1.01, 1.09, 1.10, 1.05; 192x2 1.01, 1.02, 0.98, 0.87; 256x2 1.01, 0.93, 0.84, 0.74. FP64, whose
+// entries take longer beside the parents: a wave's share.
+double part_entries(const AnsatzGeom& G) {
+  if (G.precision != ELOCAL_BF16) return 0.0;
+  const int w = G.md.nout[0];
+  return w <= 64 ? 2000.0 : w <= 128 ? 1000.0 : 200.0;
+}
+
 // Work items of the prefix-shared evaluation. A sample's sum is over groups of consecutive
 // segments, as many groups as the plain path has items (so the partial sums take no more
 // memory), and an item is one of them. A batch with few of these has an item per segment, or
-// 2^k items where a segment has more entries than one wave's share of the batch: the launch is
+// 2^k items where a segment has more entries than a part should (part_entries): the launch is
 // else as long as its longest segment (24 orbitals, 64 samples: 456 us whole, 356 in parts, 428
 // and 584 in parts of a half and a third of the share, because a part runs its segment's
 // parents again; 60 orbitals, 8 samples: 2.67 ms, 2.65). The sums are the same bit for bit:
@@ -579,7 +593,7 @@ elocal_status make_eval_geom(const elocal_ctx* h, const elocal_ansatz* a, Ansatz
 constexpr int64_t kFineItems = 131072;   // a few tens of items per wave of the chip
 constexpr int kMaxLgParts = 4;
 constexpr int64_t kMaxTickets = 1ll << 31;
-void plan_items(const elocal_ctx* h, int64_t B, double chip, bool split, EvalPlan& p) {
+void plan_items(const elocal_ctx* h, const AnsatzGeom& G, int64_t B, double chip, bool split, EvalPlan& p) {
   PrefixDev& X = p.px;
   const uint32_t nseg = X.seg0[X.nblk];
   const uint32_t group = h->tune_groups > 0 ? (uint32_t)std::min<int64_t>(h->tune_groups, nseg)
@@ -602,7 +616,8 @@ void plan_items(const elocal_ctx* h, int64_t B, double chip, bool split, EvalPla
       const double sb = pb * pb * bv * bv / 2 + (1 - pb) * (1 - pb) * bo * bo / 2 + 2 * pb * (1 - pb) * mixed;
       return 0.5 * cross + 0.25 * (sa + sb);
     };
-    const double share = std::max(64.0, (double)B * h->sys.C / (chip * p.waves * h->cu_count));
+    const double even = (double)B * h->sys.C / (chip * p.waves * h->cu_count);
+    const double share = std::max({64.0, even, std::sqrt(part_entries(G) * even)});
     for (int c = 0; c < X.nblk; ++c) {
       int k = 0;
       while (k < kMaxLgParts && ((int64_t)nseg * B << (k + 1)) <= kFineItems &&
@@ -703,7 +718,7 @@ EvalPlan plan_eval(const elocal_ctx* h, const AnsatzGeom& G, int64_t B, int64_t 
   }
   if (p.prefix) {
     plan_prefix(h, G, p.px);
-    plan_items(h, B, chip, split, p);
+    plan_items(h, G, B, chip, split, p);
     if (G.precision == ELOCAL_BF16) {
       size_t wb = 0;
       plan_prefix_lds(G, G.hmax, p.waves, G.bbytes, p, wb);

@@ -96,6 +96,19 @@ def test_items_in_parts_only_where_waves_are_idle(plan, n, na, nb, widths, sampl
     plan.host_free(h)
 
 
+@pytest.mark.parametrize("n,widths,samples", [(21, (64,), 32), (22, (64,), 48), (24, (64,), 24), (28, (64,) * 3, 32),
+                                              (24, (128,), 48), (20, (128, 128), 48)])
+def test_few_samples_of_narrow_networks_run_few_parts(plan, n, widths, samples):
+    """Every part of a segment runs the segment's parents again, which narrow networks take longer
+    for than for a part's entries: about one part per wave, not four or five."""
+    h = ctypes.c_void_p(plan.host_handle(n, n // 2, n // 2))
+    out = (ctypes.c_int64 * 4)()
+    a = ansatz(widths, elocal.BF16)
+    items = plan.host_items(h, ctypes.byref(a), ctypes.c_int64(samples), out)
+    plan.host_free(h)
+    assert 0 < items <= 2 * out[3]
+
+
 def test_units_up_to_a_degree_in_closed_form(plan):
     for n in (2, 3, 10, 33, 64):
         for w in (32, 96, 256):

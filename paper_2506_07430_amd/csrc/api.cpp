@@ -572,14 +572,15 @@ elocal_status make_eval_geom(const elocal_ctx* h, const elocal_ansatz* a, Ansatz
 // runs its segment's parents again, E / L times their time over all waves. The sum is least at
 // L = sqrt(parents' time in entries * E / waves), which is taken where it is more than a wave's share
 // of the E entries. us, parts of a wave's share and so: 22 orbitals, 64x1, 48 samples 298, 183; 28
-// orbitals, 64x3, 16 samples 352, 220; 24 orbitals, 128x1, 32 samples 246, 203. Geometric means over 16
-// to 60 orbitals, 1 to 192 samples, for 150, 600, 1000, 2200 entries: 64x1 1.01, 1.06, 1.11, 1.13 times as
-// fast; 128x2 1.01, 1.09, 1.10, 1.05; 192x2 1.01, 1.02, 0.98, 0.87; 256x2 1.01, 0.93, 0.84, 0.74. FP64, whose
-// entries take longer beside the parents: a wave's share.
-double part_entries(const AnsatzGeom& G) {
-  if (G.precision != ELOCAL_BF16) return 0.0;
-  const int w = G.md.nout[0];
-  return w <= 64 ? 2000.0 : w <= 128 ? 1000.0 : 200.0;
+// orbitals, 64x3, 16 samples 352, 220; 24 orbitals, 128x1, 32 samples 246, 203. The parents' time in
+// entries by geometric means over 1 to 192 samples, for 600, 1000, 2200 entries: 21 orbitals, width 64
+// 1.18, 1.24, 1.32 times as fast, width 128 1.13, 1.15, 1.09; 28: 1.11, 1.17, 1.20; 1.10, 1.11, 1.03; 40: 1.02,
+// 1.05, 1.04; 1.05, 1.05, 0.96; 60: 1.03, 1.03, 1.00; 1.02, 0.97, 0.87; width 256, 21 orbitals 0.93, 0.82, 0.72
+// (150: 1.00). Width 256 and FP64, whose entries take longer beside the parents: a wave's share.
+double part_entries(const elocal_ctx* h, const AnsatzGeom& G) {
+  if (G.precision != ELOCAL_BF16 || G.hmax > 128) return 0.0;
+  const double f = std::min(1.0, 28.0 / h->sys.n);
+  return (G.hmax <= 64 ? 2000.0 : 1000.0) * f * f;
 }
 
 // Work items of the prefix-shared evaluation. A sample's sum is over groups of consecutive
@@ -617,7 +618,7 @@ void plan_items(const elocal_ctx* h, const AnsatzGeom& G, int64_t B, double chip
       return 0.5 * cross + 0.25 * (sa + sb);
     };
     const double even = (double)B * h->sys.C / (chip * p.waves * h->cu_count);
-    const double share = std::max({64.0, even, std::sqrt(part_entries(G) * even)});
+    const double share = std::max({64.0, even, std::sqrt(part_entries(h, G) * even)});
     for (int c = 0; c < X.nblk; ++c) {
       int k = 0;
       while (k < kMaxLgParts && ((int64_t)nseg * B << (k + 1)) <= kFineItems &&

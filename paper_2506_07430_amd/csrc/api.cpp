@@ -543,6 +543,7 @@ void plan_prefix_lds(const AnsatzGeom& G, int kernel_hmax, int waves, size_t bia
 //   BF16, 1024 samples   64x1   16 orbitals r 11.7 0.41 0.57   20 r 18 1.01 1.03   22 r 22 1.68 1.45
 //                        128x2  12 r 6.6 0.28 0.44   16 r 11.7 0.70 0.81   20 r 15 1.48 1.41   24 r 26 3.75 2.73
 //                        256x3  12 r 6.6 0.86 1.20   18 r 11.6, 192 samples 0.64 0.63
+//   BF16, 19 orbitals    128x1  r 16.4, 16, 128, 400, 1024 samples 0.06 0.12, 0.18 0.25, 0.53 0.50, 1.08 1.08
 //   BF16, 32 samples     256x1  40 r 41 (a quarter filled) 0.97 1.36   34 r 44 (a third) 0.89 0.64
 //                        64x2   60 r 67 (a fifth) 2.53 3.58   60 r 131 (a third) 4.75 3.49
 //   FP64, 1024 samples   64x2   12 r 3.6 0.49 0.49, r 6.6 0.84 0.64   64x1  10 r 4.6 0.27 0.37   128x2  10 r 4.6 0.79 0.74
@@ -552,7 +553,8 @@ void plan_prefix_lds(const AnsatzGeom& G, int kernel_hmax, int waves, size_t bia
 bool prefix_pays(const elocal_ctx* h, const AnsatzGeom& G) {
   const double n = h->sys.n, r = (h->sys.C - 1.0) / (n * (2.0 * n - 1.0));
   const int w = G.md.nout[0];
-  if (G.precision == ELOCAL_BF16) return r >= (w <= 64 ? 19.0 : w <= 128 ? 15.0 : 11.0) && 37.0 * r >= n * n;
+  if (G.precision == ELOCAL_BF16)
+    return r >= (w <= 64 ? 19.0 : w <= 128 ? (G.md.L == 1 ? 17.4 : 15.0) : 11.0) && 37.0 * r >= n * n;
   return r >= (w <= 128 ? 4.5 : 8.0) && 80.0 * r >= n * n;
 }
 

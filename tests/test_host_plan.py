@@ -66,6 +66,16 @@ def test_few_electrons_run_every_entry(plan, n, na, nb, widths, precision):
     plan.host_free(h)
 
 
+@pytest.mark.parametrize("n,na,nb,widths", [(19, 9, 9, (128,)), (19, 9, 10, (96,)), (18, 9, 9, (128,))])
+def test_one_hidden_layer_runs_every_entry_up_to_19_orbitals(plan, n, na, nb, widths):
+    """The parents of so few entries take longer than one layer's products: 16 samples 63 us by
+    themselves and 118 shared, 1024 samples 1.08 ms either way."""
+    h = ctypes.c_void_p(plan.host_handle(n, na, nb))
+    a = ansatz(widths, elocal.BF16)
+    assert plan.host_prefix(h, ctypes.byref(a)) == 0
+    plan.host_free(h)
+
+
 def test_systems_of_the_gpu_test_take_the_shared_evaluation(plan):
     from tests.test_gpu_multi_prefix import BF16, FP64
     from tests.test_gpu_prefix_rule import SHAPES

@@ -81,3 +81,17 @@ def test_64_orbitals_few_electrons_match_oracle(precision):
     err = np.max(np.abs(e[:, 0] + 1j * e[:, 1] - ref))
     print(f"precision={precision}: max|dE_loc|={err:.2e}", flush=True)
     assert err <= (1e-10 * np.max(np.abs(ref)) if precision == elocal.FP64 else 1e-5)
+
+
+@pytest.mark.parametrize("n,na,nb,widths", [(22, 11, 11, (64,)), (24, 11, 12, (96, 96)), (34, 12, 11, (128,)),
+                                            (40, 14, 13, (64, 64))])
+def test_parts_of_segments_give_the_same_bits(n, na, nb, widths):
+    """Segments are cut into parts by the batch and the network: whatever the cut, a sample's
+    energy is the same bit for bit (1, 5 and 20 samples against all 48)."""
+    p = synth.random_problem(n, na, nb, widths, seed=795 + n, n_chol=4, decay=5.0, samples=48)
+    th_dev, th = theta_for(p.theta, elocal.BF16)
+    x = words_to_dev(ansatz_samples(p, 48, 796, th))
+    ham, ans = make_ham(p), elocal.Ansatz(widths, th_dev, elocal.BF16)
+    whole = ham.eval(ans, x)[0].clone()
+    for b in (1, 5, 20):
+        assert torch.equal(ham.eval(ans, x[:b].contiguous())[0], whole[:b]), b
